@@ -36,6 +36,8 @@
 namespace rp {
 
 int scan_i32(const int32_t* in, int64_t n, int32_t* out, int32_t* total, hipStream_t s);
+int64_t scan_i32_scratch(int64_t n);
+int scan_i32_enqueue(const int32_t* in, int64_t n, int32_t* out, int32_t* scratch, hipStream_t s);
 
 namespace {
 
@@ -98,6 +100,7 @@ amg_pick(int32_t n, const int32_t* row_ptr, const int32_t* col, const double* va
 // rows that picked each other pair up; count[0] += pairs (two rows each)
 __global__ void __launch_bounds__(AB)
 amg_pair(int32_t n, const int32_t* pick, int32_t* mate, uint32_t* count) {
+    __shared__ uint32_t red[AB / 64];
     uint32_t c = 0;
     for (int32_t i = blockIdx.x * AB + threadIdx.x; i < n; i += gridDim.x * AB) {
         const int32_t j = pick[i];
@@ -106,7 +109,9 @@ amg_pair(int32_t n, const int32_t* pick, int32_t* mate, uint32_t* count) {
             ++c;
         }
     }
-    if (c) atomicAdd(count, c);
+    // one add per block: an add per thread made every round wait on one word
+    c = block_sum<uint32_t, AB>(c, red);
+    if (threadIdx.x == 0 && c) atomicAdd(count, c);
 }
 
 __global__ void __launch_bounds__(AB)
@@ -213,6 +218,35 @@ amg_cfill(int32_t nc, const int32_t* kstart, const uint64_t* keys, const int32_t
         c_diag[I] = diag;
         if (I == nc - 1) cptr[e] = kstart[nc];
     }
+}
+
+// ---- two aggregations composed (AmgLevel::map, ::rows) -----------------------
+// fine rows of the k-th entry of the middle level's member list
+__global__ void __launch_bounds__(AB)
+amg_link_count(int32_t nm, const int32_t* mid_mem, const int32_t* mem_ptr, int32_t* cnt) {
+    for (int32_t k = blockIdx.x * AB + threadIdx.x; k < nm; k += gridDim.x * AB) {
+        const int32_t m = mid_mem[k];
+        cnt[k] = mem_ptr[m + 1] - mem_ptr[m];
+    }
+}
+
+__global__ void __launch_bounds__(AB)
+amg_link_rows(int32_t nm, const int32_t* mid_mem, const int32_t* mem_ptr, const int32_t* mem, const int32_t* pos,
+              int32_t* rows) {
+    for (int32_t k = blockIdx.x * AB + threadIdx.x; k < nm; k += gridDim.x * AB) {
+        const int32_t m = mid_mem[k], a0 = mem_ptr[m], len = mem_ptr[m + 1] - a0;
+        for (int32_t j = 0; j < len; ++j) rows[pos[k] + j] = mem[a0 + j] | (j == 0 ? INT32_MIN : 0);
+    }
+}
+
+__global__ void __launch_bounds__(AB)
+amg_link_ptr(int32_t nc, const int32_t* mid_mem_ptr, const int32_t* pos, int32_t* rows_ptr) {
+    for (int32_t I = blockIdx.x * AB + threadIdx.x; I <= nc; I += gridDim.x * AB) rows_ptr[I] = pos[mid_mem_ptr[I]];
+}
+
+__global__ void __launch_bounds__(AB)
+amg_link_map(int32_t n, const int32_t* agg, const int32_t* mid_agg, int32_t* map) {
+    for (int32_t i = blockIdx.x * AB + threadIdx.x; i < n; i += gridDim.x * AB) map[i] = mid_agg[agg[i]];
 }
 
 // ---- value refresh -----------------------------------------------------------
@@ -328,20 +362,61 @@ amg_resid(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict_
 // (coalesced over the entries, every load of a lane issued before the first
 // product) into LDS, then each lane sums its row's products in column order
 // from 0: the same single roundings as the serial row sum.  A chunk with
-// more than WCAP entries is summed straight from memory, a lane per row.
+// more than wcap() entries is summed straight from memory, a lane per row.
 constexpr int WB = 64;            // threads per block: one wavefront
-constexpr int WCAP = 1024;        // staged products per chunk
-constexpr int WU = WCAP / WB;     // loads per lane
 
+// staged products per chunk of CR rows (16 or 24 per row; more fall back to memory)
+template <int CR>
+constexpr int wcap() { return CR == 64 ? 1024 : 768; }
+
+// x of the level, and x with the coarse correction e added on the fly
 template <typename T>
-__device__ __forceinline__ T wave_row_sum(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                                          const T* __restrict__ val, const T* __restrict__ x, int32_t r0,
-                                          int32_t nr, T* prod) {
+struct PlainX {
+    const T* x;
+    __device__ __forceinline__ T operator()(int32_t i) const { return x[i]; }
+};
+template <typename T>
+struct CorrectedX {
+    const T* x;
+    const T* e;
+    const int32_t* map;
+    __device__ __forceinline__ T operator()(int32_t i) const {
 #pragma clang fp contract(off)
+        return x[i] + e[map[i]];
+    }
+};
+
+// sum of p[0 .. n) from 0, ascending; four reads of LDS in flight
+template <typename T>
+__device__ __forceinline__ T serial_sum(const T* p, int32_t n) {
+#pragma clang fp contract(off)
+    T s = T(0);
+    int32_t j = 0;
+    for (; j + 4 <= n; j += 4) {
+        const T a = p[j], b = p[j + 1], c = p[j + 2], d = p[j + 3];
+        s += a;
+        s += b;
+        s += c;
+        s += d;
+    }
+    for (; j < n; ++j) s += p[j];
+    return s;
+}
+
+template <typename T, int CR, typename X>
+__device__ __forceinline__ T wave_row_sum(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+                                          const T* __restrict__ val, const X& x, int32_t r0, int32_t nr, T* prod) {
+#pragma clang fp contract(off)
+    constexpr int WU = wcap<CR>() / WB;   // loads per lane
     const int32_t t = threadIdx.x;
     const int32_t e0 = row_ptr[r0], e1 = row_ptr[r0 + nr];
+    int32_t rs = 0, re = 0;
+    if (t < nr) {
+        rs = row_ptr[r0 + t];
+        re = row_ptr[r0 + t + 1];
+    }
     T s = T(0);
-    if (e1 - e0 <= WCAP) {
+    if (e1 - e0 <= wcap<CR>()) {
         int32_t cv[WU];
         T vv[WU], xv[WU];
 #pragma unroll
@@ -351,18 +426,17 @@ __device__ __forceinline__ T wave_row_sum(const int32_t* __restrict__ row_ptr, c
             vv[u] = e < e1 ? val[e] : T(0);
         }
 #pragma unroll
-        for (int u = 0; u < WU; ++u) xv[u] = (e0 + t + u * WB < e1) ? x[cv[u]] : T(0);
+        for (int u = 0; u < WU; ++u) xv[u] = (e0 + t + u * WB < e1) ? x(cv[u]) : T(0);
 #pragma unroll
         for (int u = 0; u < WU; ++u) {
             const int32_t e = e0 + t + u * WB;
             if (e < e1) prod[e - e0] = vv[u] * xv[u];
         }
         __syncthreads();   // one wave: orders its LDS writes before the reads
-        if (t < nr)
-            for (int32_t e = row_ptr[r0 + t]; e < row_ptr[r0 + t + 1]; ++e) s += prod[e - e0];
+        s = serial_sum(prod + (rs - e0), re - rs);
         __syncthreads();   // prod is refilled by the next chunk
-    } else if (t < nr) {
-        for (int32_t e = row_ptr[r0 + t]; e < row_ptr[r0 + t + 1]; ++e) s += val[e] * x[col[e]];
+    } else {
+        for (int32_t e = rs; e < re; ++e) s += val[e] * x(col[e]);
     }
     return s;
 }
@@ -374,12 +448,12 @@ amg_csr_resid(int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __r
               const T* __restrict__ val, const T* __restrict__ x, const T* __restrict__ r, T* __restrict__ t,
               const int32_t* gate) {
 #pragma clang fp contract(off)
-    __shared__ T prod[WCAP];
+    __shared__ T prod[wcap<CR>()];
     if (gate && *gate < 0) return;
     const int32_t nch = (n + CR - 1) / CR;
     for (int32_t c = xcd_block(); c < nch; c += gridDim.x) {
         const int32_t r0 = c * CR, nr = min(CR, n - r0);
-        const T s = wave_row_sum<T>(row_ptr, col, val, x, r0, nr, prod);
+        const T s = wave_row_sum<T, CR>(row_ptr, col, val, PlainX<T>{x}, r0, nr, prod);
         if ((int32_t)threadIdx.x < nr) {
             const int32_t i = r0 + threadIdx.x;
             t[i] = r[i] - s;
@@ -387,22 +461,23 @@ amg_csr_resid(int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __r
     }
 }
 
-// y = x + omega (dinv (r - A x)) on a coarse level
-template <typename T, int CR>
+// y = x' + omega (dinv (r - A x')) on a coarse level; x' = x, or with the
+// coarse correction (X = CorrectedX: x + e[map], formed at every use)
+template <typename T, int CR, typename X>
 __global__ void __launch_bounds__(WB)
 amg_csr_post(int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-             const T* __restrict__ val, const T* __restrict__ x, const T* __restrict__ r,
-             const T* __restrict__ dinv, T omega, T* __restrict__ y, const int32_t* gate) {
+             const T* __restrict__ val, X x, const T* __restrict__ r, const T* __restrict__ dinv, T omega,
+             T* __restrict__ y, const int32_t* gate) {
 #pragma clang fp contract(off)
-    __shared__ T prod[WCAP];
+    __shared__ T prod[wcap<CR>()];
     if (gate && *gate < 0) return;
     const int32_t nch = (n + CR - 1) / CR;
     for (int32_t c = xcd_block(); c < nch; c += gridDim.x) {
         const int32_t r0 = c * CR, nr = min(CR, n - r0);
-        const T s = wave_row_sum<T>(row_ptr, col, val, x, r0, nr, prod);
+        const T s = wave_row_sum<T, CR>(row_ptr, col, val, x, r0, nr, prod);
         if ((int32_t)threadIdx.x < nr) {
             const int32_t i = r0 + threadIdx.x;
-            y[i] = x[i] + omega * (dinv[i] * (r[i] - s));
+            y[i] = x(i) + omega * (dinv[i] * (r[i] - s));
         }
     }
 }
@@ -418,43 +493,73 @@ int chunk_grid(int64_t n, int cr) {
     return (int)std::max<int64_t>(N_XCD, std::min<int64_t>(g, 16384));
 }
 
-// rc[I] = sum of v over the members of aggregate I, ascending
+// rc[I] = the restricted v of coarse row I (its rows in the list's order, see
+// AmgLevel::rows); xc (nullable): the first sweep of the coarse level,
+// xc = omega (dinv_c rc).  A block takes RI coarse rows; its threads gather
+// the listed rows' values together into LDS (each fine row is read once, a
+// lane per row), then a thread per coarse row adds its own.
+constexpr int RI = 192;          // coarse rows per block
+constexpr int RU = 4;            // gathers per thread and pass
+constexpr int RCAP = RU * AB;    // listed rows per pass (4.6 per coarse row on average)
+
 template <typename T>
 __global__ void __launch_bounds__(AB)
-amg_restrict(int32_t nc, const int32_t* __restrict__ mem_ptr, const int32_t* __restrict__ mem,
-             const T* __restrict__ v, T* __restrict__ rc, const int32_t* gate) {
+amg_restrict(int32_t nc, const int32_t* __restrict__ rows_ptr, const int32_t* __restrict__ rows,
+             const T* __restrict__ v, T* __restrict__ rc, const T* __restrict__ dinv_c, T omega,
+             T* __restrict__ xc, const int32_t* gate) {
 #pragma clang fp contract(off)
+    __shared__ T tv[RCAP];
+    __shared__ uint8_t tn[RCAP];
     if (gate && *gate < 0) return;
-    constexpr int M = 8;   // aggregates up to M rows: every load issued first
-    for (int32_t I = blockIdx.x * AB + threadIdx.x; I < nc; I += gridDim.x * AB) {
-        const int32_t a0 = mem_ptr[I], a1 = mem_ptr[I + 1];
-        T s = T(0);
-        if (a1 - a0 <= M) {
-            int32_t mi[M];
-            T vv[M];
-#pragma unroll
-            for (int u = 0; u < M; ++u) mi[u] = a0 + u < a1 ? mem[a0 + u] : 0;
-#pragma unroll
-            for (int u = 0; u < M; ++u) vv[u] = a0 + u < a1 ? v[mi[u]] : T(0);
-#pragma unroll
-            for (int u = 0; u < M; ++u)
-                if (a0 + u < a1) s += vv[u];
-        } else {
-            for (int32_t m = a0; m < a1; ++m) s += v[mem[m]];
+    const int32_t t = threadIdx.x;
+    const int32_t nb = (nc + RI - 1) / RI;
+    for (int32_t c = xcd_block(); c < nb; c += gridDim.x) {
+        const int32_t I0 = c * RI, nI = min(RI, nc - I0);
+        const int32_t f0 = rows_ptr[I0], f1 = rows_ptr[I0 + nI];
+        int32_t fa = 0, fb = 0;
+        if (t < nI) {
+            fa = rows_ptr[I0 + t];
+            fb = rows_ptr[I0 + t + 1];
         }
-        rc[I] = s;
+        T s = T(0), s1 = T(0);
+        for (int32_t base = f0; base < f1; base += RCAP) {
+            int32_t k[RU];
+            T vv[RU];
+#pragma unroll
+            for (int u = 0; u < RU; ++u) k[u] = base + t + u * AB < f1 ? rows[base + t + u * AB] : 0;
+#pragma unroll
+            for (int u = 0; u < RU; ++u) vv[u] = base + t + u * AB < f1 ? v[k[u] & INT32_MAX] : T(0);
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
+                tv[t + u * AB] = vv[u];
+                tn[t + u * AB] = k[u] < 0;
+            }
+            __syncthreads();
+            for (int32_t f = max(fa, base); f < min(fb, base + RCAP); ++f) {
+                if (tn[f - base]) {
+                    s += s1;
+                    s1 = T(0);
+                }
+                s1 += tv[f - base];
+            }
+            __syncthreads();
+        }
+        if (t < nI) {
+            s += s1;
+            rc[I0 + t] = s;
+            if (xc) xc[I0 + t] = omega * (dinv_c[I0 + t] * s);
+        }
     }
 }
 
-// x += e[agg]  (ADD) or  y = e[agg]
-template <typename T, bool ADD>
+// x += e[map]
+template <typename T>
 __global__ void __launch_bounds__(AB)
-amg_prolong(int32_t n, const int32_t* __restrict__ agg, const T* __restrict__ e, T* __restrict__ y,
+amg_prolong(int32_t n, const int32_t* __restrict__ map, const T* __restrict__ e, T* __restrict__ x,
             const int32_t* gate) {
 #pragma clang fp contract(off)
     if (gate && *gate < 0) return;
-    for (int32_t i = blockIdx.x * AB + threadIdx.x; i < n; i += gridDim.x * AB)
-        y[i] = ADD ? y[i] + e[agg[i]] : e[agg[i]];
+    for (int32_t i = blockIdx.x * AB + threadIdx.x; i < n; i += gridDim.x * AB) x[i] = x[i] + e[map[i]];
 }
 
 // y = x + omega (dinv (r - A x)); PART: partials of (r, y) -> PART_RZ and,
@@ -532,35 +637,45 @@ amg_coarse(int32_t n, const T* __restrict__ cinv, const T* __restrict__ r, T* __
 // The tail of the V-cycle: every level from the first one with at most
 // AMG_TAIL_ROWS rows down to the coarsest, in one workgroup.  Each step is
 // the corresponding kernel's above, row by row with the same operations in
-// the same order (rows' products summed in column order from 0, members in
-// ascending order, the coarsest inverse times r with j ascending), and the
+// the same order (rows' products summed in column order from 0, listed rows
+// in their order, the coarsest inverse times r with j ascending), and the
 // workgroup barrier stands where the level kernels had a launch boundary.
 // On the small levels a launch costs more than its work.
 // ---------------------------------------------------------------------------
 constexpr int64_t AMG_TAIL_ROWS = RP_AMG_TAIL_ROWS;
-constexpr int TB = 1024;   // threads of the tail workgroup
+constexpr int TB = 1024;              // threads of the tail workgroup
+// Rows of the tail's steps together, and words of their lists and row_ptr, at
+// most for the form that keeps vectors and lists in LDS (64 KB in FP64).  Rows
+// fall by four or more from step to step, so nearly every hierarchy fits; one
+// that coarsens by a few rows a level (a chain of growing couplings) does not.
+constexpr int TAIL_LDS_ROWS = 2048;
+constexpr int TAIL_LDS_IDX = 6144;
 
+// One level the tail stops at: its first level, then the even ones, then the
+// coarsest.  A first level of odd number only restricts and prolongs.
 template <typename T>
-struct TailLevel {
-    int32_t n;
+struct TailStep {
+    int32_t n, nnz;
+    int32_t smooth;           // even level above the coarsest
+    int32_t at;               // first element of the level in the tail's vectors
+    int32_t idx;              // first word of its lists in LDS
     const int32_t* row_ptr;
     const int32_t* col;
     const T* val;
     const T* dinv;
-    const int32_t* agg;       // all tail levels but the coarsest
-    const int32_t* mem_ptr;
-    const int32_t* mem;
-    T* v[4];                  // in, x, t, out (x and t on smoothed levels)
+    const int32_t* rows_ptr;  // all steps but the coarsest, as in AmgLevel
+    const int32_t* rows;
+    const int32_t* map;
 };
 
 // row i of A x: U entries per trip, every load of a trip issued before its
 // first product; the products are added in column order from 0
 template <typename T>
-__device__ __forceinline__ T tail_row_sum(const TailLevel<T>& L, const T* __restrict__ x, int32_t i) {
+__device__ __forceinline__ T tail_row_sum(const TailStep<T>& L, const int32_t* row_ptr, const T* x, int32_t i) {
 #pragma clang fp contract(off)
-    constexpr int U = 8;
+    constexpr int U = 12;
     T s = T(0);
-    const int32_t e0 = L.row_ptr[i], e1 = L.row_ptr[i + 1];
+    const int32_t e0 = row_ptr[i], e1 = row_ptr[i + 1];
     for (int32_t eb = e0; eb < e1; eb += U) {
         int32_t c[U];
         T v[U], xv[U];
@@ -579,59 +694,121 @@ __device__ __forceinline__ T tail_row_sum(const TailLevel<T>& L, const T* __rest
     return s;
 }
 
-// y = V_lt(r) on levels lt .. last (lv[0] is level lt; r in lv[0].v[0], y
-// to lv[0].v[3])
-template <typename T>
+// one load per 128-byte line of a[0 .. n), folded into h (so that it is not dropped)
+template <typename E>
+__device__ __forceinline__ void touch(const E* a, int32_t n, uint32_t& h) {
+    constexpr int PER = 128 / sizeof(E);
+    for (int32_t i = threadIdx.x * PER; i < n; i += TB * PER) h |= *reinterpret_cast<const uint32_t*>(a + i);
+}
+
+__device__ __forceinline__ void tail_copy(int32_t* dst, const int32_t* src, int32_t n) {
+    for (int32_t i = threadIdx.x; i < n; i += TB) dst[i] = src[i];
+}
+
+// y0 = V_lt(r0) over the tail's ns steps.  LV: vectors and lists live in LDS,
+// else in work and where the hierarchy has them.  By the time the tail runs,
+// the larger levels have pushed its matrices out of the die's L2, and every
+// step would wait for memory several times over; so the workgroup first
+// touches all of them, together.  One workgroup is bound by the latency of
+// its chain of steps: 55 us after a 160^3 fine level with everything in
+// memory, 34 with the vectors in LDS and the touches, 29 with the lists too.
+template <typename T, bool LV>
 __global__ void __launch_bounds__(TB)
-amg_tail(int32_t lt, int32_t last, const TailLevel<T>* __restrict__ lv, const T* __restrict__ cinv, T omega,
-         const int32_t* gate) {
+amg_tail(int32_t ns, const TailStep<T>* __restrict__ st, const T* __restrict__ cinv, T omega,
+         const T* __restrict__ r0, T* __restrict__ y0, T* work, int32_t total, const int32_t* gate) {
 #pragma clang fp contract(off)
+    __shared__ T lds[LV ? 2 * TAIL_LDS_ROWS + AMG_TAIL_ROWS : 1];
+    __shared__ int32_t idx[LV ? TAIL_LDS_IDX : 1];
     if (gate && *gate < 0) return;
     const int32_t t = threadIdx.x;
-    for (int32_t l = lt; l < last; ++l) {
-        const TailLevel<T>& L = lv[l - lt];
-        const TailLevel<T>& C = lv[l - lt + 1];
-        const T* r = L.v[0];
-        const T* src = r;   // what restricts to the coarse level
-        if (l % 2 == 0) {
-            for (int32_t i = t; i < L.n; i += TB) L.v[1][i] = omega * (L.dinv[i] * r[i]);
+    const int32_t span = LV ? TAIL_LDS_ROWS : total;
+    // right-hand sides (results on the way up), iterates; one step's residual
+    T* const vr = LV ? lds : work;
+    T* const vx = vr + span;
+    T* const vt = vx + span;
+    uint32_t h = 0;
+    for (int32_t k = 0; k + 1 < ns; ++k) {
+        const TailStep<T>& S = st[k];
+        const int32_t nc = st[k + 1].n;
+        if (S.smooth) {
+            touch(S.col, S.nnz, h);
+            touch(S.val, S.nnz, h);
+            touch(S.dinv, S.n, h);
+        }
+        if (LV) {
+            tail_copy(idx + S.idx, S.rows_ptr, nc + 1);
+            tail_copy(idx + S.idx + nc + 1, S.rows, S.n);
+            tail_copy(idx + S.idx + nc + 1 + S.n, S.map, S.n);
+            if (S.smooth) tail_copy(idx + S.idx + nc + 1 + 2 * S.n, S.row_ptr, S.n + 1);
+        }
+    }
+    touch(cinv, st[ns - 1].n * st[ns - 1].n, h);
+    for (int32_t i = t; i < st[0].n; i += TB) {
+        const T ri = r0[i];
+        vr[i] = ri;
+        if (st[0].smooth) vx[i] = omega * (st[0].dinv[i] * ri);
+    }
+    asm volatile("" ::"v"(h));
+    __syncthreads();
+    for (int32_t k = 0; k + 1 < ns; ++k) {
+        const TailStep<T>& S = st[k];
+        const TailStep<T>& C = st[k + 1];
+        const int32_t* rows_ptr = LV ? idx + S.idx : S.rows_ptr;
+        const int32_t* rows = LV ? rows_ptr + C.n + 1 : S.rows;
+        const T* r = vr + S.at;
+        const T* src = r;   // what restricts to the next step
+        if (S.smooth) {
+            const int32_t* row_ptr = LV ? rows + 2 * S.n : S.row_ptr;
+            for (int32_t i = t; i < S.n; i += TB) vt[i] = r[i] - tail_row_sum(S, row_ptr, vx + S.at, i);
             __syncthreads();
-            for (int32_t i = t; i < L.n; i += TB) L.v[2][i] = r[i] - tail_row_sum(L, L.v[1], i);
-            __syncthreads();
-            src = L.v[2];
+            src = vt;
         }
         for (int32_t I = t; I < C.n; I += TB) {
-            T s = T(0);
-            for (int32_t m = L.mem_ptr[I]; m < L.mem_ptr[I + 1]; ++m) s += src[L.mem[m]];
-            C.v[0][I] = s;
+            T s = T(0), s1 = T(0);
+            for (int32_t f = rows_ptr[I]; f < rows_ptr[I + 1]; ++f) {
+                const int32_t q = rows[f];
+                if (q < 0) {
+                    s += s1;
+                    s1 = T(0);
+                }
+                s1 += src[q & INT32_MAX];
+            }
+            s += s1;
+            vr[C.at + I] = s;
+            if (C.smooth) vx[C.at + I] = omega * (C.dinv[I] * s);
         }
         __syncthreads();
     }
     {
-        const TailLevel<T>& L = lv[last - lt];
-        const int32_t n = L.n;
-        for (int32_t i = t; i < n; i += TB) {
-            T s = T(0);
-            for (int32_t j = 0; j < n; ++j) s += cinv[(int64_t)i * n + j] * L.v[0][j];
-            L.v[3][i] = s;
-        }
+        const TailStep<T>& L = st[ns - 1];
+        const int32_t n = L.n;   // at most AMG_COARSE_MAX
+        T* r = vr + L.at;
+        T s = T(0);
+        if (t < n)
+            for (int32_t j = 0; j < n; ++j) s += cinv[(int64_t)t * n + j] * r[j];
+        __syncthreads();
+        if (t < n) r[t] = s;
         __syncthreads();
     }
-    for (int32_t l = last - 1; l >= lt; --l) {
-        const TailLevel<T>& L = lv[l - lt];
-        const T* e = lv[l - lt + 1].v[3];
-        if (l % 2 == 1) {
-            for (int32_t i = t; i < L.n; i += TB) L.v[3][i] = e[L.agg[i]];
+    for (int32_t k = ns - 2; k >= 0; --k) {
+        const TailStep<T>& S = st[k];
+        const TailStep<T>& C = st[k + 1];
+        const int32_t* map = LV ? idx + S.idx + C.n + 1 + S.n : S.map;
+        const T* e = vr + C.at;
+        T* r = vr + S.at;
+        if (!S.smooth) {
+            for (int32_t i = t; i < S.n; i += TB) r[i] = e[map[i]];
         } else {
-            T* x = L.v[1];
-            for (int32_t i = t; i < L.n; i += TB) x[i] = x[i] + e[L.agg[i]];
+            const int32_t* row_ptr = LV ? map + S.n : S.row_ptr;
+            T* x = vx + S.at;
+            for (int32_t i = t; i < S.n; i += TB) x[i] = x[i] + e[map[i]];
             __syncthreads();
-            const T* r = L.v[0];
-            for (int32_t i = t; i < L.n; i += TB)
-                L.v[3][i] = x[i] + omega * (L.dinv[i] * (r[i] - tail_row_sum(L, x, i)));
+            for (int32_t i = t; i < S.n; i += TB)
+                r[i] = x[i] + omega * (S.dinv[i] * (r[i] - tail_row_sum(S, row_ptr, x, i)));
         }
         __syncthreads();
     }
+    for (int32_t i = t; i < st[0].n; i += TB) y0[i] = vr[i];
 }
 
 // the level-0 system of a hierarchy: the fused pattern (with its
@@ -665,6 +842,7 @@ struct Prec<double> {
     static double** vec(AmgLevel& L) { return L.vec64; }
     static const double* cinv(const AmgHier& h) { return h.cinv64; }
     static void*& tail(AmgHier& h) { return h.tail64; }
+    static double*& work(AmgHier& h) { return h.tail_work64; }
     static const double* val0(const Src& q) { return q.val64; }
     static const double* dinv0(const Src& q) { return q.dinv64; }
 };
@@ -675,6 +853,7 @@ struct Prec<float> {
     static float** vec(AmgLevel& L) { return L.vec32; }
     static const float* cinv(const AmgHier& h) { return h.cinv32; }
     static void*& tail(AmgHier& h) { return h.tail32; }
+    static float*& work(AmgHier& h) { return h.tail_work32; }
     static const float* val0(const Src& q) { return q.val32; }
     static const float* dinv0(const Src& q) { return q.dinv32; }
 };
@@ -685,29 +864,39 @@ int alloc_vectors(AmgHier& h) {
         AmgLevel& L = h.lev[l];
         T** v = Prec<T>::vec(L);
         const size_t bytes = sizeof(T) * (size_t)std::max<int64_t>(L.n, 1);
-        // in and out below level 0 (level 0 uses the solve's vectors); x and t
-        // on smoothed levels.  Each one is allocated once, so a call after a
-        // failed one completes the set.
-        const bool last = l == h.n_levels - 1;
-        const bool smooth = !last && l % 2 == 0;
+        // in and out down to the tail's first level (level 0 uses the solve's
+        // vectors); x and t above it; nothing on the odd levels above it,
+        // which the cycle steps over.  Each one is allocated once, so a call
+        // after a failed one completes the set.
+        if (l > h.tail_level || (l % 2 == 1 && l < h.tail_level)) continue;
         for (int k = 0; k < 4; ++k) {
-            const bool need = (k == 0 || k == 3) ? l > 0 : smooth;
+            const bool need = (k == 0 || k == 3) ? l > 0 : l < h.tail_level;
             if (need && !v[k]) RP_HIP_TRY(hipMalloc(&v[k], bytes));
         }
     }
-    // the tail's per-level pointers, once the vectors exist
+    // the tail's steps
     void*& tab = Prec<T>::tail(h);
     if (h.tail_level > 0 && !tab) {
-        std::vector<TailLevel<T>> tl;
-        for (int32_t l = h.tail_level; l < h.n_levels; ++l) {
-            AmgLevel& L = h.lev[l];
-            T** v = Prec<T>::vec(L);
-            tl.push_back(TailLevel<T>{(int32_t)L.n, L.row_ptr, L.col, Prec<T>::val(L), Prec<T>::dinv(L), L.agg,
-                                      L.mem_ptr, L.mem, {v[0], v[1], v[2], v[3]}});
+        std::vector<TailStep<T>> tl;
+        int64_t at = 0, idx = 0;
+        for (int32_t l = h.tail_level;; l = h.lev[l].target) {
+            const AmgLevel& L = h.lev[l];
+            const bool last = l == h.n_levels - 1;
+            const bool smooth = !last && l % 2 == 0;
+            tl.push_back(TailStep<T>{(int32_t)L.n, (int32_t)L.nnz, smooth, (int32_t)at, (int32_t)idx, L.row_ptr,
+                                     L.col, Prec<T>::val(L), Prec<T>::dinv(L), L.rows_ptr, L.rows, L.map});
+            at += L.n;
+            if (last) break;
+            idx += h.lev[L.target].n + 1 + 2 * L.n + (smooth ? L.n + 1 : 0);
         }
+        h.tail_steps = (int32_t)tl.size();
+        h.tail_rows = (int32_t)at;
+        h.tail_in_lds = at <= TAIL_LDS_ROWS && idx <= TAIL_LDS_IDX;
+        T*& w = Prec<T>::work(h);
+        if (!h.tail_in_lds && !w) RP_HIP_TRY(hipMalloc(&w, sizeof(T) * (size_t)(2 * at + AMG_TAIL_ROWS)));
         void* d = nullptr;
-        RP_HIP_TRY(hipMalloc(&d, sizeof(TailLevel<T>) * tl.size()));
-        const hipError_t e = hipMemcpy(d, tl.data(), sizeof(TailLevel<T>) * tl.size(), hipMemcpyHostToDevice);
+        RP_HIP_TRY(hipMalloc(&d, sizeof(TailStep<T>) * tl.size()));
+        const hipError_t e = hipMemcpy(d, tl.data(), sizeof(TailStep<T>) * tl.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(d);
             RP_HIP_TRY(e);
@@ -717,26 +906,92 @@ int alloc_vectors(AmgHier& h) {
     return RP_OK;
 }
 
-SpmvIdx level_idx(const Src& q, const AmgLevel& L, int32_t l) {
-    if (l == 0) return q.ix;
-    return SpmvIdx{L.row_ptr, L.col, nullptr, nullptr, nullptr};
+// Levels below level 0 with at most this many rows add the coarse correction
+// where the post-smoothing reads x: two more gathers per entry, a launch less.
+// Measured per level (FP64): 8.8 us against 4.9 + 4.7 at 24000 rows, even at
+// 10^5, 13.4 against 5 + 6 with launches at 10^5 and slower beyond.  (The
+// residual in the restriction's kernel, its rows in list order, was slower
+// above 20000 rows and gained nothing below.)
+constexpr int64_t AMG_FUSE_UP_ROWS = 1 << 16;
+
+// from the right-hand side r of even level l: residual after one sweep from
+// zero (x = omega (dinv r) is in v[1]) restricted to level L.target, with that
+// level's first sweep
+template <typename T>
+int cycle_down(AmgHier& h, const Src& q, int32_t l, const T* r, const int32_t* gate, hipStream_t s) {
+    AmgLevel& L = h.lev[l];
+    AmgLevel& C = h.lev[L.target];
+    const int32_t n = (int32_t)L.n, nc = (int32_t)C.n;
+    const T omega = (T)RP_AMG_OMEGA;
+    T** v = Prec<T>::vec(L);
+    T** cv = Prec<T>::vec(C);
+    T* xc = L.target < h.tail_level ? cv[1] : nullptr;   // the tail makes its own first sweep
+    const T* dinv_c = Prec<T>::dinv(C);
+    if (l == 0) {
+        hipLaunchKernelGGL(amg_resid<T>, dim3(spmv_grid(n)), dim3(SPMV_BLOCK), 0, s, n, q.ix, Prec<T>::val0(q),
+                           v[1], r, v[2], gate);
+    } else {
+        const int cr = chunk_rows(L), g = chunk_grid(n, cr);
+        if (cr == 64)
+            hipLaunchKernelGGL((amg_csr_resid<T, 64>), dim3(g), dim3(WB), 0, s, n, L.row_ptr, L.col,
+                               Prec<T>::val(L), v[1], r, v[2], gate);
+        else
+            hipLaunchKernelGGL((amg_csr_resid<T, 32>), dim3(g), dim3(WB), 0, s, n, L.row_ptr, L.col,
+                               Prec<T>::val(L), v[1], r, v[2], gate);
+    }
+    hipLaunchKernelGGL(amg_restrict<T>, dim3(chunk_grid(nc, RI)), dim3(AB), 0, s, nc, L.rows_ptr, L.rows, v[2], cv[0],
+                       dinv_c, omega, xc, gate);
+    RP_HIP_TRY(hipGetLastError());
+    return RP_OK;
 }
 
-// y = V_l(r) on stream s (level 0: r and y are the solve's vectors)
+// level l > 0 on the way up: y (v[3]) from x (v[1]), the right-hand side
+// (v[0]) and the correction e of level L.target
 template <typename T>
-int vcycle(AmgHier& h, const Src& q, int32_t l, const T* r, T* y, T* part, int32_t n_part, bool rr,
-           const int32_t* gate, hipStream_t s) {
+int cycle_up(AmgHier& h, int32_t l, const int32_t* gate, hipStream_t s) {
     AmgLevel& L = h.lev[l];
     const int32_t n = (int32_t)L.n;
     const T omega = (T)RP_AMG_OMEGA;
-    const bool want = part != nullptr;
-    if (l > 0 && l == h.tail_level) {
-        hipLaunchKernelGGL(amg_tail<T>, dim3(1), dim3(TB), 0, s, l, h.n_levels - 1,
-                           (const TailLevel<T>*)Prec<T>::tail(h), Prec<T>::cinv(h), omega, gate);
-        RP_HIP_TRY(hipGetLastError());
-        return RP_OK;
+    T** v = Prec<T>::vec(L);
+    const T* e = Prec<T>::vec(h.lev[L.target])[3];
+    const int cr = chunk_rows(L), g = chunk_grid(n, cr);
+#define RP_LAUNCH(CR, X, x)                                                                                   \
+    hipLaunchKernelGGL((amg_csr_post<T, CR, X>), dim3(g), dim3(WB), 0, s, n, L.row_ptr, L.col, Prec<T>::val(L), x, \
+                       v[0], Prec<T>::dinv(L), omega, v[3], gate)
+    if (n <= AMG_FUSE_UP_ROWS) {
+        const CorrectedX<T> x{v[1], e, L.map};
+        if (cr == 64) RP_LAUNCH(64, CorrectedX<T>, x);
+        else RP_LAUNCH(32, CorrectedX<T>, x);
+    } else {
+        hipLaunchKernelGGL(amg_prolong<T>, dim3(grid_of(n)), dim3(AB), 0, s, n, L.map, e, v[1], gate);
+        const PlainX<T> x{v[1]};
+        if (cr == 64) RP_LAUNCH(64, PlainX<T>, x);
+        else RP_LAUNCH(32, PlainX<T>, x);
     }
-    if (l == h.n_levels - 1) {
+#undef RP_LAUNCH
+    RP_HIP_TRY(hipGetLastError());
+    return RP_OK;
+}
+
+// y = V_0(r) on stream s: down the even levels to the tail, the tail, and up
+// again.  An odd level above the tail only restricts and prolongs, so the
+// cycle steps over it through the composed lists (AmgLevel::rows, ::map): a
+// small level's launch costs about 4.6 us whatever it does, and a large one's
+// vectors a pass each.  With the odd levels as launches of their own, a first
+// sweep per level and the tail's vectors in memory, a cycle took 355 us at
+// 131 x 117 x 142 cells, 598 at 160^3 and 1799 at 256^3 (FP64, 40 launches);
+// now 277, 461 and 1524 us (19 to 21 launches).  What is left is the fine
+// level's two products (38 + 39 us of the 277, 5.4 TB/s) and, below about
+// 10^5 rows, the launches.  swept: amg_first_sweep(h) already holds
+// omega (dinv r).
+template <typename T>
+int vcycle(AmgHier& h, const Src& q, const T* r, T* y, T* part, int32_t n_part, bool rr, bool swept,
+           const int32_t* gate, hipStream_t s) {
+    AmgLevel& L0 = h.lev[0];
+    const int32_t n = (int32_t)L0.n;
+    const T omega = (T)RP_AMG_OMEGA;
+    const bool want = part != nullptr;
+    if (h.n_levels == 1) {
 #define RP_LAUNCH(PT, RRF)                                                                                       \
     hipLaunchKernelGGL((amg_coarse<T, PT, RRF>), dim3(1), dim3(AB), 0, s, n, Prec<T>::cinv(h), r, y, part, n_part, \
                        gate)
@@ -747,47 +1002,33 @@ int vcycle(AmgHier& h, const Src& q, int32_t l, const T* r, T* y, T* part, int32
         RP_HIP_TRY(hipGetLastError());
         return RP_OK;
     }
-    AmgLevel& C = h.lev[l + 1];
-    const int32_t nc = (int32_t)C.n;
-    T** cv = Prec<T>::vec(C);
-    if (l % 2 == 1) {
-        hipLaunchKernelGGL(amg_restrict<T>, dim3(grid_of(nc)), dim3(AB), 0, s, nc, L.mem_ptr, L.mem, r, cv[0], gate);
-        RP_HIP_TRY(hipGetLastError());
-        RP_TRY(vcycle<T>(h, q, l + 1, cv[0], cv[3], nullptr, 0, false, gate, s));
-        hipLaunchKernelGGL((amg_prolong<T, false>), dim3(grid_of(n)), dim3(AB), 0, s, n, L.agg, cv[3], y, gate);
-        RP_HIP_TRY(hipGetLastError());
-        return RP_OK;
+    T** v = Prec<T>::vec(L0);
+    if (!swept)
+        hipLaunchKernelGGL(amg_pre<T>, dim3(grid_of(n)), dim3(AB), 0, s, n, r, Prec<T>::dinv0(q), v[1], omega,
+                           gate);
+    for (int32_t l = 0; l < h.tail_level; l = h.lev[l].target)
+        RP_TRY(cycle_down<T>(h, q, l, l == 0 ? r : Prec<T>::vec(h.lev[l])[0], gate, s));
+    {
+        T** tv = Prec<T>::vec(h.lev[h.tail_level]);
+#define RP_LAUNCH(LV)                                                                                          \
+    hipLaunchKernelGGL((amg_tail<T, LV>), dim3(1), dim3(TB), 0, s, h.tail_steps,               \
+                       (const TailStep<T>*)Prec<T>::tail(h), Prec<T>::cinv(h), omega, (const T*)tv[0], tv[3], \
+                       Prec<T>::work(h), h.tail_rows, gate)
+        if (h.tail_in_lds) RP_LAUNCH(true);
+        else RP_LAUNCH(false);
+#undef RP_LAUNCH
     }
-    T** v = Prec<T>::vec(L);
-    const T* val = l == 0 ? Prec<T>::val0(q) : Prec<T>::val(L);
-    const T* dinv = l == 0 ? Prec<T>::dinv0(q) : Prec<T>::dinv(L);
-    const SpmvIdx ix = level_idx(q, L, l);
-    const int gs = spmv_grid(n), cr = chunk_rows(L), gc = chunk_grid(n, cr);
-    hipLaunchKernelGGL(amg_pre<T>, dim3(grid_of(n)), dim3(AB), 0, s, n, r, dinv, v[1], omega, gate);
-    if (l == 0)
-        hipLaunchKernelGGL(amg_resid<T>, dim3(gs), dim3(SPMV_BLOCK), 0, s, n, ix, val, v[1], r, v[2], gate);
-    else if (cr == 64)
-        hipLaunchKernelGGL((amg_csr_resid<T, 64>), dim3(gc), dim3(WB), 0, s, n, L.row_ptr, L.col, val, v[1], r,
-                           v[2], gate);
-    else
-        hipLaunchKernelGGL((amg_csr_resid<T, 32>), dim3(gc), dim3(WB), 0, s, n, L.row_ptr, L.col, val, v[1], r,
-                           v[2], gate);
-    hipLaunchKernelGGL(amg_restrict<T>, dim3(grid_of(nc)), dim3(AB), 0, s, nc, L.mem_ptr, L.mem, v[2], cv[0], gate);
     RP_HIP_TRY(hipGetLastError());
-    RP_TRY(vcycle<T>(h, q, l + 1, cv[0], cv[3], nullptr, 0, false, gate, s));
-    hipLaunchKernelGGL((amg_prolong<T, true>), dim3(grid_of(n)), dim3(AB), 0, s, n, L.agg, cv[3], v[1], gate);
+    // the even levels above the tail, back to level 2
+    for (int32_t l = (h.tail_level - 1) & ~1; l > 0; l -= 2) RP_TRY(cycle_up<T>(h, l, gate, s));
+    hipLaunchKernelGGL(amg_prolong<T>, dim3(grid_of(n)), dim3(AB), 0, s, n, L0.map,
+                       (const T*)Prec<T>::vec(h.lev[L0.target])[3], v[1], gate);
 #define RP_LAUNCH(PT, RRF)                                                                                    \
-    hipLaunchKernelGGL((amg_post<T, PT, RRF>), dim3(gs), dim3(SPMV_BLOCK), 0, s, n, ix, val, v[1], r, dinv, omega, \
-                       y, part, gate)
+    hipLaunchKernelGGL((amg_post<T, PT, RRF>), dim3(spmv_grid(n)), dim3(SPMV_BLOCK), 0, s, n, q.ix, Prec<T>::val0(q), \
+                       v[1], r, Prec<T>::dinv0(q), omega, y, part, gate)
     if (want && rr) RP_LAUNCH(true, true);
     else if (want) RP_LAUNCH(true, false);
-    else if (l == 0) RP_LAUNCH(false, false);
-    else if (cr == 64)
-        hipLaunchKernelGGL((amg_csr_post<T, 64>), dim3(gc), dim3(WB), 0, s, n, L.row_ptr, L.col, val, v[1], r, dinv,
-                           omega, y, gate);
-    else
-        hipLaunchKernelGGL((amg_csr_post<T, 32>), dim3(gc), dim3(WB), 0, s, n, L.row_ptr, L.col, val, v[1], r, dinv,
-                           omega, y, gate);
+    else RP_LAUNCH(false, false);
 #undef RP_LAUNCH
     RP_HIP_TRY(hipGetLastError());
     return RP_OK;
@@ -811,7 +1052,7 @@ T* dalloc(int64_t n) {
 
 void free_level(AmgLevel& L) {
     void* q[] = {L.row_ptr, L.col, L.val64, L.val32, L.dinv64, L.dinv32, L.diag_pos, L.agg, L.mem_ptr, L.mem,
-                 L.cptr, L.cpos, L.vec64[0], L.vec64[1], L.vec64[2], L.vec64[3], L.vec32[0], L.vec32[1],
+                 L.cptr, L.cpos, L.links, L.vec64[0], L.vec64[1], L.vec64[2], L.vec64[3], L.vec32[0], L.vec32[1],
                  L.vec32[2], L.vec32[3]};
     for (void* a : q)
         if (a) (void)hipFree(a);
@@ -918,6 +1159,47 @@ int coarsen(AmgHier& h, const Src& q, int32_t l, hipStream_t s) {
     return RP_OK;
 }
 
+// Where the V-cycle's step at level l restricts to: the next level if the
+// tail starts there, if it is the coarsest, or if l itself is an odd level
+// (the tail's first); else past the odd level below l, whose aggregates are
+// then composed with level l's.
+int link_levels(AmgHier& h, hipStream_t s) {
+    int32_t* tmp = nullptr;   // counts, positions and the scan's scratch, for the largest odd level
+    struct Free {
+        int32_t*& q;
+        ~Free() {
+            if (q) (void)hipFree(q);
+        }
+    } guard{tmp};
+    for (int32_t l = 0; l < h.n_levels - 1; l = h.lev[l].target) {
+        AmgLevel &L = h.lev[l], &M = h.lev[l + 1];
+        if (l + 1 == h.tail_level || l + 1 == h.n_levels - 1 || l % 2 == 1) {
+            L.target = l + 1;
+            L.map = L.agg;
+            L.rows = L.mem;
+            L.rows_ptr = L.mem_ptr;
+            continue;
+        }
+        L.target = l + 2;
+        const int32_t n = (int32_t)L.n, nm = (int32_t)M.n, nc = (int32_t)h.lev[l + 2].n;
+        if (!tmp) RP_DALLOC(tmp, int32_t, 2 * ((int64_t)nm + 1) + scan_i32_scratch(nm));
+        int32_t *cnt = tmp, *pos = tmp + nm + 1, *scratch = pos + nm + 1;
+        RP_DALLOC(L.links, int32_t, 2 * (int64_t)n + nc + 1);
+        int32_t *map = L.links, *rows = map + n, *rows_ptr = rows + n;
+        L.map = map;
+        L.rows = rows;
+        L.rows_ptr = rows_ptr;
+        hipLaunchKernelGGL(amg_link_count, dim3(grid_of(nm)), dim3(AB), 0, s, nm, M.mem, L.mem_ptr, cnt);
+        RP_TRY(scan_i32_enqueue(cnt, nm, pos, scratch, s));
+        hipLaunchKernelGGL(amg_link_rows, dim3(grid_of(nm)), dim3(AB), 0, s, nm, M.mem, L.mem_ptr, L.mem, pos, rows);
+        hipLaunchKernelGGL(amg_link_ptr, dim3(grid_of(nc + 1)), dim3(AB), 0, s, nc, M.mem_ptr, pos, rows_ptr);
+        hipLaunchKernelGGL(amg_link_map, dim3(grid_of(n)), dim3(AB), 0, s, n, L.agg, M.agg, map);
+        RP_HIP_TRY(hipGetLastError());
+    }
+    RP_HIP_TRY(hipStreamSynchronize(s));   // tmp is released
+    return RP_OK;
+}
+
 // coarse values, diagonals and the coarsest inverse from the plan's values
 int refresh(AmgHier& h, const Src& q, int64_t version, hipStream_t s) {
     hipLaunchKernelGGL(amg_fill, dim3(1), dim3(AB), 0, s, 1, 0, (int32_t*)h.flag);
@@ -953,7 +1235,7 @@ void free_hier(AmgHier*& hp) {
     AmgHier& h = *hp;
     // every level: a failed coarsening leaves arrays on the level it was building
     for (int32_t l = 0; l < AMG_MAX_LEVELS; ++l) free_level(h.lev[l]);
-    for (void* a : {(void*)h.cinv64, (void*)h.cinv32, (void*)h.cwork, (void*)h.flag, h.tail64, h.tail32})
+    for (void* a : {(void*)h.cinv64, (void*)h.cinv32, (void*)h.cwork, (void*)h.flag, h.tail64, h.tail32, (void*)h.tail_work64, (void*)h.tail_work32})
         if (a) (void)hipFree(a);
     delete hp;
     hp = nullptr;
@@ -1008,6 +1290,7 @@ int amg_setup(rp_plan* p, hipStream_t s, bool ordered) {
     // the first level below level 0 small enough for the one-workgroup tail
     for (int32_t l = 1; l < h.n_levels && h.tail_level == 0; ++l)
         if (h.lev[l].n <= AMG_TAIL_ROWS) h.tail_level = l;
+    if ((rc = link_levels(h, s)) != RP_OK) return fail(rc);
     const int64_t nL = h.lev[h.n_levels - 1].n;
     h.cinv64 = dalloc<double>(nL * nL);
     h.cinv32 = dalloc<float>(nL * nL);
@@ -1029,14 +1312,21 @@ int amg_prepare(rp_plan* p, bool fp32, hipStream_t s, bool ordered) {
 }
 
 template <typename T>
-int amg_apply(rp_plan* p, const T* r, T* y, T* part, int32_t n_part, bool rr, const int32_t* gate, hipStream_t s,
-              bool ordered) {
-    return vcycle<T>(*hier(p, ordered), source(p, ordered), 0, r, y, part, n_part, rr, gate, s);
+T* amg_first_sweep(rp_plan* p, bool ordered) {
+    return Prec<T>::vec(hier(p, ordered)->lev[0])[1];
 }
 
-template int amg_apply<double>(rp_plan*, const double*, double*, double*, int32_t, bool, const int32_t*,
+template <typename T>
+int amg_apply(rp_plan* p, const T* r, T* y, T* part, int32_t n_part, bool rr, bool swept, const int32_t* gate,
+              hipStream_t s, bool ordered) {
+    return vcycle<T>(*hier(p, ordered), source(p, ordered), r, y, part, n_part, rr, swept, gate, s);
+}
+
+template double* amg_first_sweep<double>(rp_plan*, bool);
+template float* amg_first_sweep<float>(rp_plan*, bool);
+template int amg_apply<double>(rp_plan*, const double*, double*, double*, int32_t, bool, bool, const int32_t*,
                                hipStream_t, bool);
-template int amg_apply<float>(rp_plan*, const float*, float*, float*, int32_t, bool, const int32_t*, hipStream_t,
-                              bool);
+template int amg_apply<float>(rp_plan*, const float*, float*, float*, int32_t, bool, bool, const int32_t*,
+                              hipStream_t, bool);
 
 }  // namespace rp

@@ -488,7 +488,7 @@ int rp_plan_amg_apply(rp_plan* p, const double* r, double* z, void* stream) {
     RP_TRY(values_solvable(p, s));
     RP_TRY(amg_prepare(p, false, s));
     if (p->n_rows == 0) return RP_OK;
-    return amg_apply<double>(p, r, z, nullptr, 0, false, nullptr, s);
+    return amg_apply<double>(p, r, z, nullptr, 0, false, false, nullptr, s);
 }
 
 int rp_plan_set_vec_grid(rp_plan* p, int32_t blocks) {

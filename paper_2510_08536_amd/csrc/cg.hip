@@ -191,12 +191,14 @@ cg_spmv_pq(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict
 
 // K2: alpha = rz_k / (p, q); r -= alpha q; partials of (r, M^-1 r) ->
 // PART_RZ (RZ: Jacobi M) and (r, r) -> PART_RR.  x moves in K3, which reads
-// p anyway.  Without RZ the preconditioner runs after this kernel and writes
-// the (r, z) partials itself.
+// p anyway.  Without RZ the V-cycle runs after this kernel and writes the
+// (r, z) partials itself; its first sweep, sweep = omega (dinv r), is made
+// here from the r at hand (nullptr: the hierarchy has no level to sweep).
 template <typename T, bool RZ = true>
 __global__ void __launch_bounds__(VEC_BLOCK)
 cg_update_r(int32_t n, int32_t k_arg, int32_t g_spmv, T* __restrict__ r, const T* __restrict__ q,
-            const T* __restrict__ dinv, T* __restrict__ part, CgState<T>* st) {
+            const T* __restrict__ dinv, T* __restrict__ part, CgState<T>* st, T* __restrict__ sweep = nullptr,
+            T omega = T(0)) {
 #pragma clang fp contract(off)
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     // K3 runs only if kk names its iteration, so every path that does no
@@ -240,17 +242,16 @@ cg_update_r(int32_t n, int32_t k_arg, int32_t g_spmv, T* __restrict__ r, const T
             const int32_t e = n - 1 - (i + u * di);
             rv[u] = r[e];
             qv[u] = q[e];
-            dv[u] = RZ ? dinv[e] : T(0);
+            dv[u] = dinv[e];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int32_t e = n - 1 - (i + u * di);
             const T ri = rv[u] - a * qv[u];
             r[e] = ri;
-            if (RZ) {
-                const T zi = dv[u] * ri;
-                prz += ri * zi;
-            }
+            const T zi = dv[u] * ri;
+            if (RZ) prz += ri * zi;
+            else if (sweep) sweep[e] = omega * zi;
             prr += ri * ri;
         }
     }
@@ -258,10 +259,9 @@ cg_update_r(int32_t n, int32_t k_arg, int32_t g_spmv, T* __restrict__ r, const T
         const int32_t e = n - 1 - i;
         const T ri = r[e] - a * q[e];
         r[e] = ri;
-        if (RZ) {
-            const T zi = dinv[e] * ri;
-            prz += ri * zi;
-        }
+        const T zi = dinv[e] * ri;
+        if (RZ) prz += ri * zi;
+        else if (sweep) sweep[e] = omega * zi;
         prr += ri * ri;
     }
     const T b1 = RZ ? block_sum<T, VEC_BLOCK>(prz, red) : T(0);
@@ -828,7 +828,7 @@ int launch_finalize(Cg<T>& c, int32_t mode, int32_t k, T tol2, T pause_frac2, in
 template <typename T>
 int launch_start(Cg<T>& c, int32_t k, T tol2, T pause_frac2, int32_t max_iter) {
     if (c.amg) {
-        RP_TRY(amg_apply<T>(c.plan, c.r, c.p, c.part, c.g_rz, false, nullptr, c.s, c.amg_ordered));
+        RP_TRY(amg_apply<T>(c.plan, c.r, c.p, c.part, c.g_rz, false, false, nullptr, c.s, c.amg_ordered));
     } else if (c.bj_minv && c.bj_lane) {
 #define RP_LAUNCH(BS)                                                                                          \
     hipLaunchKernelGGL((cg_precond_bj_lane<T, BS, false>), dim3(c.g_vec), dim3(VEC_BLOCK), 0, c.s, c.n, c.bj_minv, \
@@ -853,7 +853,7 @@ template <typename T>
 int launch_resume(Cg<T>& c) {
     const int32_t k = c.h->iter - 1;
     if (c.amg) {
-        RP_TRY(amg_apply<T>(c.plan, c.r, c.z, c.part, c.g_rz, true, nullptr, c.s, c.amg_ordered));
+        RP_TRY(amg_apply<T>(c.plan, c.r, c.z, c.part, c.g_rz, true, false, nullptr, c.s, c.amg_ordered));
         hipLaunchKernelGGL((cg_update_xp<T, true>), dim3(c.g_vec), dim3(VEC_BLOCK), 0, c.s, c.n, k, c.g_rz, c.g_rz, 1,
                            c.r, c.dinv, c.z, c.x, c.p, c.part, c.st);
     } else if (c.bj_minv) {
@@ -895,9 +895,11 @@ int launch_iteration(Cg<T>& c, int32_t k, hipStream_t s) {
     if (c.amg) {
         // K2 without (r, z); the V-cycle (skipped when K2 did no update)
         // stores z and the (r, z) partials; K3 reads z
-        hipLaunchKernelGGL((cg_update_r<T, false>), gv, bv, 0, s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st);
+        T* sweep = amg_first_sweep<T>(c.plan, c.amg_ordered);
+        hipLaunchKernelGGL((cg_update_r<T, false>), gv, bv, 0, s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st,
+                           sweep, (T)RP_AMG_OMEGA);
         RP_HIP_TRY(hipGetLastError());
-        RP_TRY(amg_apply<T>(c.plan, c.r, c.z, c.part, c.g_rz, false, &c.st->kk, s, c.amg_ordered));
+        RP_TRY(amg_apply<T>(c.plan, c.r, c.z, c.part, c.g_rz, false, sweep != nullptr, &c.st->kk, s, c.amg_ordered));
         hipLaunchKernelGGL((cg_update_xp<T, true>), gv, bv, 0, s, c.n, k, c.g_rz, c.g_vec, 0, c.r, c.dinv, c.z, c.x,
                            c.p, c.part, c.st);
     } else if (c.bj_minv) {
@@ -917,7 +919,8 @@ int launch_iteration(Cg<T>& c, int32_t k, hipStream_t s) {
         hipLaunchKernelGGL((cg_update_xp<T, true>), gv, bv, 0, s, c.n, k, c.g_vec, c.g_vec, 0, c.r, c.dinv, c.z, c.x, c.p,
                            c.part, c.st);
     } else {
-        hipLaunchKernelGGL(cg_update_r<T>, gv, bv, 0, s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st);
+        hipLaunchKernelGGL(cg_update_r<T>, gv, bv, 0, s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st,
+                           (T*)nullptr, T(0));
         hipLaunchKernelGGL((cg_update_xp<T, false>), gv, bv, 0, s, c.n, k, c.g_vec, c.g_vec, 0, c.r, c.dinv, c.z, c.x, c.p,
                            c.part, c.st);
     }
@@ -996,7 +999,8 @@ int iterate_two(Cg<T>& c, int chunk, int32_t max_iter) {
         const int32_t ks = c.h->iter;
         const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)ks + chunk, max_iter);
         for (int32_t k = ks; k < k1; ++k) {
-            hipLaunchKernelGGL(cg_update_r<T>, gv, bv, 0, c.s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st);
+            hipLaunchKernelGGL(cg_update_r<T>, gv, bv, 0, c.s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st,
+                               (T*)nullptr, T(0));
             hipLaunchKernelGGL(cg_update_xp_spmv<T>, gs, bs, 0, c.s, c.n, k, c.g_vec, c.ix.row_ptr, c.ix.col, c.val,
                                c.r, c.dinv, pb[(k - k0) & 1], pb[(k - k0 + 1) & 1], c.x, c.q, c.part, c.st);
         }

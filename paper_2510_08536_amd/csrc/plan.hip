@@ -263,14 +263,22 @@ __global__ void scan_down(const int32_t* in, int64_t n, const int32_t* block_sum
     if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = block_sums[nb];
 }
 
-int exclusive_scan(const int32_t* in, int64_t n, int32_t* out, int32_t* total, hipStream_t s) {
-    const int32_t nb = (int32_t)((n + SCAN_CHUNK - 1) / SCAN_CHUNK);
-    int32_t* sums = nullptr;
-    RP_HIP_TRY(hipMalloc(&sums, sizeof(int32_t) * (nb + 1)));
+int32_t scan_blocks(int64_t n) { return (int32_t)((n + SCAN_CHUNK - 1) / SCAN_CHUNK); }
+
+// the scan's kernels; sums: scan_blocks(n) + 1 words, the last the total
+hipError_t enqueue_scan(const int32_t* in, int64_t n, int32_t* out, int32_t* sums, hipStream_t s) {
+    const int32_t nb = scan_blocks(n);
     if (nb > 0) hipLaunchKernelGGL(scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, s, in, n, sums);
     hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, sums, nb);
     hipLaunchKernelGGL(scan_down, dim3(nb > 0 ? nb : 1), dim3(SCAN_BLOCK), 0, s, in, n, sums, nb, out);
-    hipError_t e = hipGetLastError();
+    return hipGetLastError();
+}
+
+int exclusive_scan(const int32_t* in, int64_t n, int32_t* out, int32_t* total, hipStream_t s) {
+    const int32_t nb = scan_blocks(n);
+    int32_t* sums = nullptr;
+    RP_HIP_TRY(hipMalloc(&sums, sizeof(int32_t) * (nb + 1)));
+    hipError_t e = enqueue_scan(in, n, out, sums, s);
     if (e == hipSuccess) e = hipMemcpyAsync(total, sums + nb, sizeof(int32_t), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(sums);
@@ -464,6 +472,13 @@ int goi_build(rp_plan* p, hipStream_t s) {
 // out[0..n] with out[n] = *total (read back to the host)
 int scan_i32(const int32_t* in, int64_t n, int32_t* out, int32_t* total, hipStream_t s) {
     return exclusive_scan(in, n, out, total, s);
+}
+
+// the same without a readback: scratch holds scan_i32_scratch(n) words
+int64_t scan_i32_scratch(int64_t n) { return (int64_t)scan_blocks(n) + 1; }
+int scan_i32_enqueue(const int32_t* in, int64_t n, int32_t* out, int32_t* scratch, hipStream_t s) {
+    RP_HIP_TRY(enqueue_scan(in, n, out, scratch, s));
+    return RP_OK;
 }
 
 int plan_build(rp_plan* p, const rp_rank_desc* share) {

@@ -135,8 +135,20 @@ struct AmgLevel {
     int32_t* mem = nullptr;       // [n]       ascending
     int32_t* cptr = nullptr;      // [nnz_c + 1] coarse entry e sums the values at
     int32_t* cpos = nullptr;      // [nnz]       positions cpos[cptr[e] .. cptr[e+1])
+    // levels the V-cycle stops at (even ones, the tail's first one, the
+    // coarsest): it restricts to level `target`, mostly the one after the next
+    // (an odd level only restricts and prolongs).  Coarse row I of it sums the rows
+    // rows[rows_ptr[I] .. rows_ptr[I+1]) in that order; the sign bit marks the
+    // first row of each aggregate of the level stepped over, whose sum is
+    // formed first.  map[i] = coarse row of row i.  links: the three arrays
+    // where the level has its own (else agg, mem and mem_ptr serve).
+    int32_t target = 0;
+    const int32_t* map = nullptr;       // [n]
+    const int32_t* rows = nullptr;      // [n]
+    const int32_t* rows_ptr = nullptr;  // [n_target + 1]
+    int32_t* links = nullptr;
     // V-cycle vectors per precision: in (levels >= 1), x and t (smoothed
-    // levels), out (levels >= 1)
+    // levels), out (levels >= 1); none on odd levels above the tail
     double* vec64[4] = {nullptr, nullptr, nullptr, nullptr};
     float* vec32[4] = {nullptr, nullptr, nullptr, nullptr};
 };
@@ -154,6 +166,11 @@ struct AmgHier {
     int32_t tail_level = 0;       // 0: none
     void* tail64 = nullptr;
     void* tail32 = nullptr;
+    int32_t tail_steps = 0;       // levels the tail stops at
+    int32_t tail_rows = 0;        // their rows
+    bool tail_in_lds = false;     // vectors and lists fit in LDS
+    double* tail_work64 = nullptr;   // the tail's vectors where LDS cannot hold them
+    float* tail_work32 = nullptr;
 };
 
 // ---------------------------------------------------------------------------
@@ -382,10 +399,14 @@ int amg_prepare(rp_plan* p, bool fp32, hipStream_t s, bool ordered = false);
 void amg_free(rp_plan* p);
 // y = V-cycle(r) on the level-0 system.  part != null: partials of (r, y) ->
 // PART_RZ (and, rr, of (r, r) -> PART_RR), n_part of them.  gate != null:
-// every kernel returns when *gate < 0.
+// every kernel returns when *gate < 0.  swept: the caller has put the cycle's
+// first sweep, RP_AMG_OMEGA (dinv r), into amg_first_sweep's vector.
 template <typename T>
-int amg_apply(rp_plan* p, const T* r, T* y, T* part, int32_t n_part, bool rr, const int32_t* gate, hipStream_t s,
-              bool ordered = false);
+int amg_apply(rp_plan* p, const T* r, T* y, T* part, int32_t n_part, bool rr, bool swept, const int32_t* gate,
+              hipStream_t s, bool ordered = false);
+// the level-0 iterate of the V-cycle; nullptr where level 0 is the coarsest
+template <typename T>
+T* amg_first_sweep(rp_plan* p, bool ordered);
 // order.hip
 // reverse Cuthill-McKee order of a structurally symmetric pattern: perm[k] = row at position k
 std::vector<int32_t> rcm_order(int32_t n, const int32_t* row_ptr, const int32_t* col);
