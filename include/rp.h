@@ -84,8 +84,9 @@ extern "C" {
                                      with at most this many rows down runs in one workgroup */
 
 /* ---- launches per Jacobi-PCG iteration (rp_solve_opts.fused_loop) ------- */
-#define RP_LOOP_AUTO 0            /* two launches on systems of at most RP_LOOP_TWO_MAX_ROWS
-                                     rows, three on larger ones */
+#define RP_LOOP_AUTO 0            /* on systems of at most RP_LOOP_TWO_MAX_ROWS rows all
+                                     iterations in one launch, or two launches each where
+                                     a row has more than 8 entries; three on larger ones */
 #define RP_LOOP_COOPERATIVE 1     /* all iterations in one cooperative launch */
 #define RP_LOOP_THREE 2           /* three launches (SpMV; r update; x and p update) */
 #define RP_LOOP_TWO_MAX_ROWS 262144
@@ -145,10 +146,13 @@ typedef struct rp_solve_opts {
                                 RP_LOOP_THREE: one launch per phase (SpMV with (p, q);
                                 r update with (r, z), (r, r); x and p update).
                                 RP_LOOP_AUTO (default): the same on systems above
-                                RP_LOOP_TWO_MAX_ROWS rows; on smaller ones two launches, the
-                                x and p update of iteration k fused with the SpMV of k + 1
-                                (each row forms the new p of its columns itself), with
-                                results bit-identical to RP_LOOP_THREE.
+                                RP_LOOP_TWO_MAX_ROWS rows; on smaller ones all iterations in
+                                one cooperative launch that keeps the system in registers
+                                and exchanges values, without barriers (every row at most 8
+                                entries, and the device holds a thread per row); else two
+                                launches, the x and p update of iteration k fused with the
+                                SpMV of k + 1 (each row forms the new p of its columns
+                                itself).  Results bit-identical to RP_LOOP_THREE.
                                 RP_LOOP_COOPERATIVE: all iterations in one cooperative
                                 launch (the phases separated by grid-wide barriers; same
                                 arithmetic, partial sums over a smaller grid); on MI355X it

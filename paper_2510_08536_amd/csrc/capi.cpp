@@ -90,7 +90,7 @@ void free_plan(rp_plan* p) {
                    p->d_valT, p->d_tflag, p->d_ro_perm, p->d_ro_row_ptr, p->d_ro_col, p->d_ro_sig,
                    p->d_ro_val64, p->d_ro_val32, p->d_ro_dinv64, p->d_ro_dinv32, p->d_ro_b, p->d_ro_x,
                    p->d_ro_valT, (void*)p->d_src, p->d_bj_start, p->d_bj_minv64, p->d_bj_minv32, p->d_z,
-                   p->d_z32, p->d_bj_flag, p->d_loop_bar};
+                   p->d_z32, p->d_bj_flag, p->d_loop_bar, p->d_slots};
     amg_free(p);
     for (void* q : dev)
         if (q) (void)hipFree(q);
@@ -145,7 +145,7 @@ int alloc_values(rp_plan* p) {
     RP_TRY(dalloc(&p->d_bi_st, 1));
     RP_HIP_TRY(hipMemset(p->d_bi_st, 0, sizeof(BiState)));
     RP_HIP_TRY(hipHostMalloc((void**)&p->h_bi_st, sizeof(BiState), hipHostMallocDefault));
-    RP_HIP_TRY(hipHostMalloc((void**)&p->h_flags, 2 * sizeof(uint32_t), hipHostMallocDefault));
+    RP_HIP_TRY(hipHostMalloc((void**)&p->h_flags, 3 * sizeof(uint32_t), hipHostMallocDefault));
     RP_HIP_TRY(hipMalloc((void**)&p->d_src, sizeof(const double*) * 4 * (size_t)std::max(p->alpha, 1)));
     return RP_OK;
 }

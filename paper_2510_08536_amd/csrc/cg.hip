@@ -7,9 +7,11 @@
 //                                    partials of (r, M^-1 r) and (r, r)
 //   K3  x += alpha p; stop tests, beta = rz_{k+1} / rz_k, p = M^-1 r + beta p
 // (x moves in K3, which reads p anyway: one pass over p less per iteration)
-// Small systems run K3 of iteration k and K1 of iteration k + 1 as one
-// kernel (cg_update_xp_spmv), two launches per iteration with the same
-// results bit for bit.
+// Small systems run every iteration in one launch that keeps the system in
+// registers (cg_resident in cg_loop.hip), or, where its rows are too long for
+// that, K3 of iteration k and K1 of iteration k + 1 as one kernel
+// (cg_update_xp_spmv), two launches per iteration; the same results bit for
+// bit either way.
 // Each kernel starts by adding up the previous kernel's per-block partials
 // (every block the same sum, in index order), so reductions need no atomics,
 // no fences and no extra launches, and reruns are bit-identical.  The
@@ -46,6 +48,13 @@ namespace rp {
 template <typename T>
 int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const T* dinv, T* x, T* r, T* pv, T* q,
                    CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s, bool* ran);
+// the same by the resident loop, on a plan with resident_block > 0; enqueued,
+// the abort word to h_flags[2]
+template <typename T>
+int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
+                       const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s);
+template <typename T>
+int resident_block(rp_plan* p, int* out);
 
 namespace {
 
@@ -233,20 +242,23 @@ cg_update_r(int32_t n, int32_t k_arg, int32_t g_spmv, T* __restrict__ r, const T
     // from the bottom up: each kernel then starts on the lines its
     // predecessor touched last, which are still in the 256 MB memory-side
     // cache.  U of the thread's grid-stride elements per trip, all loads
-    // first; the sums take the elements in the loop's order.
+    // first; the sums take the elements in the loop's order.  A grid with a
+    // thread per row (small systems) takes the rows in order, so that a
+    // block's partials are one row group's.
+    const int32_t up = di >= n ? 0 : n - 1, sign = di >= n ? 1 : -1;
     constexpr int U = vec_unroll_r<T>();
     for (; (int64_t)i + (int64_t)(U - 1) * di < n; i += U * di) {
         T rv[U], qv[U], dv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int32_t e = n - 1 - (i + u * di);
+            const int32_t e = up + sign * (i + u * di);
             rv[u] = r[e];
             qv[u] = q[e];
             dv[u] = dinv[e];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int32_t e = n - 1 - (i + u * di);
+            const int32_t e = up + sign * (i + u * di);
             const T ri = rv[u] - a * qv[u];
             r[e] = ri;
             const T zi = dv[u] * ri;
@@ -256,7 +268,7 @@ cg_update_r(int32_t n, int32_t k_arg, int32_t g_spmv, T* __restrict__ r, const T
         }
     }
     for (; i < n; i += di) {
-        const int32_t e = n - 1 - i;
+        const int32_t e = up + sign * i;
         const T ri = r[e] - a * q[e];
         r[e] = ri;
         const T zi = dinv[e] * ri;
@@ -363,7 +375,8 @@ cg_update_xp(int32_t n, int32_t k_arg, int32_t g_rz, int32_t g_rr, int32_t resum
 }
 
 // K3 of iteration k fused with K1 of iteration k + 1 (systems of at most
-// RP_LOOP_TWO_MAX_ROWS rows, Jacobi M, rows read as plain CSR).  The stop
+// RP_LOOP_TWO_MAX_ROWS rows that do not fit the resident loop, Jacobi M, rows
+// read as plain CSR).  The stop
 // tests and x += alpha p_k are K3's.  Unless stopping, p_{k+1} = M^-1 r +
 // beta p_k of a row is formed wherever it is needed: once by the row itself,
 // which stores it into pn, and again, by the same operations, by every row
@@ -1014,13 +1027,55 @@ int iterate_two(Cg<T>& c, int chunk, int32_t max_iter) {
     return RP_OK;
 }
 
+// whether these options run the iterations of c in the resident loop, which
+// looks at the device state itself: a solve may then enqueue it behind the
+// start kernels without reading their state (start_ahead)
+template <typename T>
+int runs_resident(const Cg<T>& c, const rp_solve_opts& o, bool* yes) {
+    *yes = false;
+    if (o.fused_loop != RP_LOOP_AUTO || c.n > RP_LOOP_TWO_MAX_ROWS || c.plan->timing.enabled || o.graph ||
+        c.bj_minv || c.amg || c.plan->vec_grid_override != 0)   // its sums are those of the default vector grid
+        return RP_OK;
+    int bt = 0;
+    RP_TRY(resident_block<T>(c.plan, &bt));
+    *yes = bt > 0;
+    return RP_OK;
+}
+
+// the state after launch_start at iteration k: read it, or (resident) take
+// it as running; the loop's own read brings the truth
+template <typename T>
+int start_ahead(Cg<T>& c, bool resident, int32_t k, int32_t max_iter) {
+    if (!resident || k >= max_iter) return read_state(c);
+    c.h->done = CG_RUNNING;
+    c.h->iter = k;
+    return RP_OK;
+}
+
 // enqueue chunks of up to `chunk` iterations (never past max_iter) until the
 // state leaves CG_RUNNING or the budget is spent.  graph: each chunk is one
 // replay of a captured graph of `chunk` iterations (kernels past max_iter do
 // nothing); per-kernel timing always launches eagerly.
 template <typename T>
-int iterate(Cg<T>& c, int chunk, int32_t max_iter, bool graph, int32_t fused_loop) {
-    const bool timed = c.plan->timing.enabled;
+int iterate(Cg<T>& c, const rp_solve_opts& o, bool resident) {
+    const bool timed = c.plan->timing.enabled, graph = o.graph != 0;
+    const int chunk = std::max(1, o.check_every);
+    const int32_t max_iter = o.max_iter, fused_loop = o.fused_loop;
+    if (resident) {
+        // a launch's length is bounded: other work on the device waits for it
+        constexpr int64_t LOOP_ITERS = 1 << 16;
+        while (c.h->done == CG_RUNNING && c.h->iter < max_iter) {
+            const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)c.h->iter + LOOP_ITERS, max_iter);
+            RP_TRY(launch_cg_resident<T>(c.plan, c.n, c.ix.row_ptr, c.ix.col, c.val, c.dinv, c.x, c.r, c.p, c.st,
+                                         c.h->iter, k1, c.s));
+            RP_TRY(read_state(c));
+            if (c.plan->h_flags[2]) {
+                set_error("the resident CG loop gave up waiting for another workgroup's values");
+                return RP_ERR_HIP;
+            }
+        }
+        return RP_OK;
+    }
     if (fused_loop == RP_LOOP_AUTO && c.n <= RP_LOOP_TWO_MAX_ROWS && !timed && !graph && !c.bj_minv && !c.amg)
         return iterate_two(c, chunk, max_iter);
     if (fused_loop == RP_LOOP_COOPERATIVE && !timed && !graph && !c.bj_minv && !c.amg) {
@@ -1119,10 +1174,11 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
         use_amg(c, p->d_z, ordered);
     }
     const double tol2 = o.tol * o.tol;
-    const int chunk = std::max(1, o.check_every);
+    bool resident = false;
+    RP_TRY(runs_resident(c, o, &resident));
     RP_TRY((launch_residual<double, false>(c, o.x0_zero != 0, nullptr)));
     RP_TRY(launch_start(c, 0, tol2, 0.0, o.max_iter));
-    RP_TRY(read_state(c));
+    RP_TRY(start_ahead(c, resident, 0, o.max_iter));
     bool fresh = true;  // rr_true belongs to the current x
     int status = RP_NOT_CONVERGED;
     info.restarts = 0;
@@ -1157,8 +1213,9 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
             break;
         }
         if (c.h->iter >= o.max_iter) break;
-        RP_TRY(iterate(c, chunk, o.max_iter, o.graph != 0, o.fused_loop));
-        fresh = false;
+        const int32_t it_before = c.h->iter;
+        RP_TRY(iterate(c, o, resident));
+        if (c.h->iter > it_before || c.h->done == CG_RUNNING) fresh = false;
     }
     if (!fresh && c.h->done != CG_ZERO_RHS) {
         RP_TRY((launch_residual<double, false>(c, false, nullptr)));
@@ -1193,7 +1250,8 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
         RP_TRY(amg_prepare(p, true, s, ordered));
         use_amg(in, p->d_z32, ordered);
     }
-    const int chunk = std::max(1, o.check_every);
+    bool resident = false;
+    RP_TRY(runs_resident(in, o, &resident));
 
     RP_TRY((launch_residual<double, true>(out, o.x0_zero != 0, p->d_r32)));
     RP_TRY(launch_finalize(out, FIN_RESIDUAL, 0, 0.0, 0.0));
@@ -1229,11 +1287,11 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
             }
             RP_TRY((launch_residual<float, false>(in, true, nullptr)));
             RP_TRY(launch_start(in, total_inner, tol2_in, pause2, o.max_iter));
-            RP_TRY(read_state(in));
+            RP_TRY(start_ahead(in, resident, total_inner, o.max_iter));
             start_inner = false;
         }
         const int32_t it_before = in.h->iter;
-        RP_TRY(iterate(in, chunk, o.max_iter, o.graph != 0, o.fused_loop));
+        RP_TRY(iterate(in, o, resident));
         total_inner = in.h->iter;
         const int32_t d = in.h->done;
         // fold the FP32 correction into x and take the FP64 residual
@@ -1259,7 +1317,7 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
         if (total_inner >= o.max_iter || outer >= o.max_outer || stall >= 4) break;
         if (reliable && d == CG_PAUSED) {
             RP_TRY(launch_resume(in));   // keep the search direction, replaced residual
-            RP_TRY(read_state(in));
+            RP_TRY(start_ahead(in, resident, total_inner, o.max_iter));
         } else {
             start_inner = true;          // restart FP32 PCG on the new residual
         }

@@ -1,4 +1,6 @@
-// CG iterations in one cooperative launch (rp_solve_opts.fused_loop).
+// CG iterations in one cooperative launch (rp_solve_opts.fused_loop), in two
+// forms: cg_loop (RP_LOOP_COOPERATIVE), for systems of any size, and
+// cg_resident (RP_LOOP_AUTO on small systems), described further down.
 //
 // On small systems an iteration is bound by the gaps between its three
 // dependent kernels, not by memory.  Here one launch, with every block
@@ -172,6 +174,320 @@ cg_loop(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict__ 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The resident loop: the default on small systems whose rows hold at most
+// RES_COLS entries (launch_cg_resident).
+//
+// A row belongs to one thread for the whole launch, with its entries, x, r,
+// p and M^-1 in registers, and with p of the columns it couples to; every
+// thread forms the new p of its columns itself (as the two-launch iteration
+// does) from their z = M^-1 r.  So an iteration exchanges z and the three
+// sums, and needs two exchanges where the loop above needs three barriers:
+//   (p, q) partials;   alpha, r, z;   z and the (r, z), (r, r) partials;
+//   stop tests, x, beta, p.
+// An exchange is no barrier and has no fences.  What is exchanged is stored
+// and loaded by agent-scope relaxed atomics, which pass the die's L2 by, so
+// nothing is written back or invalidated; and every value is its own flag:
+// its slot holds EMPTY (a NaN no value is stored as) until it is stored, and
+// a reader loads until it is not.  So z needs no order with the partials, and
+// a reader waits once for both.  z of columns in the block's own rows goes
+// through LDS; a row is published only if it couples to another block's rows
+// (the pattern is structurally symmetric, so only those have readers there).
+// The slots rotate through RES_SETS sets; a thread empties its own slots of
+// set k - 1 once its block has seen every (p, q) partial of iteration k (all
+// blocks are then past iteration k - 1), and waits for those stores before
+// the block's next (p, q) partial is published, so nobody can meet set k - 1
+// again with old values in it.
+//
+// The partials are those of the launched kernels on systems of this size: one
+// per group of SPMV_BLOCK consecutive rows for all three sums (vec_grid gives
+// K2 one element per thread), summed in the same order, so every iterate is
+// the three-launch form's bit for bit.  The wait is bounded as above.
+//
+// Bound by the two exchanges: a store and the load that meets it cross the
+// die boundaries, about 1.5 us each way with the reductions.  Per iteration
+// against two launches: FP64 6.6 / 12.8 us at 32768 rows, 8.4 / 14.4 at
+// 130050, 11.3 / 19.9 at 262144; FP32 7.3 / 12.6, 9.0 / 14.2, 11.3 / 17.2.
+// With r published in front of the partials, and read after them, the
+// iteration at 32768 rows took 8.5 us.
+// ---------------------------------------------------------------------------
+constexpr int RES_COLS = 8;                    // entries per row at most
+constexpr int RES_GROUPS = VEC_GRID_MAX;       // row groups at most
+constexpr int RES_SETS = 4;
+
+// a value as the word it is exchanged as
+template <typename T>
+struct Word;
+template <>
+struct Word<double> {
+    typedef uint64_t type;
+    static constexpr type EMPTY = ~0ull;
+    static __device__ __forceinline__ type of(double v) {
+        return v == v ? (type)__double_as_longlong(v) : 0x7FF8000000000000ull;
+    }
+    static __device__ __forceinline__ double value(type u) { return __longlong_as_double((long long)u); }
+};
+template <>
+struct Word<float> {
+    typedef uint32_t type;
+    static constexpr type EMPTY = ~0u;
+    static __device__ __forceinline__ type of(float v) { return v == v ? __float_as_uint(v) : 0x7FC00000u; }
+    static __device__ __forceinline__ float value(type u) { return __uint_as_float(u); }
+};
+
+template <typename V>
+__device__ __forceinline__ V agent_load(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// from a byte offset to a base that is the same in every lane (one address register)
+template <typename V>
+__device__ __forceinline__ V agent_load_at(const V* base, uint32_t bytes) {
+    return agent_load(reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + bytes));
+}
+template <typename V>
+__device__ __forceinline__ void agent_store(V* p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// every slot empty (all-ones words of either size), no abort
+__global__ void clear_slots(uint32_t* slots, int32_t words, uint32_t* bar) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) slots[i] = ~0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) bar[0] = 0u;
+}
+
+// spins of one wait: true = give up (too many, or another block gave up)
+__device__ __forceinline__ bool wait_over(uint32_t& spins, const uint32_t* bar) {
+    return ++spins > BAR_SPINS || (spins % 256 == 0 && load_relaxed(bar) != 0u);
+}
+
+// The sums of N values per group once no slot of slots[0 .. N ng) is empty
+// (value j of group m at N m + j), added up as sum_partials_all does it with
+// SPMV_BLOCK threads: thread t adds groups t, t + 256, ...; the wave sums go
+// to red[j][0 .. 4).  False: the wait was abandoned.
+template <typename T, int N>
+__device__ __forceinline__ bool gather_slots(const typename Word<T>::type* slots, int32_t ng, int32_t t,
+                                             const uint32_t* bar, T (*red)[SPMV_BLOCK / 64]) {
+#pragma clang fp contract(off)
+    T s[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) s[j] = T(0);
+    bool good = true;
+    for (int32_t m = t; m < ng; m += SPMV_BLOCK) {
+        typename Word<T>::type u[N];
+        for (uint32_t spins = 0;;) {
+            bool empty = false;
+#pragma unroll
+            for (int j = 0; j < N; ++j) u[j] = agent_load(slots + N * m + j);
+#pragma unroll
+            for (int j = 0; j < N; ++j) empty |= u[j] == Word<T>::EMPTY;
+            if (!empty) break;
+            if (wait_over(spins, bar)) {
+                good = false;
+                break;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) s[j] += Word<T>::value(u[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        s[j] = wave_sum(s[j]);
+        if ((t & 63) == 0) red[j][t >> 6] = s[j];
+    }
+    return good;
+}
+
+template <typename T>
+__device__ __forceinline__ T sum_red(const T* red) {
+#pragma clang fp contract(off)
+    T s = T(0);
+    for (int w = 0; w < SPMV_BLOCK / 64; ++w) s += red[w];
+    return s;
+}
+
+// BT threads per block: BT / SPMV_BLOCK row groups.  slots: RES_SETS sets of
+// 3 RES_GROUPS partials; zs: RES_SETS sets of n values of z.
+template <typename T, int BT>
+__global__ void __launch_bounds__(BT)
+cg_resident(int32_t n, int32_t ng, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+            const T* __restrict__ val, const T* __restrict__ dinv, T* __restrict__ x, T* __restrict__ r,
+            T* __restrict__ p, CgState<T>* st, int32_t k0, int32_t k_end, typename Word<T>::type* slots,
+            typename Word<T>::type* zs, uint32_t* bar) {
+#pragma clang fp contract(off)
+    typedef typename Word<T>::type W;
+    constexpr W EMPTY = Word<T>::EMPTY;
+    __shared__ T red1[BT / 64], red2[BT / 64];   // wave sums of this block's groups
+    __shared__ T all[2][SPMV_BLOCK / 64];
+    __shared__ T zl[BT];                         // z of this block's rows
+    __shared__ int32_t bad;
+    if (st->done != CG_RUNNING) return;
+    const int32_t t = threadIdx.x, i = blockIdx.x * BT + t;
+    const int32_t group = i / SPMV_BLOCK;
+    const bool first = t % SPMV_BLOCK == 0 && group < ng;   // publishes the group's sums
+    const int32_t k_stop = min(k_end, st->max_iter);
+    const T thresh = st->thresh, pause_thresh = st->pause_thresh;
+    T rz = st->rz[k0 & 3];
+    int32_t len = 0, c[RES_COLS];
+    T v[RES_COLS], pj[RES_COLS];
+    T xi = T(0), ri = T(0), pi = T(0), di = T(0);
+    bool remote = false;
+    if (i < n) {
+        const int32_t e0 = row_ptr[i];
+        len = row_ptr[i + 1] - e0;
+#pragma unroll
+        for (int u = 0; u < RES_COLS; ++u) {
+            c[u] = u < len ? col[e0 + u] : i;
+            v[u] = u < len ? val[e0 + u] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < RES_COLS; ++u) pj[u] = p[c[u]];
+        xi = x[i];
+        ri = r[i];
+        pi = p[i];
+        di = dinv[i];
+    } else {
+#pragma unroll
+        for (int u = 0; u < RES_COLS; ++u) {
+            c[u] = i;
+            v[u] = T(0);
+            pj[u] = T(0);
+        }
+    }
+    // columns of this block's own rows are read from zl, c = -1 - place; of the
+    // others c is the byte offset
+#pragma unroll
+    for (int u = 0; u < RES_COLS; ++u) {
+        const int32_t place = c[u] - (int32_t)blockIdx.x * BT;
+        const bool own = place >= 0 && place < BT;
+        remote |= !own;
+        c[u] = own ? -1 - place : c[u] * (int32_t)sizeof(W);
+    }
+    if (t == 0) bad = 0;
+    __syncthreads();
+    int32_t k = k0, stop = CG_RUNNING;
+    T pq = T(0), a = T(0), beta = T(0), rr = T(0);
+    bool given_up = false;
+    for (; k < k_stop; ++k) {
+        W* const s_pq = slots + (k % RES_SETS) * 3 * RES_GROUPS;
+        W* const s_rr = s_pq + RES_GROUPS;   // (r, z) and (r, r), a pair per group
+        W* const z_k = zs + (int64_t)(k % RES_SETS) * n;
+        // q = A p, partials of (p, q)
+        T q = T(0);
+#pragma unroll
+        for (int u = 0; u < RES_COLS; ++u)
+            if (u < len) q += v[u] * pj[u];
+        T w1 = wave_sum(pi * q);
+        if ((t & 63) == 0) red1[t >> 6] = w1;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the slots emptied last time are
+        __syncthreads();
+        if (first) agent_store(s_pq + group, Word<T>::of(sum_red(red1 + t / 64)));
+        if (t < SPMV_BLOCK && !gather_slots<T, 1>(s_pq, ng, t, bar, all)) bad = 1;
+        __syncthreads();
+        if (bad) {
+            given_up = true;
+            break;
+        }
+        pq = sum_red(all[0]);
+        if (!(pq > T(0)) || !isfinite(pq)) {
+            stop = CG_BREAKDOWN;
+            break;
+        }
+        a = rz / pq;
+        // r -= alpha q; z = M^-1 r; partials of (r, z), (r, r)
+        ri = ri - a * q;
+        const T zi = di * ri;
+        if (remote) agent_store(z_k + i, Word<T>::of(zi));
+        zl[t] = zi;
+        w1 = wave_sum(ri * zi);
+        const T w2 = wave_sum(ri * ri);
+        if ((t & 63) == 0) {
+            red1[t >> 6] = w1;
+            red2[t >> 6] = w2;
+        }
+        __syncthreads();
+        if (first) {
+            agent_store(s_rr + 2 * group, Word<T>::of(sum_red(red1 + t / 64)));
+            agent_store(s_rr + 2 * group + 1, Word<T>::of(sum_red(red2 + t / 64)));
+        }
+        if (k > k0) {   // every block is past iteration k - 1
+            if (remote) agent_store(zs + (int64_t)((k - 1) % RES_SETS) * n + i, EMPTY);
+            if (first) {
+                W* const old = slots + ((k - 1) % RES_SETS) * 3 * RES_GROUPS;
+                agent_store(old + group, EMPTY);
+                agent_store(old + RES_GROUPS + 2 * group, EMPTY);
+                agent_store(old + RES_GROUPS + 2 * group + 1, EMPTY);
+            }
+        }
+        W zj[RES_COLS];
+        if (remote) {
+#pragma unroll
+            for (int u = 0; u < RES_COLS; ++u) zj[u] = c[u] >= 0 ? agent_load_at(z_k, (uint32_t)c[u]) : W(0);
+        }
+        if (t < SPMV_BLOCK && !gather_slots<T, 2>(s_rr, ng, t, bar, all)) bad = 1;
+        if (remote) {
+            for (uint32_t spins = 0;;) {
+                bool empty = false;
+#pragma unroll
+                for (int u = 0; u < RES_COLS; ++u) empty |= zj[u] == EMPTY;
+                if (!empty) break;
+                if (wait_over(spins, bar)) {
+                    bad = 1;
+                    break;
+                }
+#pragma unroll
+                for (int u = 0; u < RES_COLS; ++u)
+                    if (zj[u] == EMPTY) zj[u] = agent_load_at(z_k, (uint32_t)c[u]);
+            }
+        }
+        __syncthreads();
+        if (bad) {
+            given_up = true;
+            break;
+        }
+        const T rzn = sum_red(all[0]);
+        rr = sum_red(all[1]);
+        // x += alpha p; stop tests; beta = rz_{k+1} / rz_k; p = z + beta p
+        xi = xi + a * pi;
+        if (rr <= thresh) stop = CG_CONVERGED;
+        else if (!(rzn > T(0)) || !isfinite(rzn)) stop = CG_BREAKDOWN;
+        else if (rr <= pause_thresh) stop = CG_PAUSED;
+        if (stop != CG_RUNNING) {
+            ++k;   // this iteration counts
+            break;
+        }
+        beta = rzn / rz;
+        rz = rzn;
+        pi = zi + beta * pi;
+#pragma unroll
+        for (int u = 0; u < RES_COLS; ++u) {
+            const T z = c[u] < 0 ? zl[-1 - c[u]] : Word<T>::value(zj[u]);
+            pj[u] = z + beta * pj[u];
+        }
+    }
+    if (given_up) {
+        if (t == 0) atomicOr(bar, 1u);
+        return;
+    }
+    if (i < n) {
+        x[i] = xi;
+        r[i] = ri;
+        p[i] = pi;
+    }
+    if (i == 0) {
+        // rz_k of the last iteration that began, for a resumed direction: the
+        // stop left rz alone, a finished iteration moved it on
+        const int32_t at = stop == CG_RUNNING || (stop == CG_BREAKDOWN && !(pq > T(0) && isfinite(pq))) ? k : k - 1;
+        st->rz[at & 3] = rz;
+        st->pq = pq;
+        st->alpha = a;
+        st->beta = beta;
+        if (k > k0) st->rr = rr;
+        st->iter = k;
+        st->kk = -1;
+        st->done = stop;
+    }
+}
+
 // blocks of the cooperative launch for n rows: about two groups of rows per
 // block, at most LOOP_GRID_MAX blocks (a barrier costs about one L2
 // write-back and invalidate per block, so fewer, fuller blocks are cheaper
@@ -226,6 +542,70 @@ int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const
     return RP_OK;
 }
 
+template <typename T>
+const void* resident_kernel(int bt) {
+    return bt == 512 ? (const void*)cg_resident<T, 512> : (const void*)cg_resident<T, 1024>;
+}
+
+// Threads per block of the resident loop, 0 where the plan or the device does
+// not fit it (a row of more than RES_COLS entries; more rows than the device
+// holds at a row per thread).  Measured per iteration, 512 against 1024
+// threads: FP64 6.7 / 8.7 us at 32768 rows and 8.4 / 10.2 at 130050 (1024
+// threads leave it 128 registers, and it spills), but only 1024 hold 262144
+// rows (11.3); FP32 8.0 / 7.3 us and 9.8 / 9.2 (fewer blocks to wait for).
+template <typename T>
+int resident_block(rp_plan* p, int* out) {
+    int& bt = p->resident_block[sizeof(T) == 4];
+    if (bt < 0) {
+        const int64_t n = p->n_rows;
+        int cus = 0, coop = 0, fit = 0;
+        RP_HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, p->device));
+        RP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+        if (coop && p->max_row <= RES_COLS && n <= (int64_t)RES_GROUPS * SPMV_BLOCK)
+            for (int t = sizeof(T) == 8 ? 512 : 1024; t <= 1024 && fit == 0; t *= 2) {
+                int per_cu = 0;
+                RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<T>(t), t, 0));
+                if (n <= (int64_t)cus * per_cu * t) fit = t;
+            }
+        bt = fit;
+    }
+    *out = bt;
+    return RP_OK;
+}
+
+template int resident_block<double>(rp_plan*, int*);
+template int resident_block<float>(rp_plan*, int*);
+
+// The iterations k0 .. min(k_end, budget) by the resident loop, enqueued, on a
+// plan that fits it (resident_block > 0).  The abort word goes to h_flags[2],
+// to be looked at once the stream has passed.
+template <typename T>
+int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
+                       const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s) {
+    const int bt = p->resident_block[sizeof(T) == 4];
+    int32_t ng = (n + SPMV_BLOCK - 1) / SPMV_BLOCK;
+    // slots of either precision: the sums, then z
+    typedef typename Word<T>::type W;
+    const int64_t len = (int64_t)RES_SETS * (3 * RES_GROUPS + n);
+    if (!p->d_slots) RP_HIP_TRY(hipMalloc(&p->d_slots, len * sizeof(uint64_t)));
+    if (!p->d_loop_bar) RP_HIP_TRY(hipMalloc(&p->d_loop_bar, BAR_WORDS * sizeof(uint32_t)));
+    W* slots = (W*)p->d_slots;
+    W* zs = slots + RES_SETS * 3 * RES_GROUPS;
+    uint32_t* bar = p->d_loop_bar;
+    hipLaunchKernelGGL(clear_slots, dim3(256), dim3(256), 0, s, (uint32_t*)slots, (int32_t)(len * sizeof(W) / 4), bar);
+    RP_HIP_TRY(hipGetLastError());
+    void* args[] = {&n, &ng, (void*)&row_ptr, (void*)&col, (void*)&val, (void*)&dinv, &x, &r, &pv, &st, &k0, &k_end,
+                    &slots, &zs, &bar};
+    RP_HIP_TRY(hipLaunchCooperativeKernel(resident_kernel<T>(bt), dim3((n + bt - 1) / bt), dim3(bt), args, 0, s));
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + 2, p->d_loop_bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    return RP_OK;
+}
+
+template int launch_cg_resident<double>(rp_plan*, int32_t, const int32_t*, const int32_t*, const double*,
+                                        const double*, double*, double*, double*, CgState<double>*, int32_t, int32_t,
+                                        hipStream_t);
+template int launch_cg_resident<float>(rp_plan*, int32_t, const int32_t*, const int32_t*, const float*, const float*,
+                                       float*, float*, float*, CgState<float>*, int32_t, int32_t, hipStream_t);
 template int launch_cg_loop<double>(rp_plan*, int32_t, const SpmvIdx&, const double*, const double*, double*,
                                     double*, double*, double*, CgState<double>*, int32_t, int32_t, hipStream_t, bool*);
 template int launch_cg_loop<float>(rp_plan*, int32_t, const SpmvIdx&, const float*, const float*, float*, float*,

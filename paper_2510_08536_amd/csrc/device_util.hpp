@@ -12,11 +12,44 @@
 namespace rp {
 
 // ---- wavefront (64 lanes) ------------------------------------------------
+// the value another lane of the 16-lane row holds (DPP control word), and the
+// value of lane l, for 4- and 8-byte types
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_row(T v) {
+    constexpr int N = sizeof(T) / 4;
+    int32_t w[N];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = __builtin_amdgcn_mov_dpp(w[i], CTRL, 0xF, 0xF, true);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int l) {
+    constexpr int N = sizeof(T) / 4;
+    int32_t w[N];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = __builtin_amdgcn_readlane(w[i], l);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
+// Sum over the wave, in every lane (all 64 lanes active): pairs of lanes,
+// quads, eights and rows of 16 by DPP (the mirrors meet the other half, whose
+// lanes all hold its sum), then the four rows' sums.  Register moves instead
+// of six trips through LDS: a reduction's latency, which small kernels and
+// the starts of all solver kernels wait for, is a few times shorter.
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma clang fp contract(off)
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_row<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+    v += dpp_row<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+    v += dpp_row<0x141>(v);   // row_half_mirror
+    v += dpp_row<0x140>(v);   // row_mirror
+    const T a = lane_value(v, 0) + lane_value(v, 16);
+    const T b = lane_value(v, 32) + lane_value(v, 48);
+    return a + b;
 }
 
 __device__ __forceinline__ int32_t wave_incl_scan(int32_t v) {

@@ -418,7 +418,8 @@ goi_encode(int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __rest
     if (t < GOI_KMAX) goi_off[(int64_t)g * GOI_KMAX + t] = t < K ? tab[t] : 0;
 }
 
-// out[g] = k of group g, out[ng + g] = row_ptr[g * SPMV_BLOCK], out[2 ng] = row_ptr[n]
+// out[g] = k of group g, out[ng + g] = row_ptr[g * SPMV_BLOCK], out[2 ng] =
+// row_ptr[n], out[2 ng + 1] = 0
 __global__ void goi_summary(int32_t n, int32_t ng, const int32_t* __restrict__ row_ptr,
                             const int32_t* __restrict__ goi_k, int32_t* __restrict__ out) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -426,11 +427,25 @@ __global__ void goi_summary(int32_t n, int32_t ng, const int32_t* __restrict__ r
         out[g] = goi_k[g];
         out[ng + g] = row_ptr[g * SPMV_BLOCK];
     }
-    if (g == 0) out[2 * (int64_t)ng] = row_ptr[n];
+    if (g == 0) {
+        out[2 * (int64_t)ng] = row_ptr[n];
+        out[2 * (int64_t)ng + 1] = 0;   // longest_row's result
+    }
+}
+
+// *out = the longest row's entries (*out = 0 on entry)
+__global__ void __launch_bounds__(SPMV_BLOCK)
+longest_row(int32_t n, const int32_t* __restrict__ row_ptr, int32_t* out) {
+    __shared__ int32_t red[SPMV_BLOCK / 64];
+    int32_t m = 0;
+    for (int32_t i = blockIdx.x * SPMV_BLOCK + threadIdx.x; i < n; i += gridDim.x * SPMV_BLOCK)
+        m = max(m, row_ptr[i + 1] - row_ptr[i]);
+    m = -block_min_i32(-m, red);
+    if (threadIdx.x == 0) atomicMax(out, m);
 }
 
 // Build the coded index and count what it covers (n_groups, coded_groups,
-// coded_rows, coded_nnz).
+// coded_rows, coded_nnz), and the longest row.
 int goi_build(rp_plan* p, hipStream_t s) {
     const int64_t n = p->n_rows;
     const int64_t ng = (n + SPMV_BLOCK - 1) / SPMV_BLOCK;
@@ -446,15 +461,18 @@ int goi_build(rp_plan* p, hipStream_t s) {
     // per group: k and the first entry (row_ptr at every SPMV_BLOCK-th row),
     // gathered on the device and copied back in one piece
     int32_t* d_sum = nullptr;
-    RP_HIP_TRY(hipMalloc(&d_sum, sizeof(int32_t) * (2 * ng + 1)));
-    std::vector<int32_t> h(2 * ng + 1);
+    RP_HIP_TRY(hipMalloc(&d_sum, sizeof(int32_t) * (2 * ng + 2)));
+    std::vector<int32_t> h(2 * ng + 2);
     hipLaunchKernelGGL(goi_summary, dim3((uint32_t)((ng + 255) / 256)), dim3(256), 0, s, (int32_t)n, (int32_t)ng,
                        p->d_row_ptr, p->d_goi_k, d_sum);
+    hipLaunchKernelGGL(longest_row, dim3((uint32_t)std::min<int64_t>(ng, 1024)), dim3(SPMV_BLOCK), 0, s, (int32_t)n,
+                       p->d_row_ptr, d_sum + 2 * ng + 1);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), d_sum, sizeof(int32_t) * (2 * ng + 1), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), d_sum, sizeof(int32_t) * (2 * ng + 2), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(d_sum);
     RP_HIP_TRY(e);
+    p->max_row = h[2 * ng + 1];
     const int32_t* k = h.data();
     const int32_t* start = h.data() + ng;
     for (int64_t g = 0; g < ng; ++g) {

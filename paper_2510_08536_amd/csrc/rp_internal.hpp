@@ -254,7 +254,7 @@ struct rp_plan {
     rp::BiState* h_bi_st = nullptr;
     double* d_bi_work = nullptr;             // [5 n_rows] BiCGStab vectors rh, y, s, z, t (first use)
     uint32_t* d_flags = nullptr;     // [2] error bits, asymmetry flag
-    uint32_t* h_flags = nullptr;     // pinned mirror
+    uint32_t* h_flags = nullptr;     // pinned mirror; [2]: abort word of the resident CG loop
 
     // offset-coded SpMV index (see spmv.hpp), built with the pattern
     int32_t* d_goi_k = nullptr;      // [groups] offsets per group, 0 = CSR group
@@ -262,6 +262,7 @@ struct rp_plan {
     uint16_t* d_goi_mask = nullptr;  // [n_rows]
     int32_t goi_on = 1;              // the kernels use the coded groups
     int64_t n_groups = 0, coded_groups = 0, coded_rows = 0, coded_nnz = 0;
+    int32_t max_row = 0;             // entries of the longest row
 
     // x windows of the SpMV (see spmv.hpp): -1 none, 0 diagonal, 1..2 +-d pairs;
     // xw_mode is what the kernels use: xw_found when enabled, else -1
@@ -302,6 +303,8 @@ struct rp_plan {
     float* d_z32 = nullptr;            // [n_rows] of the FP32 iteration
     uint32_t* d_bj_flag = nullptr;     // set when a block is not positive definite
 
+    uint64_t* d_slots = nullptr;       // what the resident CG loop exchanges (cg_loop.hip)
+    int resident_block[2] = {-1, -1};  // its block size in FP64, FP32; 0: the plan does not fit it; -1: not asked yet
     uint32_t* d_loop_bar = nullptr;    // abort word and per-block barrier flags of the CG loop (cg_loop.hip)
 
     rp::AmgHier* amg = nullptr;        // multigrid hierarchy (RP_PRECOND_AMG), built on first use
@@ -336,8 +339,12 @@ inline int spmv_grid(int64_t n_rows) {
 }
 // elementwise kernels: grid-stride loops over at most VEC_GRID_MAX blocks
 constexpr int VEC_GRID_MAX = 1024;  // 512 and 2048 measured slower for K2/K3
+// Systems of at most RP_LOOP_TWO_MAX_ROWS rows get one element per thread, so
+// that a block's partial sums are those of one SpMV row group (the resident
+// CG loop forms its sums per row group too, and all forms agree bit for bit).
 inline int vec_grid(int64_t n) {
-    int64_t g = (n + VEC_BLOCK * 4 - 1) / (VEC_BLOCK * 4);
+    const int64_t per = n <= RP_LOOP_TWO_MAX_ROWS ? 1 : 4;
+    int64_t g = (n + VEC_BLOCK * per - 1) / (VEC_BLOCK * per);
     if (g < 1) g = 1;
     if (g > VEC_GRID_MAX) g = VEC_GRID_MAX;
     return (int)g;
