@@ -84,9 +84,9 @@ extern "C" {
                                      with at most this many rows down runs in one workgroup */
 
 /* ---- launches per Jacobi-PCG iteration (rp_solve_opts.fused_loop) ------- */
-#define RP_LOOP_AUTO 0            /* on systems of at most RP_LOOP_TWO_MAX_ROWS rows all
-                                     iterations in one launch, or two launches each where
-                                     a row has more than 8 entries; three on larger ones */
+#define RP_LOOP_AUTO 0            /* all iterations in one launch where the system fits it
+                                     (see fused_loop); else two launches each on systems of
+                                     at most RP_LOOP_TWO_MAX_ROWS rows, three on larger ones */
 #define RP_LOOP_COOPERATIVE 1     /* all iterations in one cooperative launch */
 #define RP_LOOP_THREE 2           /* three launches (SpMV; r update; x and p update) */
 #define RP_LOOP_TWO_MAX_ROWS 262144
@@ -145,14 +145,18 @@ typedef struct rp_solve_opts {
     int32_t fused_loop;      /* RP_CG with Jacobi, how an iteration is launched.
                                 RP_LOOP_THREE: one launch per phase (SpMV with (p, q);
                                 r update with (r, z), (r, r); x and p update).
-                                RP_LOOP_AUTO (default): the same on systems above
-                                RP_LOOP_TWO_MAX_ROWS rows; on smaller ones all iterations in
-                                one cooperative launch that keeps the system in registers
-                                and exchanges values, without barriers (every row at most 8
-                                entries, and the device holds a thread per row); else two
-                                launches, the x and p update of iteration k fused with the
-                                SpMV of k + 1 (each row forms the new p of its columns
-                                itself).  Results bit-identical to RP_LOOP_THREE.
+                                RP_LOOP_AUTO (default): all iterations in one cooperative
+                                launch that exchanges values instead of waiting at barriers,
+                                on systems of at most RP_LOOP_TWO_MAX_ROWS rows (every row
+                                at most 8 entries) with the system in registers, and in fused
+                                order on medium ones (2 million rows in FP64, 4 in FP32, a
+                                row at most 7 entries, rows numbered with locality) with the
+                                vectors in registers and LDS.  Else two launches on systems
+                                of at most RP_LOOP_TWO_MAX_ROWS rows, the x and p update of
+                                iteration k fused with the SpMV of k + 1 (each row forms the
+                                new p of its columns itself), and RP_LOOP_THREE on larger
+                                ones.  Results bit-identical to RP_LOOP_THREE, on medium
+                                systems up to the rounding of the dot products.
                                 RP_LOOP_COOPERATIVE: all iterations in one cooperative
                                 launch (the phases separated by grid-wide barriers; same
                                 arithmetic, partial sums over a smaller grid); on MI355X it

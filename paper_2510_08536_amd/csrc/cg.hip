@@ -11,7 +11,8 @@
 // registers (cg_resident in cg_loop.hip), or, where its rows are too long for
 // that, K3 of iteration k and K1 of iteration k + 1 as one kernel
 // (cg_update_xp_spmv), two launches per iteration; the same results bit for
-// bit either way.
+// bit either way.  Medium systems run every iteration in one launch that keeps
+// the vectors in registers and LDS and streams the matrix (cg_tile.hip).
 // Each kernel starts by adding up the previous kernel's per-block partials
 // (every block the same sum, in index order), so reductions need no atomics,
 // no fences and no extra launches, and reruns are bit-identical.  The
@@ -55,6 +56,12 @@ int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int3
                        const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s);
 template <typename T>
 int resident_block(rp_plan* p, int* out);
+// cg_tile.hip: the same on medium systems in fused order
+template <typename T>
+int tile_fits(rp_plan* p, hipStream_t s, bool* yes);
+template <typename T>
+int launch_cg_tile(rp_plan* p, const T* val, const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0,
+                   int32_t k_end, hipStream_t s);
 
 namespace {
 
@@ -1027,26 +1034,34 @@ int iterate_two(Cg<T>& c, int chunk, int32_t max_iter) {
     return RP_OK;
 }
 
-// whether these options run the iterations of c in the resident loop, which
-// looks at the device state itself: a solve may then enqueue it behind the
-// start kernels without reading their state (start_ahead)
+// The one-launch loop that runs the iterations of c under these options, if
+// any.  The loops look at the device state themselves: a solve may enqueue one
+// behind the start kernels without reading their state (start_ahead).
+enum class Loop { LAUNCHES, RESIDENT, TILE };
+
 template <typename T>
-int runs_resident(const Cg<T>& c, const rp_solve_opts& o, bool* yes) {
-    *yes = false;
-    if (o.fused_loop != RP_LOOP_AUTO || c.n > RP_LOOP_TWO_MAX_ROWS || c.plan->timing.enabled || o.graph ||
-        c.bj_minv || c.amg || c.plan->vec_grid_override != 0)   // its sums are those of the default vector grid
+int choose_loop(const Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
+    *loop = Loop::LAUNCHES;
+    if (o.fused_loop != RP_LOOP_AUTO || c.plan->timing.enabled || o.graph || c.bj_minv || c.amg ||
+        c.plan->vec_grid_override != 0)   // a fixed vector grid asks for the launched kernels
         return RP_OK;
-    int bt = 0;
-    RP_TRY(resident_block<T>(c.plan, &bt));
-    *yes = bt > 0;
+    if (c.n <= RP_LOOP_TWO_MAX_ROWS) {
+        int bt = 0;
+        RP_TRY(resident_block<T>(c.plan, &bt));
+        if (bt > 0) *loop = Loop::RESIDENT;
+    } else if (c.ix.row_ptr == c.plan->d_row_ptr) {   // the tiles are the fused order's
+        bool fits = false;
+        RP_TRY(tile_fits<T>(c.plan, c.s, &fits));
+        if (fits) *loop = Loop::TILE;
+    }
     return RP_OK;
 }
 
-// the state after launch_start at iteration k: read it, or (resident) take
-// it as running; the loop's own read brings the truth
+// the state after launch_start at iteration k: read it, or (one-launch loops)
+// take it as running; the loop's own read brings the truth
 template <typename T>
-int start_ahead(Cg<T>& c, bool resident, int32_t k, int32_t max_iter) {
-    if (!resident || k >= max_iter) return read_state(c);
+int start_ahead(Cg<T>& c, Loop loop, int32_t k, int32_t max_iter) {
+    if (loop == Loop::LAUNCHES || k >= max_iter) return read_state(c);
     c.h->done = CG_RUNNING;
     c.h->iter = k;
     return RP_OK;
@@ -1057,20 +1072,23 @@ int start_ahead(Cg<T>& c, bool resident, int32_t k, int32_t max_iter) {
 // replay of a captured graph of `chunk` iterations (kernels past max_iter do
 // nothing); per-kernel timing always launches eagerly.
 template <typename T>
-int iterate(Cg<T>& c, const rp_solve_opts& o, bool resident) {
+int iterate(Cg<T>& c, const rp_solve_opts& o, Loop loop) {
     const bool timed = c.plan->timing.enabled, graph = o.graph != 0;
     const int chunk = std::max(1, o.check_every);
     const int32_t max_iter = o.max_iter, fused_loop = o.fused_loop;
-    if (resident) {
+    if (loop != Loop::LAUNCHES) {
         // a launch's length is bounded: other work on the device waits for it
         constexpr int64_t LOOP_ITERS = 1 << 16;
         while (c.h->done == CG_RUNNING && c.h->iter < max_iter) {
             const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)c.h->iter + LOOP_ITERS, max_iter);
-            RP_TRY(launch_cg_resident<T>(c.plan, c.n, c.ix.row_ptr, c.ix.col, c.val, c.dinv, c.x, c.r, c.p, c.st,
-                                         c.h->iter, k1, c.s));
+            if (loop == Loop::RESIDENT)
+                RP_TRY(launch_cg_resident<T>(c.plan, c.n, c.ix.row_ptr, c.ix.col, c.val, c.dinv, c.x, c.r, c.p, c.st,
+                                             c.h->iter, k1, c.s));
+            else
+                RP_TRY(launch_cg_tile<T>(c.plan, c.val, c.dinv, c.x, c.r, c.p, c.st, c.h->iter, k1, c.s));
             RP_TRY(read_state(c));
             if (c.plan->h_flags[2]) {
-                set_error("the resident CG loop gave up waiting for another workgroup's values");
+                set_error("the one-launch CG loop gave up waiting for another workgroup's values");
                 return RP_ERR_HIP;
             }
         }
@@ -1174,11 +1192,11 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
         use_amg(c, p->d_z, ordered);
     }
     const double tol2 = o.tol * o.tol;
-    bool resident = false;
-    RP_TRY(runs_resident(c, o, &resident));
+    Loop loop;
+    RP_TRY(choose_loop(c, o, &loop));
     RP_TRY((launch_residual<double, false>(c, o.x0_zero != 0, nullptr)));
     RP_TRY(launch_start(c, 0, tol2, 0.0, o.max_iter));
-    RP_TRY(start_ahead(c, resident, 0, o.max_iter));
+    RP_TRY(start_ahead(c, loop, 0, o.max_iter));
     bool fresh = true;  // rr_true belongs to the current x
     int status = RP_NOT_CONVERGED;
     info.restarts = 0;
@@ -1214,7 +1232,7 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
         }
         if (c.h->iter >= o.max_iter) break;
         const int32_t it_before = c.h->iter;
-        RP_TRY(iterate(c, o, resident));
+        RP_TRY(iterate(c, o, loop));
         if (c.h->iter > it_before || c.h->done == CG_RUNNING) fresh = false;
     }
     if (!fresh && c.h->done != CG_ZERO_RHS) {
@@ -1250,8 +1268,8 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
         RP_TRY(amg_prepare(p, true, s, ordered));
         use_amg(in, p->d_z32, ordered);
     }
-    bool resident = false;
-    RP_TRY(runs_resident(in, o, &resident));
+    Loop loop;
+    RP_TRY(choose_loop(in, o, &loop));
 
     RP_TRY((launch_residual<double, true>(out, o.x0_zero != 0, p->d_r32)));
     RP_TRY(launch_finalize(out, FIN_RESIDUAL, 0, 0.0, 0.0));
@@ -1287,11 +1305,11 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
             }
             RP_TRY((launch_residual<float, false>(in, true, nullptr)));
             RP_TRY(launch_start(in, total_inner, tol2_in, pause2, o.max_iter));
-            RP_TRY(start_ahead(in, resident, total_inner, o.max_iter));
+            RP_TRY(start_ahead(in, loop, total_inner, o.max_iter));
             start_inner = false;
         }
         const int32_t it_before = in.h->iter;
-        RP_TRY(iterate(in, o, resident));
+        RP_TRY(iterate(in, o, loop));
         total_inner = in.h->iter;
         const int32_t d = in.h->done;
         // fold the FP32 correction into x and take the FP64 residual
@@ -1317,7 +1335,7 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
         if (total_inner >= o.max_iter || outer >= o.max_outer || stall >= 4) break;
         if (reliable && d == CG_PAUSED) {
             RP_TRY(launch_resume(in));   // keep the search direction, replaced residual
-            RP_TRY(start_ahead(in, resident, total_inner, o.max_iter));
+            RP_TRY(start_ahead(in, loop, total_inner, o.max_iter));
         } else {
             start_inner = true;          // restart FP32 PCG on the new residual
         }

@@ -25,20 +25,16 @@
 // word and leaves, and every block that sees the abort word leaves too; the
 // host reports it.  The flags and the abort word are cleared by a kernel
 // before each launch.
+#include "exchange.hpp"
 #include "spmv.hpp"
 
 namespace rp {
 
 namespace {
 
-constexpr uint32_t BAR_SPINS = 1u << 22;   // a few seconds of polling at most
 constexpr int FLAG_STRIDE = 32;            // words: one 128-byte line per block flag
 constexpr int FLAG0 = FLAG_STRIDE;         // word 0: abort word; flags from line 1
 constexpr int LOOP_GRID_MAX = 128;
-
-__device__ __forceinline__ uint32_t load_relaxed(const uint32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // all blocks of the grid; false when the wait was abandoned.  seq counts
 // the barriers of this launch (the same in every block).
@@ -213,96 +209,11 @@ cg_loop(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict__ 
 // ---------------------------------------------------------------------------
 constexpr int RES_COLS = 8;                    // entries per row at most
 constexpr int RES_GROUPS = VEC_GRID_MAX;       // row groups at most
-constexpr int RES_SETS = 4;
-
-// a value as the word it is exchanged as
-template <typename T>
-struct Word;
-template <>
-struct Word<double> {
-    typedef uint64_t type;
-    static constexpr type EMPTY = ~0ull;
-    static __device__ __forceinline__ type of(double v) {
-        return v == v ? (type)__double_as_longlong(v) : 0x7FF8000000000000ull;
-    }
-    static __device__ __forceinline__ double value(type u) { return __longlong_as_double((long long)u); }
-};
-template <>
-struct Word<float> {
-    typedef uint32_t type;
-    static constexpr type EMPTY = ~0u;
-    static __device__ __forceinline__ type of(float v) { return v == v ? __float_as_uint(v) : 0x7FC00000u; }
-    static __device__ __forceinline__ float value(type u) { return __uint_as_float(u); }
-};
-
-template <typename V>
-__device__ __forceinline__ V agent_load(const V* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// from a byte offset to a base that is the same in every lane (one address register)
-template <typename V>
-__device__ __forceinline__ V agent_load_at(const V* base, uint32_t bytes) {
-    return agent_load(reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + bytes));
-}
-template <typename V>
-__device__ __forceinline__ void agent_store(V* p, V v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // every slot empty (all-ones words of either size), no abort
 __global__ void clear_slots(uint32_t* slots, int32_t words, uint32_t* bar) {
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) slots[i] = ~0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) bar[0] = 0u;
-}
-
-// spins of one wait: true = give up (too many, or another block gave up)
-__device__ __forceinline__ bool wait_over(uint32_t& spins, const uint32_t* bar) {
-    return ++spins > BAR_SPINS || (spins % 256 == 0 && load_relaxed(bar) != 0u);
-}
-
-// The sums of N values per group once no slot of slots[0 .. N ng) is empty
-// (value j of group m at N m + j), added up as sum_partials_all does it with
-// SPMV_BLOCK threads: thread t adds groups t, t + 256, ...; the wave sums go
-// to red[j][0 .. 4).  False: the wait was abandoned.
-template <typename T, int N>
-__device__ __forceinline__ bool gather_slots(const typename Word<T>::type* slots, int32_t ng, int32_t t,
-                                             const uint32_t* bar, T (*red)[SPMV_BLOCK / 64]) {
-#pragma clang fp contract(off)
-    T s[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) s[j] = T(0);
-    bool good = true;
-    for (int32_t m = t; m < ng; m += SPMV_BLOCK) {
-        typename Word<T>::type u[N];
-        for (uint32_t spins = 0;;) {
-            bool empty = false;
-#pragma unroll
-            for (int j = 0; j < N; ++j) u[j] = agent_load(slots + N * m + j);
-#pragma unroll
-            for (int j = 0; j < N; ++j) empty |= u[j] == Word<T>::EMPTY;
-            if (!empty) break;
-            if (wait_over(spins, bar)) {
-                good = false;
-                break;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < N; ++j) s[j] += Word<T>::value(u[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        s[j] = wave_sum(s[j]);
-        if ((t & 63) == 0) red[j][t >> 6] = s[j];
-    }
-    return good;
-}
-
-template <typename T>
-__device__ __forceinline__ T sum_red(const T* red) {
-#pragma clang fp contract(off)
-    T s = T(0);
-    for (int w = 0; w < SPMV_BLOCK / 64; ++w) s += red[w];
-    return s;
 }
 
 // BT threads per block: BT / SPMV_BLOCK row groups.  slots: RES_SETS sets of

@@ -1,0 +1,610 @@
+// CG iterations on medium systems in one cooperative launch: one workgroup
+// per compute unit, each owning a tile of consecutive rows for the whole
+// launch.
+//
+// With three launches an iteration of a system of 10^6 rows spends some 13 us
+// on launches and 10 n words on vectors.  Here x, r, z and M^-1 of a thread's
+// rows stay in registers and p of the tile in LDS, together with p of its
+// halo (the columns of its rows that other tiles own), so an iteration reads
+// the matrix's values once, from the 256 MB memory-side cache where they fit
+// it, and nothing else of size: the taps of the product come from LDS.  As in
+// the resident loop for small systems (cg_loop.hip), an iteration exchanges
+// z = M^-1 r and the three sums by value (exchange.hpp), in two exchanges:
+//   (p, q) partials;   alpha, r, z;   z of the rows in other tiles' halos and
+//   the (r, z), (r, r) partials;      stop tests, x, beta, p of tile and halo.
+//
+// The plan builds, once, each tile's halo (sorted) and, per row, the places in
+// LDS of its columns (16-bit words, in column order); the values follow in
+// slices of 64 rows, entry by entry, so that a wavefront's loads are whole
+// lines.  They are refreshed by one pass when a solve finds them older than
+// the last update.  Row sums run in column order from 0, every product and sum
+// rounded once, so q is the SpMV's bit for bit; the dot products add a tile's
+// rows first, so they differ from the launched kernels' by rounding.
+//
+// A plan fits if no row has more than U entries, the tiles hold its rows (16 per
+// thread in FP64, 32 in FP32), and every tile's rows and halo fit LDS: a mesh
+// in a rank's natural order does; randomly numbered rows, whose halo is nearly
+// the whole rank, do not, and keep three launches.
+//
+// Per iteration against three launches: FP64 26.3 -> 11.2 us at 80^3 rows, 36.8
+// -> 16.4 at 96^3, 57.2 -> 23.6 at 110 x 108 x 112, 68.5 -> 38.2 at 128^3; FP32
+// 20.6 -> 9.6, 28.1 -> 12.1, 44.5 -> 15.6, 46.7 -> 20.0, and 72.6 -> 50 at 160^3.
+// About 7 us of it are the exchanges; the rest streams the values and, past
+// some 10 rows per thread, the places (128^3 FP64: 150 MB at 4.8 TB/s).
+// Non-temporal loads of the values made it slower (16.4 -> 18 us at 96^3: they
+// come from the caches), more rows in flight no faster.
+#include <algorithm>
+#include <utility>
+#include <vector>
+
+#include "exchange.hpp"
+
+namespace rp {
+
+namespace {
+
+constexpr int TT = 512;                 // threads per block: 8 wavefronts, 256 registers each
+constexpr int U = 7;                    // entries per row at most: a cell and its six faces
+constexpr int HALO_PER_THREAD = 16;
+constexpr int HALO_MAX = HALO_PER_THREAD * TT;
+constexpr int LIST_MAX = 16384;         // halo entries with repeats, while building
+
+// words of p (tile and halo) in LDS
+template <typename T>
+constexpr int lds_words() { return sizeof(T) == 8 ? 18432 : 36864; }   // 144 KB
+
+struct __align__(16) Places {
+    uint32_t w[4];   // entry 2 i in the low half of w[i], the next one in the high half
+};
+
+// ---- structure ---------------------------------------------------------------
+// One block per tile b, rows first[b] .. first[b + 1) (R at most): collect the
+// columns outside the tile, sort them in LDS, drop repeats -> halo and its
+// length (-1: does not fit); then the places, row l of tile b at b R + l.
+__global__ void __launch_bounds__(1024)
+tile_build(int32_t R, const int32_t* __restrict__ first, const int32_t* __restrict__ row_ptr,
+           const int32_t* __restrict__ col, int32_t* __restrict__ halo, int32_t* __restrict__ n_halo,
+           Places* __restrict__ places) {
+    __shared__ int32_t list[LIST_MAX];
+    __shared__ int32_t uniq[HALO_MAX];
+    __shared__ int32_t wtot[16];
+    __shared__ int32_t count;
+    const int32_t t = threadIdx.x, b = blockIdx.x;
+    const int32_t base = first[b], rows = first[b + 1] - base;
+    Places* const pb = places + (int64_t)b * R;
+    if (t == 0) count = 0;
+    __syncthreads();
+    for (int32_t i = t; i < rows; i += 1024)
+        for (int32_t e = row_ptr[base + i]; e < row_ptr[base + i + 1]; ++e) {
+            const int32_t c = col[e] - base;
+            if (c < 0 || c >= rows) {
+                const int32_t at = atomicAdd(&count, 1);
+                if (at < LIST_MAX) list[at] = c + base;
+            }
+        }
+    __syncthreads();
+    const int32_t m = count;
+    if (m > LIST_MAX) {
+        if (t == 0) n_halo[b] = -1;
+        return;
+    }
+    int32_t P2 = 1;
+    while (P2 < m) P2 *= 2;
+    for (int32_t i = m + t; i < P2; i += 1024) list[i] = INT32_MAX;
+    __syncthreads();
+    for (int32_t k = 2; k <= P2; k *= 2)
+        for (int32_t j = k / 2; j > 0; j /= 2) {
+            for (int32_t i = t; i < P2; i += 1024) {
+                const int32_t o = i ^ j;
+                if (o > i) {
+                    const int32_t x = list[i], y = list[o];
+                    if ((x > y) == ((i & k) == 0)) {
+                        list[i] = y;
+                        list[o] = x;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    // each thread takes LIST_MAX / 1024 consecutive elements of the sorted list
+    constexpr int PER = LIST_MAX / 1024;
+    int32_t c = 0;
+    for (int32_t i = t * PER; i < min(m, t * PER + PER); ++i) c += i == 0 || list[i] != list[i - 1];
+    const int32_t inc = wave_incl_scan(c);
+    if ((t & 63) == 63) wtot[t >> 6] = inc;
+    __syncthreads();
+    int32_t at = inc - c, H = 0;
+    for (int q = 0; q < 16; ++q) {
+        if (q < (t >> 6)) at += wtot[q];
+        H += wtot[q];
+    }
+    if (H > HALO_MAX) {
+        if (t == 0) n_halo[b] = -1;
+        return;
+    }
+    for (int32_t i = t * PER; i < min(m, t * PER + PER); ++i)
+        if (i == 0 || list[i] != list[i - 1]) uniq[at++] = list[i];
+    __syncthreads();
+    for (int32_t i = t; i < H; i += 1024) halo[(int64_t)b * HALO_MAX + i] = uniq[i];
+    if (t == 0) n_halo[b] = H;
+    for (int32_t i = t; i < rows; i += 1024) {
+        const int32_t e0 = row_ptr[base + i], len = row_ptr[base + i + 1] - e0;
+        Places pl;
+        for (int u = 0; u < 8; ++u) {
+            uint32_t w = (uint32_t)i;   // a missing entry: its own row's place, times 0
+            if (u < len) {
+                const int32_t g = col[e0 + u], cl = g - base;
+                if (cl >= 0 && cl < rows) {
+                    w = (uint32_t)cl;
+                } else {
+                    int32_t lo = 0, hi = H;
+                    while (lo < hi) {
+                        const int32_t mid = (lo + hi) >> 1;
+                        if (uniq[mid] < g) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    w = (uint32_t)(R + lo);
+                }
+            }
+            if (u % 2 == 0) pl.w[u / 2] = w;
+            else pl.w[u / 2] |= w << 16;
+        }
+        pb[i] = pl;
+    }
+    // the places past the tile's rows: no entries
+    for (int32_t i = rows + t; i < R; i += 1024) {
+        const uint32_t w = (uint32_t)i | ((uint32_t)i << 16);
+        pb[i] = Places{{w, w, w, w}};
+    }
+}
+
+// values in slices of 64 rows: entry u of row l of tile b at
+// ((b R + l) / 64 U + u) 64 + l % 64; zeros past the tile's rows
+template <typename T>
+__global__ void __launch_bounds__(256)
+tile_values(int32_t R, const int32_t* __restrict__ first, const int32_t* __restrict__ row_ptr,
+            const T* __restrict__ val, T* __restrict__ out) {
+    const int32_t base = first[blockIdx.y], rows = first[blockIdx.y + 1] - base;
+    const int32_t l = blockIdx.x * 256 + threadIdx.x;   // R is a multiple of 256
+    const int32_t e0 = l < rows ? row_ptr[base + l] : 0, len = l < rows ? row_ptr[base + l + 1] - e0 : 0;
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = u < len ? val[e0 + u] : T(0);
+    T* o = out + (((int64_t)blockIdx.y * R + l) >> 6) * U * 64 + (l & 63);
+#pragma unroll
+    for (int u = 0; u < U; ++u) o[u * 64] = v[u];
+}
+
+__global__ void clear_words(uint32_t* w, int64_t words, uint32_t* bar) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) w[i] = ~0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) bar[0] = 0u;
+}
+
+// ---- iterations ----------------------------------------------------------------
+__device__ __forceinline__ uint32_t place(const Places& pl, int u) {
+    return u % 2 == 0 ? pl.w[u / 2] & 0xFFFFu : pl.w[u / 2] >> 16;
+}
+
+// A pointer that is the same in every lane, hidden from the compiler: what is
+// loaded from it in a loop stays in the loop, and it is an address in scalar
+// registers to which every lane adds the same offset of its own.  (Left to
+// itself the compiler keeps an address per row and entry, or the values
+// themselves, for all iterations, and spills them.)
+template <typename P>
+__device__ __forceinline__ __attribute__((address_space(1))) P* hidden(P* p) {
+    __attribute__((address_space(1))) P* q = (__attribute__((address_space(1))) P*)p;
+    asm volatile("" : "+s"(q));
+    return q;
+}
+
+// sum over the block's TT threads, in every thread; red: TT / 64 words
+template <typename T>
+__device__ __forceinline__ T tile_sum(const T* red) {
+#pragma clang fp contract(off)
+    T s = T(0);
+    for (int w = 0; w < TT / 64; ++w) s += red[w];
+    return s;
+}
+
+// NR rows per thread: tiles of at most R = NR TT rows
+template <typename T, int NR>
+__global__ void __launch_bounds__(TT)
+cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict__ halo, const int32_t* __restrict__ n_halo,
+        const Places* __restrict__ places, const T* __restrict__ val, const T* __restrict__ dinv, T* __restrict__ x,
+        T* __restrict__ r, T* __restrict__ p, CgState<T>* st, int32_t k0, int32_t k_end,
+        typename Word<T>::type* slots, typename Word<T>::type* zs, uint32_t* bar) {
+#pragma clang fp contract(off)
+    typedef typename Word<T>::type W;
+    constexpr W EMPTY = Word<T>::EMPTY;
+    constexpr int R = NR * TT;
+    constexpr int D = sizeof(T) == 8 ? 2 : 3;   // rows whose loads are in flight (more: no gain)
+    // rows whose places stay in registers, as many as these allow without
+    // spilling; the others' are read every iteration
+    constexpr int W32 = sizeof(T) / 4;
+    constexpr int FREE = (256 - 4 * W32 * NR - D * U * W32 - (W32 == 2 ? 140 : 112)) / 4;   // the rest measured
+    constexpr int KEEP = FREE < NR ? (FREE > 0 ? FREE : 0) : NR;
+    __shared__ T P[lds_words<T>()];
+    __shared__ T red1[TT / 64], red2[TT / 64];
+    __shared__ T all[2][SPMV_BLOCK / 64];
+    __shared__ int32_t bad;
+    if (st->done != CG_RUNNING) return;
+    const int32_t t = threadIdx.x, b = blockIdx.x, G = gridDim.x;
+    const int32_t base = first[b], rows = first[b + 1] - base, H = n_halo[b];
+    const int32_t k_stop = min(k_end, st->max_iter);
+    const T thresh = st->thresh, pause_thresh = st->pause_thresh;
+    T rz = st->rz[k0 & 3];
+    T xv[NR], rv[NR], zv[NR], dv[NR];   // zv: q between the exchanges, then z
+    Places pk[KEEP > 0 ? KEEP : 1];
+    int32_t hid[HALO_PER_THREAD];       // byte offsets of the halo's rows, -1: none
+    uint32_t remote = 0;                // rows in other tiles' halos, a bit each
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const int32_t l = j * TT + t;
+        xv[j] = rv[j] = zv[j] = dv[j] = T(0);
+        if (l < rows) {
+            const int32_t i = base + l;
+            xv[j] = x[i];
+            rv[j] = r[i];
+            dv[j] = dinv[i];
+            P[l] = p[i];
+        } else {
+            P[l] = T(0);
+        }
+        const Places pl = places[b * R + l];
+        bool out = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) out |= place(pl, u) >= (uint32_t)R;
+        remote |= (uint32_t)out << j;
+        if (j < KEEP) pk[j < KEEP ? j : 0] = pl;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int h = 0; h < HALO_PER_THREAD; ++h) {
+        const int32_t l = h * TT + t;
+        hid[h] = -1;
+        if (l < H) {
+            const int32_t c = halo[(int64_t)b * HALO_MAX + l];
+            P[R + l] = p[c];
+            hid[h] = c * (int32_t)sizeof(W);
+        }
+    }
+    if (t == 0) bad = 0;
+    __syncthreads();
+    int32_t k = k0, stop = CG_RUNNING;
+    T pq = T(0), a = T(0), beta = T(0), rr = T(0);
+    bool given_up = false;
+    const int32_t lane0 = (t >> 6) * U * 64 + (t & 63);
+    for (; k < k_stop; ++k) {
+        W* const s_pq = slots + (k % RES_SETS) * 3 * SPMV_BLOCK;
+        W* const s_rr = s_pq + SPMV_BLOCK;   // (r, z) and (r, r), a pair per tile
+        W* const z_k = zs + (int64_t)(k % RES_SETS) * n;
+        // q = A p, partial of (p, q)
+        T ppq = T(0);
+        T v[D][U];
+        Places pl[D];
+#pragma unroll
+        for (int j = 0; j < NR + D - 1; ++j) {
+            if (j < NR) {
+                const auto vj = hidden(val + ((int64_t)b * (R / 64) + j * (TT / 64)) * U * 64);
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[j % D][u] = vj[u * 64 + lane0];
+                if (j >= KEEP) pl[j % D] = *(const Places*)(hidden(places + b * R + j * TT) + t);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // D rows ahead and no more
+            if (j >= D - 1) {
+                const int i = j - (D - 1);
+                Places q_pl = i < KEEP ? pk[i < KEEP ? i : 0] : pl[i % D];
+                // unpacked here, not once for all iterations (7 registers a row)
+                if (i < KEEP)
+                    asm volatile("" : "+v"(q_pl.w[0]), "+v"(q_pl.w[1]), "+v"(q_pl.w[2]), "+v"(q_pl.w[3]));
+                T q = T(0);
+#pragma unroll
+                for (int u = 0; u < U; ++u) q += v[i % D][u] * P[place(q_pl, u)];
+                zv[i] = q;
+                ppq += P[i * TT + t] * q;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        T w1 = wave_sum(ppq);
+        if ((t & 63) == 0) red1[t >> 6] = w1;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the slots emptied last time are
+        __syncthreads();
+        if (t == 0) agent_store(s_pq + b, Word<T>::of(tile_sum(red1)));
+        if (t < SPMV_BLOCK && !gather_slots<T, 1>(s_pq, G, t, bar, all)) bad = 1;
+        __syncthreads();
+        if (bad) {
+            given_up = true;
+            break;
+        }
+        pq = sum_red(all[0]);
+        if (!(pq > T(0)) || !isfinite(pq)) {
+            stop = CG_BREAKDOWN;
+            break;
+        }
+        a = rz / pq;
+        // r -= alpha q; z = M^-1 r; partials of (r, z), (r, r)
+        T prz = T(0), prr = T(0);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            rv[j] = rv[j] - a * zv[j];
+            const T zi = dv[j] * rv[j];
+            zv[j] = zi;
+            if (remote & (1u << j)) agent_store((W*)(hidden(z_k + (base + j * TT)) + t), Word<T>::of(zi));
+            prz += rv[j] * zi;
+            prr += rv[j] * rv[j];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        w1 = wave_sum(prz);
+        const T w2 = wave_sum(prr);
+        if ((t & 63) == 0) {
+            red1[t >> 6] = w1;
+            red2[t >> 6] = w2;
+        }
+        __syncthreads();
+        if (t == 0) {
+            agent_store(s_rr + 2 * b, Word<T>::of(tile_sum(red1)));
+            agent_store(s_rr + 2 * b + 1, Word<T>::of(tile_sum(red2)));
+        }
+        if (k > k0) {   // every tile is past iteration k - 1
+            W* const zo = zs + (int64_t)((k - 1) % RES_SETS) * n + base;
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (remote & (1u << j)) agent_store((W*)(hidden(zo + j * TT) + t), EMPTY);
+            if (t == 0) {
+                W* const old = slots + ((k - 1) % RES_SETS) * 3 * SPMV_BLOCK;
+                agent_store(old + b, EMPTY);
+                agent_store(old + SPMV_BLOCK + 2 * b, EMPTY);
+                agent_store(old + SPMV_BLOCK + 2 * b + 1, EMPTY);
+            }
+        }
+        W zh[HALO_PER_THREAD];
+#pragma unroll
+        for (int h = 0; h < HALO_PER_THREAD; ++h)
+            zh[h] = hid[h] >= 0 ? agent_load_at(z_k, (uint32_t)hid[h]) : W(0);
+        if (t < SPMV_BLOCK && !gather_slots<T, 2>(s_rr, G, t, bar, all)) bad = 1;
+        for (uint32_t spins = 0;;) {
+            bool empty = false;
+#pragma unroll
+            for (int h = 0; h < HALO_PER_THREAD; ++h) empty |= zh[h] == EMPTY;
+            if (!empty) break;
+            if (wait_over(spins, bar)) {
+                bad = 1;
+                break;
+            }
+#pragma unroll
+            for (int h = 0; h < HALO_PER_THREAD; ++h)
+                if (zh[h] == EMPTY) zh[h] = agent_load_at(z_k, (uint32_t)hid[h]);
+        }
+        __syncthreads();
+        if (bad) {
+            given_up = true;
+            break;
+        }
+        const T rzn = sum_red(all[0]);
+        rr = sum_red(all[1]);
+        // x += alpha p; stop tests; beta = rz_{k+1} / rz_k; p = z + beta p
+        if (rr <= thresh) stop = CG_CONVERGED;
+        else if (!(rzn > T(0)) || !isfinite(rzn)) stop = CG_BREAKDOWN;
+        else if (rr <= pause_thresh) stop = CG_PAUSED;
+        if (stop == CG_RUNNING) beta = rzn / rz;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const int32_t l = j * TT + t;
+            if (l < rows) {
+                const T pi = P[l];
+                xv[j] = xv[j] + a * pi;
+                if (stop == CG_RUNNING) P[l] = zv[j] + beta * pi;
+            }
+        }
+        if (stop != CG_RUNNING) {
+            ++k;   // this iteration counts
+            break;
+        }
+        rz = rzn;
+#pragma unroll
+        for (int h = 0; h < HALO_PER_THREAD; ++h)
+            if (hid[h] >= 0) {
+                const int32_t l = R + h * TT + t;
+                P[l] = Word<T>::value(zh[h]) + beta * P[l];
+            }
+        __syncthreads();
+    }
+    if (given_up) {
+        if (t == 0) atomicOr(bar, 1u);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const int32_t l = j * TT + t;
+        if (l < rows) {
+            x[base + l] = xv[j];
+            r[base + l] = rv[j];
+            p[base + l] = P[l];
+        }
+    }
+    if (b == 0 && t == 0) {
+        // rz_k of the last iteration that began, for a resumed direction: the
+        // stop left rz alone, a finished iteration moved it on
+        const int32_t at = stop == CG_RUNNING || (stop == CG_BREAKDOWN && !(pq > T(0) && isfinite(pq))) ? k : k - 1;
+        st->rz[at & 3] = rz;
+        st->pq = pq;
+        st->alpha = a;
+        st->beta = beta;
+        if (k > k0) st->rr = rr;
+        st->iter = k;
+        st->kk = -1;
+        st->done = stop;
+    }
+}
+
+// the rows per thread there are kernels for
+constexpr int NRS[] = {3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 18, 20, 22, 24, 28, 32};
+template <typename T>
+constexpr int nr_max() { return sizeof(T) == 8 ? 16 : 32; }   // x, r, z and M^-1 in half of the registers
+
+template <typename T, int... I>
+const void* pick_kernel(int nr, std::integer_sequence<int, I...>) {
+    const void* f = nullptr;
+    ((nr == NRS[I] && NRS[I] <= nr_max<T>() ? (void)(f = (const void*)cg_tile<T, std::min(NRS[I], nr_max<T>())>)
+                                            : (void)0), ...);
+    return f;
+}
+template <typename T>
+const void* tile_kernel(int nr) {
+    return pick_kernel<T>(nr, std::make_integer_sequence<int, (int)(sizeof(NRS) / sizeof(NRS[0]))>());
+}
+
+// Tiles of at most R rows over the plan's rows, at most `most` of them, none
+// across two ranks (by_rank: such a tile's halo is that of two) or simply one
+// after the other; empty if R is too small.
+std::vector<int32_t> cut(const rp_plan* p, int64_t R, int most, bool by_rank) {
+    std::vector<int32_t> first;
+    auto run = [&](int64_t r0, int64_t rows) {   // even pieces of whole slices
+        const int64_t t = (rows + R - 1) / R;
+        const int64_t len = t > 0 ? ((rows + t - 1) / t + 63) / 64 * 64 : 0;
+        for (int64_t a = 0; a < rows; a += len) first.push_back((int32_t)(r0 + a));
+    };
+    if (by_rank)
+        for (int32_t s = 0; s < p->alpha; ++s) run(p->row0[s], p->n_cells[s]);
+    else
+        run(0, p->n_rows);
+    if ((int)first.size() > most) return {};
+    first.push_back((int32_t)p->n_rows);
+    return first;
+}
+
+int tile_free(rp_plan* p) {
+    auto& tl = p->tiles;
+    for (void** q : {(void**)&tl.first, (void**)&tl.halo, (void**)&tl.n_halo, &tl.places}) {
+        if (*q) RP_HIP_TRY(hipFree(*q));
+        *q = nullptr;
+    }
+    return RP_OK;
+}
+
+// the structure for one cut; *fits = false if a tile's halo is too long
+int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t s, bool* fits) {
+    auto& tl = p->tiles;
+    const int32_t G = (int32_t)first.size() - 1, R = nr * TT;
+    RP_TRY(tile_free(p));
+    RP_HIP_TRY(hipMalloc(&tl.first, sizeof(int32_t) * first.size()));
+    RP_HIP_TRY(hipMalloc(&tl.halo, sizeof(int32_t) * (size_t)G * HALO_MAX));
+    RP_HIP_TRY(hipMalloc(&tl.n_halo, sizeof(int32_t) * (size_t)G));
+    RP_HIP_TRY(hipMalloc(&tl.places, sizeof(Places) * (size_t)G * R));
+    RP_HIP_TRY(hipMemcpyAsync(tl.first, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(tile_build, dim3(G), dim3(1024), 0, s, R, tl.first, p->d_row_ptr, p->d_col, tl.halo, tl.n_halo,
+                       (Places*)tl.places);
+    RP_HIP_TRY(hipGetLastError());
+    std::vector<int32_t> h(G);
+    RP_HIP_TRY(hipMemcpyAsync(h.data(), tl.n_halo, sizeof(int32_t) * (size_t)G, hipMemcpyDeviceToHost, s));
+    RP_HIP_TRY(hipStreamSynchronize(s));
+    const auto mm = std::minmax_element(h.begin(), h.end());
+    *fits = *mm.first >= 0;
+    if (*fits) {
+        tl.R = R;
+        tl.G = G;
+        tl.halo_most = *mm.second;
+    }
+    return RP_OK;
+}
+
+// the plan's tiles, or that it does not fit (tiles.R = 0), found out once
+int tile_setup(rp_plan* p, hipStream_t s) {
+    auto& tl = p->tiles;
+    if (tl.asked) return RP_OK;
+    int cus = 0, coop = 0;
+    RP_HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, p->device));
+    RP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    const int most = std::min(cus, SPMV_BLOCK);   // a thread per tile's sums
+    // by rank where that costs at most a quarter more rows per thread, else
+    // (or where a halo is too long) in one run
+    int nr[2] = {0, 0};
+    std::vector<int32_t> first[2];
+    if (coop && p->max_row <= U)
+        for (int k = 0; k < 2; ++k)
+            for (int v : NRS) {
+                first[k] = cut(p, (int64_t)v * TT, most, k == 0);
+                if (!first[k].empty()) {
+                    nr[k] = v;
+                    break;
+                }
+            }
+    bool fits = false;
+    if (nr[0] > 0 && 4 * nr[0] <= 5 * nr[1]) RP_TRY(tile_try(p, nr[0], first[0], s, &fits));
+    if (!fits && nr[1] > 0) RP_TRY(tile_try(p, nr[1], first[1], s, &fits));
+    if (!fits) RP_TRY(tile_free(p));
+    tl.asked = true;
+    return RP_OK;
+}
+
+template <typename T>
+struct TileVal;
+template <>
+struct TileVal<double> {
+    static double*& val(rp_plan* p) { return p->tiles.val64; }
+    static int64_t& version(rp_plan* p) { return p->tiles.version64; }
+};
+template <>
+struct TileVal<float> {
+    static float*& val(rp_plan* p) { return p->tiles.val32; }
+    static int64_t& version(rp_plan* p) { return p->tiles.version32; }
+};
+
+}  // namespace
+
+// whether the plan fits the tiled loop in this precision
+template <typename T>
+int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
+    *yes = false;
+    RP_TRY(tile_setup(p, s));
+    const auto& tl = p->tiles;
+    const int nr = tl.R / TT;
+    if (tl.R == 0 || nr > nr_max<T>() || tl.R + tl.halo_most > lds_words<T>()) return RP_OK;
+    int per_cu = 0;
+    RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tile_kernel<T>(nr), TT, 0));
+    *yes = per_cu > 0;
+    return RP_OK;
+}
+
+// The iterations k0 .. min(k_end, budget) by the tiled loop, enqueued, on a
+// plan that fits it.  The abort word goes to h_flags[2].
+template <typename T>
+int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0,
+                   int32_t k_end, hipStream_t s) {
+    auto& tl = p->tiles;
+    int32_t n = (int32_t)p->n_rows;
+    T*& val = TileVal<T>::val(p);
+    if (!val) RP_HIP_TRY(hipMalloc(&val, sizeof(T) * (size_t)tl.G * tl.R * U));
+    if (TileVal<T>::version(p) != p->values_version) {
+        hipLaunchKernelGGL(tile_values<T>, dim3(tl.R / 256, tl.G), dim3(256), 0, s, tl.R, tl.first, p->d_row_ptr, src,
+                           val);
+        RP_HIP_TRY(hipGetLastError());
+        TileVal<T>::version(p) = p->values_version;
+    }
+    typedef typename Word<T>::type W;
+    const int64_t len = (int64_t)RES_SETS * (3 * SPMV_BLOCK + (int64_t)n);
+    if (!tl.slots) RP_HIP_TRY(hipMalloc(&tl.slots, len * sizeof(uint64_t)));
+    if (!tl.bar) RP_HIP_TRY(hipMalloc(&tl.bar, sizeof(uint32_t)));
+    W* slots = (W*)tl.slots;
+    W* zs = slots + RES_SETS * 3 * SPMV_BLOCK;
+    uint32_t* bar = tl.bar;
+    hipLaunchKernelGGL(clear_words, dim3(1024), dim3(256), 0, s, (uint32_t*)slots, len * (int64_t)(sizeof(W) / 4), bar);
+    RP_HIP_TRY(hipGetLastError());
+    const int32_t *first = tl.first, *halo = tl.halo, *n_halo = tl.n_halo;
+    const Places* places = (const Places*)tl.places;
+    const T* v = val;
+    void* args[] = {&n, (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&v, (void*)&dinv, &x, &r, &pv, &st,
+                    &k0, &k_end, &slots, &zs, &bar};
+    RP_HIP_TRY(hipLaunchCooperativeKernel(tile_kernel<T>(tl.R / TT), dim3(tl.G), dim3(TT), args, 0, s));
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + 2, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    return RP_OK;
+}
+
+template int tile_fits<double>(rp_plan*, hipStream_t, bool*);
+template int tile_fits<float>(rp_plan*, hipStream_t, bool*);
+template int launch_cg_tile<double>(rp_plan*, const double*, const double*, double*, double*, double*,
+                                    CgState<double>*, int32_t, int32_t, hipStream_t);
+template int launch_cg_tile<float>(rp_plan*, const float*, const float*, float*, float*, float*, CgState<float>*,
+                                   int32_t, int32_t, hipStream_t);
+
+}  // namespace rp
