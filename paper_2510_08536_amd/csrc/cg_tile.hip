@@ -22,13 +22,19 @@
 // rows first, so they differ from the launched kernels' by rounding.
 //
 // A plan fits if no row has more than U entries, the tiles hold its rows (16 per
-// thread in FP64, 32 in FP32), and every tile's rows and halo fit LDS: a mesh
-// in a rank's natural order does; randomly numbered rows, whose halo is nearly
-// the whole rank, do not, and keep three launches.
+// thread in FP64, 32 in FP32), and every tile's rows and halo fit LDS.  A mesh
+// in a rank's natural order does as it is.  Where the numbering has no
+// locality (an unstructured mesh) and a tile's halo would be nearly the whole
+// rank, the tiles are cut from an order of their own (tile_order.hip): `order`
+// gives the row at each position, the loop's private copies follow it and a
+// launch's vectors are gathered before it and scattered after.
 //
 // Per iteration against three launches: FP64 26.3 -> 11.2 us at 80^3 rows, 36.8
 // -> 16.4 at 96^3, 57.2 -> 23.6 at 110 x 108 x 112, 68.5 -> 38.2 at 128^3; FP32
 // 20.6 -> 9.6, 28.1 -> 12.1, 44.5 -> 15.6, 46.7 -> 20.0, and 72.6 -> 50 at 160^3.
+// Cells numbered at random, by the order: FP64 62 -> 16.6 us at 100 x 90 x 95
+// (48 ranks), 130 -> 42 at 128^3; FP32 52 -> 13.1, 110 -> 22, and 235 -> 51 at
+// 150 x 160 x 160; finding the order takes the first solve 7 and 16 ms more.
 // About 7 us of it are the exchanges; the rest streams the values and, past
 // some 10 rows per thread, the places (128^3 FP64: 150 MB at 4.8 TB/s).
 // Non-temporal loads of the values made it slower (16.4 -> 18 us at 96^3: they
@@ -40,6 +46,9 @@
 #include "exchange.hpp"
 
 namespace rp {
+
+// tile_order.hip
+int tile_order(rp_plan* p, int64_t cap, int32_t* order, int32_t* inv, hipStream_t s, bool* ok, bool* memory);
 
 namespace {
 
@@ -61,10 +70,12 @@ struct __align__(16) Places {
 // One block per tile b, rows first[b] .. first[b + 1) (R at most): collect the
 // columns outside the tile, sort them in LDS, drop repeats -> halo and its
 // length (-1: does not fit); then the places, row l of tile b at b R + l.
+// Rows and columns are positions; order and inv (nullptr: the identity)
+// translate.
 __global__ void __launch_bounds__(1024)
-tile_build(int32_t R, const int32_t* __restrict__ first, const int32_t* __restrict__ row_ptr,
-           const int32_t* __restrict__ col, int32_t* __restrict__ halo, int32_t* __restrict__ n_halo,
-           Places* __restrict__ places) {
+tile_build(int32_t R, const int32_t* __restrict__ first, const int32_t* __restrict__ order,
+           const int32_t* __restrict__ inv, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+           int32_t* __restrict__ halo, int32_t* __restrict__ n_halo, Places* __restrict__ places) {
     __shared__ int32_t list[LIST_MAX];
     __shared__ int32_t uniq[HALO_MAX];
     __shared__ int32_t wtot[16];
@@ -74,14 +85,16 @@ tile_build(int32_t R, const int32_t* __restrict__ first, const int32_t* __restri
     Places* const pb = places + (int64_t)b * R;
     if (t == 0) count = 0;
     __syncthreads();
-    for (int32_t i = t; i < rows; i += 1024)
-        for (int32_t e = row_ptr[base + i]; e < row_ptr[base + i + 1]; ++e) {
-            const int32_t c = col[e] - base;
+    for (int32_t i = t; i < rows; i += 1024) {
+        const int32_t row = order ? order[base + i] : base + i;
+        for (int32_t e = row_ptr[row]; e < row_ptr[row + 1]; ++e) {
+            const int32_t c = (inv ? inv[col[e]] : col[e]) - base;
             if (c < 0 || c >= rows) {
                 const int32_t at = atomicAdd(&count, 1);
                 if (at < LIST_MAX) list[at] = c + base;
             }
         }
+    }
     __syncthreads();
     const int32_t m = count;
     if (m > LIST_MAX) {
@@ -128,12 +141,13 @@ tile_build(int32_t R, const int32_t* __restrict__ first, const int32_t* __restri
     for (int32_t i = t; i < H; i += 1024) halo[(int64_t)b * HALO_MAX + i] = uniq[i];
     if (t == 0) n_halo[b] = H;
     for (int32_t i = t; i < rows; i += 1024) {
-        const int32_t e0 = row_ptr[base + i], len = row_ptr[base + i + 1] - e0;
+        const int32_t row = order ? order[base + i] : base + i;
+        const int32_t e0 = row_ptr[row], len = row_ptr[row + 1] - e0;
         Places pl;
         for (int u = 0; u < 8; ++u) {
             uint32_t w = (uint32_t)i;   // a missing entry: its own row's place, times 0
             if (u < len) {
-                const int32_t g = col[e0 + u], cl = g - base;
+                const int32_t g = inv ? inv[col[e0 + u]] : col[e0 + u], cl = g - base;
                 if (cl >= 0 && cl < rows) {
                     w = (uint32_t)cl;
                 } else {
@@ -162,11 +176,16 @@ tile_build(int32_t R, const int32_t* __restrict__ first, const int32_t* __restri
 // ((b R + l) / 64 U + u) 64 + l % 64; zeros past the tile's rows
 template <typename T>
 __global__ void __launch_bounds__(256)
-tile_values(int32_t R, const int32_t* __restrict__ first, const int32_t* __restrict__ row_ptr,
-            const T* __restrict__ val, T* __restrict__ out) {
+tile_values(int32_t R, const int32_t* __restrict__ first, const int32_t* __restrict__ order,
+            const int32_t* __restrict__ row_ptr, const T* __restrict__ val, T* __restrict__ out) {
     const int32_t base = first[blockIdx.y], rows = first[blockIdx.y + 1] - base;
     const int32_t l = blockIdx.x * 256 + threadIdx.x;   // R is a multiple of 256
-    const int32_t e0 = l < rows ? row_ptr[base + l] : 0, len = l < rows ? row_ptr[base + l + 1] - e0 : 0;
+    int32_t e0 = 0, len = 0;
+    if (l < rows) {
+        const int32_t row = order ? order[base + l] : base + l;
+        e0 = row_ptr[row];
+        len = row_ptr[row + 1] - e0;
+    }
     T v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = u < len ? val[e0 + u] : T(0);
@@ -178,6 +197,36 @@ tile_values(int32_t R, const int32_t* __restrict__ first, const int32_t* __restr
 __global__ void clear_words(uint32_t* w, int64_t words, uint32_t* bar) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) w[i] = ~0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) bar[0] = 0u;
+}
+
+// the vectors of a launch from rows to positions, out[0 .. 4 n): x, r, p, M^-1;
+// and x, r, p back.  (Translated inside cg_tile the index takes registers of
+// every iteration: 128^3 FP64 38.7 -> 50.5 us.)
+template <typename T>
+__global__ void __launch_bounds__(256)
+to_positions(int32_t n, const int32_t* __restrict__ order, const T* __restrict__ x, const T* __restrict__ r,
+             const T* __restrict__ p, const T* __restrict__ dinv, T* __restrict__ out) {
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int32_t row = order[i];
+    const int64_t m = n;
+    out[i] = x[row];
+    out[m + i] = r[row];
+    out[2 * m + i] = p[row];
+    out[3 * m + i] = dinv[row];
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+from_positions(int32_t n, const int32_t* __restrict__ inv, const T* __restrict__ in, T* __restrict__ x,
+               T* __restrict__ r, T* __restrict__ p) {
+    const int32_t row = blockIdx.x * 256 + threadIdx.x;
+    if (row >= n) return;
+    const int32_t i = inv[row];
+    const int64_t m = n;
+    x[row] = in[i];
+    r[row] = in[m + i];
+    p[row] = in[2 * m + i];
 }
 
 // ---- iterations ----------------------------------------------------------------
@@ -454,9 +503,9 @@ const void* tile_kernel(int nr) {
     return pick_kernel<T>(nr, std::make_integer_sequence<int, (int)(sizeof(NRS) / sizeof(NRS[0]))>());
 }
 
-// Tiles of at most R rows over the plan's rows, at most `most` of them, none
-// across two ranks (by_rank: such a tile's halo is that of two) or simply one
-// after the other; empty if R is too small.
+// Tiles of at most R rows over the plan's rows (or positions), at most `most`
+// of them, none across two ranks (by_rank: such a tile's halo is that of two)
+// or simply one after the other; empty if R is too small.
 std::vector<int32_t> cut(const rp_plan* p, int64_t R, int most, bool by_rank) {
     std::vector<int32_t> first;
     auto run = [&](int64_t r0, int64_t rows) {   // even pieces of whole slices
@@ -473,6 +522,16 @@ std::vector<int32_t> cut(const rp_plan* p, int64_t R, int most, bool by_rank) {
     return first;
 }
 
+// Memory the loop keeps with the plan, if there is some: without it a solve
+// takes three launches, as a plan that does not fit does.
+template <typename V>
+bool got(V** q, size_t bytes) {
+    if (*q || hipMalloc((void**)q, std::max<size_t>(bytes, 1)) == hipSuccess) return true;
+    *q = nullptr;
+    (void)hipGetLastError();
+    return false;
+}
+
 int tile_free(rp_plan* p) {
     auto& tl = p->tiles;
     for (void** q : {(void**)&tl.first, (void**)&tl.halo, (void**)&tl.n_halo, &tl.places}) {
@@ -482,18 +541,31 @@ int tile_free(rp_plan* p) {
     return RP_OK;
 }
 
-// the structure for one cut; *fits = false if a tile's halo is too long
-int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t s, bool* fits) {
+int order_free(rp_plan* p) {
+    auto& tl = p->tiles;
+    for (void** q : {(void**)&tl.order, (void**)&tl.inv, &tl.vec}) {
+        if (*q) RP_HIP_TRY(hipFree(*q));
+        *q = nullptr;
+    }
+    return RP_OK;
+}
+
+// the structure for one cut; *fits = false if a tile's halo is too long, or
+// there is no memory for it (*memory = false)
+int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t s, bool* fits,
+             bool* memory) {
     auto& tl = p->tiles;
     const int32_t G = (int32_t)first.size() - 1, R = nr * TT;
     RP_TRY(tile_free(p));
-    RP_HIP_TRY(hipMalloc(&tl.first, sizeof(int32_t) * first.size()));
-    RP_HIP_TRY(hipMalloc(&tl.halo, sizeof(int32_t) * (size_t)G * HALO_MAX));
-    RP_HIP_TRY(hipMalloc(&tl.n_halo, sizeof(int32_t) * (size_t)G));
-    RP_HIP_TRY(hipMalloc(&tl.places, sizeof(Places) * (size_t)G * R));
+    *fits = false;
+    if (!got(&tl.first, sizeof(int32_t) * first.size()) || !got(&tl.halo, sizeof(int32_t) * (size_t)G * HALO_MAX) ||
+        !got(&tl.n_halo, sizeof(int32_t) * (size_t)G) || !got(&tl.places, sizeof(Places) * (size_t)G * R)) {
+        *memory = false;
+        return RP_OK;
+    }
     RP_HIP_TRY(hipMemcpyAsync(tl.first, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(tile_build, dim3(G), dim3(1024), 0, s, R, tl.first, p->d_row_ptr, p->d_col, tl.halo, tl.n_halo,
-                       (Places*)tl.places);
+    hipLaunchKernelGGL(tile_build, dim3(G), dim3(1024), 0, s, R, tl.first, tl.order, tl.inv, p->d_row_ptr, p->d_col,
+                       tl.halo, tl.n_halo, (Places*)tl.places);
     RP_HIP_TRY(hipGetLastError());
     std::vector<int32_t> h(G);
     RP_HIP_TRY(hipMemcpyAsync(h.data(), tl.n_halo, sizeof(int32_t) * (size_t)G, hipMemcpyDeviceToHost, s));
@@ -529,11 +601,22 @@ int tile_setup(rp_plan* p, hipStream_t s) {
                     break;
                 }
             }
-    bool fits = false;
-    if (nr[0] > 0 && 4 * nr[0] <= 5 * nr[1]) RP_TRY(tile_try(p, nr[0], first[0], s, &fits));
-    if (!fits && nr[1] > 0) RP_TRY(tile_try(p, nr[1], first[1], s, &fits));
+    bool fits = false, memory = true;
+    if (nr[0] > 0 && 4 * nr[0] <= 5 * nr[1]) RP_TRY(tile_try(p, nr[0], first[0], s, &fits, &memory));
+    if (!fits && nr[1] > 0) {
+        RP_TRY(tile_try(p, nr[1], first[1], s, &fits, &memory));
+        if (!fits && memory) {
+            bool ok = false;
+            memory = got(&tl.order, sizeof(int32_t) * (size_t)p->n_rows) &&
+                     got(&tl.inv, sizeof(int32_t) * (size_t)p->n_rows) &&
+                     got(&tl.vec, 4 * sizeof(double) * (size_t)p->n_rows);
+            if (memory) RP_TRY(tile_order(p, first[1][1], tl.order, tl.inv, s, &ok, &memory));
+            if (ok) RP_TRY(tile_try(p, nr[1], first[1], s, &fits, &memory));
+            if (!fits) RP_TRY(order_free(p));
+        }
+    }
     if (!fits) RP_TRY(tile_free(p));
-    tl.asked = true;
+    tl.asked = memory;   // without memory now, a later solve may find some
     return RP_OK;
 }
 
@@ -556,13 +639,16 @@ struct TileVal<float> {
 template <typename T>
 int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
     *yes = false;
+    if (p->n_rows > (int64_t)SPMV_BLOCK * nr_max<T>() * TT) return RP_OK;
     RP_TRY(tile_setup(p, s));
     const auto& tl = p->tiles;
     const int nr = tl.R / TT;
     if (tl.R == 0 || nr > nr_max<T>() || tl.R + tl.halo_most > lds_words<T>()) return RP_OK;
     int per_cu = 0;
     RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tile_kernel<T>(nr), TT, 0));
-    *yes = per_cu > 0;
+    *yes = per_cu > 0 && got(&TileVal<T>::val(p), sizeof(T) * (size_t)tl.G * tl.R * U) &&
+           got(&tl.slots, sizeof(uint64_t) * RES_SETS * (3 * SPMV_BLOCK + (size_t)p->n_rows)) &&
+           got(&tl.bar, sizeof(uint32_t));
     return RP_OK;
 }
 
@@ -573,18 +659,15 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
                    int32_t k_end, hipStream_t s) {
     auto& tl = p->tiles;
     int32_t n = (int32_t)p->n_rows;
-    T*& val = TileVal<T>::val(p);
-    if (!val) RP_HIP_TRY(hipMalloc(&val, sizeof(T) * (size_t)tl.G * tl.R * U));
+    T* val = TileVal<T>::val(p);
     if (TileVal<T>::version(p) != p->values_version) {
-        hipLaunchKernelGGL(tile_values<T>, dim3(tl.R / 256, tl.G), dim3(256), 0, s, tl.R, tl.first, p->d_row_ptr, src,
-                           val);
+        hipLaunchKernelGGL(tile_values<T>, dim3(tl.R / 256, tl.G), dim3(256), 0, s, tl.R, tl.first, tl.order,
+                           p->d_row_ptr, src, val);
         RP_HIP_TRY(hipGetLastError());
         TileVal<T>::version(p) = p->values_version;
     }
     typedef typename Word<T>::type W;
     const int64_t len = (int64_t)RES_SETS * (3 * SPMV_BLOCK + (int64_t)n);
-    if (!tl.slots) RP_HIP_TRY(hipMalloc(&tl.slots, len * sizeof(uint64_t)));
-    if (!tl.bar) RP_HIP_TRY(hipMalloc(&tl.bar, sizeof(uint32_t)));
     W* slots = (W*)tl.slots;
     W* zs = slots + RES_SETS * 3 * SPMV_BLOCK;
     uint32_t* bar = tl.bar;
@@ -593,9 +676,23 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
     const int32_t *first = tl.first, *halo = tl.halo, *n_halo = tl.n_halo;
     const Places* places = (const Places*)tl.places;
     const T* v = val;
-    void* args[] = {&n, (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&v, (void*)&dinv, &x, &r, &pv, &st,
-                    &k0, &k_end, &slots, &zs, &bar};
+    T *tx = x, *tr = r, *tp = pv;
+    const T* td = dinv;
+    if (tl.order) {   // the vectors at the tiles' positions
+        tx = (T*)tl.vec;
+        tr = tx + n;
+        tp = tr + n;
+        td = tp + n;
+        hipLaunchKernelGGL(to_positions<T>, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.order, x, r, pv, dinv, tx);
+        RP_HIP_TRY(hipGetLastError());
+    }
+    void* args[] = {&n, (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&v, (void*)&td, &tx, &tr,
+                    &tp, &st, &k0, &k_end, &slots, &zs, &bar};
     RP_HIP_TRY(hipLaunchCooperativeKernel(tile_kernel<T>(tl.R / TT), dim3(tl.G), dim3(TT), args, 0, s));
+    if (tl.order) {
+        hipLaunchKernelGGL(from_positions<T>, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.inv, tx, x, r, pv);
+        RP_HIP_TRY(hipGetLastError());
+    }
     RP_HIP_TRY(hipMemcpyAsync(p->h_flags + 2, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return RP_OK;
 }

@@ -310,6 +310,8 @@ struct rp_plan {
         int32_t R = 0, G = 0;          // rows per tile at most, tiles
         int32_t* first = nullptr;      // [G + 1] first row of each tile
         int32_t halo_most = 0;         // longest halo
+        int32_t *order = nullptr, *inv = nullptr;   // [n] row at each position and back; nullptr: fused order
+        void* vec = nullptr;           // x, r, p, M^-1 at the positions of an order
         int32_t* halo = nullptr;       // [G * HALO_MAX] columns of a tile's rows outside it, ascending
         int32_t* n_halo = nullptr;     // [G]
         void* places = nullptr;        // [G R] 8 x uint16: place in LDS of each entry's column

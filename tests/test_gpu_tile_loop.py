@@ -4,9 +4,11 @@ a tile's rows first, so iterates after a fixed budget agree to rounding (1e-11
 relative in FP64, far above what a reordered sum of this length changes) and
 solves meet the same residual.  Sizes: just past the small systems' limit,
 tiles that end inside a rank, with a partial last one, ranks of unequal size,
-more ranks than tiles, a mesh whose far couplings all leave the tile.  A
-randomly numbered mesh, whose halos do not fit, keeps three launches, bit for
-bit."""
+more ranks than tiles, a mesh whose far couplings all leave the tile; randomly
+numbered meshes, whose tiles are cut from an order of the loop's own: ranks
+numbered apart, a chain (regions of one dimension) and cells without a
+coupling, which no region reaches.  Rows of more entries than a tile's slices
+hold keep three launches, bit for bit."""
 import numpy as np
 import pytest
 
@@ -24,6 +26,9 @@ CASES = {
     "unequal_ranks": lambda: synth.small((70, 65, 90), ("rcb", 7), kappa=(1e-2, 1.0), seed=3),
     "many_ranks": lambda: synth.small((72, 70, 68), ("blocks", 7, 7, 7), kappa=(1e-1, 1.0), seed=4),
     "large_tiles": lambda: synth.small((104, 100, 96), ("blocks", 2, 3, 2), kappa=(1e-2, 1.0), seed=5),
+    "random": lambda: synth.small((68, 66, 64), ("blocks", 1, 1, 1), kappa=(1e-1, 1.0), seed=8, scramble=True),
+    "random_ranks": lambda: synth.small((90, 85, 88), ("rcb", 5), kappa=(1e-2, 1.0), seed=9, scramble=True),
+    "random_thin": lambda: synth.small((26243, 5, 2), ("blocks", 3, 1, 1), kappa=(1e-1, 1.0), seed=10, scramble=True),
 }
 
 
@@ -66,8 +71,31 @@ def test_values_follow_updates():
     plan.close()
 
 
-def test_random_numbering_keeps_three_launches():
-    w = synth.small((68, 66, 64), ("blocks", 1, 1, 1), kappa=(1e-1, 1.0), seed=8, scramble=True)
+def test_random_chain_with_uncoupled_cells():
+    """A chain of 200 000 randomly numbered cells and 70 000 cells without a
+    face: the seeds grow along the chain only, the cells alone fill regions by
+    index."""
+    n, c = 270000, 200000
+    g = np.random.default_rng(11)
+    chain = g.permutation(n)[:c].astype(np.int32)
+    own, nbr = np.minimum(chain[:-1], chain[1:]), np.maximum(chain[:-1], chain[1:])
+    o = np.lexsort((nbr, own))
+    ranks = [dict(owner=own[o], neighbour=nbr[o], iface_cell=np.zeros(0, np.int32),
+                  iface_nbr_rank=np.zeros(0, np.int32), iface_nbr_cell=np.zeros(0, np.int32))]
+    from paper_2510_08536_amd import Plan
+    plan = Plan([n], 0, 1, ranks)
+    plan.update([np.full(n, 2.5)], [np.full(c - 1, -1.0)], [np.zeros(0)])
+    b = dev_tensor(g.uniform(-1, 1, n))
+    for precision, bar in (("fp64", 1e-11), ("mixed", 1e-9)):
+        xa, ia = plan.solve(b, tol=1e-10, precision=precision)
+        xt, it = plan.solve(b, tol=1e-10, precision=precision, fused_loop=RP_LOOP_THREE)
+        assert ia["status"] == it["status"] == 0 and ia["iters"] == it["iters"]
+        assert float((xa - xt).norm()) <= bar * float(xt.norm()), precision
+    plan.close()
+
+
+def test_long_rows_keep_three_launches():
+    w = synth.small((68, 66, 64), ("blocks", 2, 1, 1), kappa=(1e-1, 1.0), seed=12, stencil=27)
     plan = make_plan(w)
     update(plan, share_values(w))
     b = dev_tensor(w.rhs())
