@@ -641,7 +641,7 @@ int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
     *yes = false;
     if (p->n_rows > (int64_t)SPMV_BLOCK * nr_max<T>() * TT) return RP_OK;
     RP_TRY(tile_setup(p, s));
-    const auto& tl = p->tiles;
+    auto& tl = p->tiles;
     const int nr = tl.R / TT;
     if (tl.R == 0 || nr > nr_max<T>() || tl.R + tl.halo_most > lds_words<T>()) return RP_OK;
     int per_cu = 0;
