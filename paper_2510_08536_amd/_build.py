@@ -17,13 +17,15 @@ LIB = os.path.join(HERE, "librp.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["plan.hip", "update.hip", "spmv.hip", "cg.hip", "grad.hip", "order.hip", "precond.hip", "amg.hip", "cg_loop.hip", "cg_tile.hip", "tile_order.hip", "noalloc.hip", "capi.cpp", "ipc.cpp"]
+SOURCES = ["plan.hip", "update.hip", "spmv.hip", "cg.hip", "grad.hip", "order.hip", "precond.hip", "amg.hip",
+           "cg_loop.hip", "cg_tile.hip", "tile_order.hip", "bi_tile.hip", "noalloc.hip", "capi.cpp", "ipc.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-I", INCLUDE]
-# cg_tile.hip keeps a thread's rows in arrays that are only ever indexed by
+# these keep a thread's rows in arrays that are only ever indexed by
 # constants; the pass would make each one register tuple, copied whole
-SOURCE_FLAGS = {"cg_tile.hip": ["-mllvm", "-disable-promote-alloca-to-vector"]}
+SOURCE_FLAGS = {"cg_tile.hip": ["-mllvm", "-disable-promote-alloca-to-vector"],
+                "bi_tile.hip": ["-mllvm", "-disable-promote-alloca-to-vector"]}
 
 
 def _compile(src: str, out_dir: str = BUILD, extra=()) -> str:

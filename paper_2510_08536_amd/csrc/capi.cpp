@@ -91,7 +91,8 @@ void free_plan(rp_plan* p) {
                    p->d_ro_val64, p->d_ro_val32, p->d_ro_dinv64, p->d_ro_dinv32, p->d_ro_b, p->d_ro_x,
                    p->d_ro_valT, (void*)p->d_src, p->d_bj_start, p->d_bj_minv64, p->d_bj_minv32, p->d_z,
                    p->d_z32, p->d_bj_flag, p->d_loop_bar, p->d_slots, p->tiles.first, p->tiles.order, p->tiles.inv,
-                   p->tiles.vec, p->tiles.halo, p->tiles.n_halo, p->tiles.places, p->tiles.val64, p->tiles.val32, p->tiles.slots, p->tiles.bar};
+                   p->tiles.vec, p->tiles.halo, p->tiles.n_halo, p->tiles.places, p->tiles.val64, p->tiles.val32,
+                   p->tiles.slots, p->tiles.bi_slots, p->tiles.bar};
     amg_free(p);
     for (void* q : dev)
         if (q) (void)hipFree(q);

@@ -62,6 +62,10 @@ int tile_fits(rp_plan* p, hipStream_t s, bool* yes);
 template <typename T>
 int launch_cg_tile(rp_plan* p, const T* val, const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0,
                    int32_t k_end, hipStream_t s);
+// bi_tile.hip: BiCGStab's iterations k0 .. k_end the same way
+int bi_tile_fits(rp_plan* p, hipStream_t s, bool* yes);
+int launch_bi_tile(rp_plan* p, const double* src, bool transposed, const double* dinv, double* x, double* r,
+                   const double* rh, double* pv, double* v, BiState* st, int32_t k0, int32_t k_end, hipStream_t s);
 
 namespace {
 
@@ -1412,6 +1416,7 @@ bi_finalize(int32_t start, int32_t k, double tol2, int32_t g_spmv, const double*
     const double thresh = tol2 * bb;
     st->thresh = thresh;
     st->rr = rr;
+    st->rho[k & 3] = rr;   // (rh, r), for the one-launch loop
     st->iter = k;
     int32_t d = CG_RUNNING;
     if (bb == 0.0) d = CG_ZERO_RHS;
@@ -1642,8 +1647,22 @@ int bi_true_residual(Bi& q) {
     return bi_read(q);
 }
 
-int bi_iterate(Bi& q, int chunk, int32_t max_iter) {
+int bi_iterate(Bi& q, int chunk, int32_t max_iter, bool tile, bool transposed) {
     Cg<double>& c = q.c;
+    if (tile) {
+        constexpr int64_t LOOP_ITERS = 1 << 15;   // a launch's length is bounded: other work waits for it
+        while (q.h->done == CG_RUNNING && q.h->iter < max_iter) {
+            const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)q.h->iter + LOOP_ITERS, max_iter);
+            RP_TRY(launch_bi_tile(c.plan, c.val, transposed, c.dinv, c.x, c.r, q.rh, q.p, q.v, q.st, q.h->iter, k1,
+                                  c.s));
+            RP_TRY(bi_read(q));
+            if (c.plan->h_flags[2]) {
+                set_error("the one-launch BiCGStab loop gave up waiting for another workgroup's values");
+                return RP_ERR_HIP;
+            }
+        }
+        return RP_OK;
+    }
     const dim3 gs(c.g_spmv), bs(SPMV_BLOCK), gv(c.g_vec), bv(VEC_BLOCK);
     while (q.h->done == CG_RUNNING && q.h->iter < max_iter) {
         const int32_t k0 = q.h->iter;
@@ -1688,6 +1707,9 @@ int solve_bicgstab(rp_plan* p, const double* b, double* x, const rp_solve_opts& 
          p->d_bi_work + 4 * n, p->d_bi_st, p->h_bi_st};
     const double tol2 = o.tol * o.tol;
     const int chunk = std::max(1, o.check_every);
+    bool tile = false;
+    if (o.fused_loop == RP_LOOP_AUTO && !ordered && !p->timing.enabled && p->vec_grid_override == 0)
+        RP_TRY(bi_tile_fits(p, s, &tile));
     RP_TRY(bi_launch_start(q, o.x0_zero != 0, 0, tol2));
     bool fresh = true;  // rr_true belongs to the current x
     int status = RP_NOT_CONVERGED;
@@ -1720,7 +1742,7 @@ int solve_bicgstab(rp_plan* p, const double* b, double* x, const rp_solve_opts& 
             break;
         }
         if (q.h->iter >= o.max_iter) break;
-        RP_TRY(bi_iterate(q, chunk, o.max_iter));
+        RP_TRY(bi_iterate(q, chunk, o.max_iter, tile, o.transpose != 0));
         fresh = false;
     }
     if (!fresh && q.h->done != CG_ZERO_RHS) RP_TRY(bi_true_residual(q));

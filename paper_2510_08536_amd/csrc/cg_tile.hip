@@ -43,7 +43,7 @@
 #include <utility>
 #include <vector>
 
-#include "exchange.hpp"
+#include "tile.hpp"
 
 namespace rp {
 
@@ -52,19 +52,7 @@ int tile_order(rp_plan* p, int64_t cap, int32_t* order, int32_t* inv, hipStream_
 
 namespace {
 
-constexpr int TT = 512;                 // threads per block: 8 wavefronts, 256 registers each
-constexpr int U = 7;                    // entries per row at most: a cell and its six faces
-constexpr int HALO_PER_THREAD = 16;
-constexpr int HALO_MAX = HALO_PER_THREAD * TT;
-constexpr int LIST_MAX = 16384;         // halo entries with repeats, while building
-
-// words of p (tile and halo) in LDS
-template <typename T>
-constexpr int lds_words() { return sizeof(T) == 8 ? 18432 : 36864; }   // 144 KB
-
-struct __align__(16) Places {
-    uint32_t w[4];   // entry 2 i in the low half of w[i], the next one in the high half
-};
+constexpr int LIST_MAX = 16384;   // halo entries with repeats, while building
 
 // ---- structure ---------------------------------------------------------------
 // One block per tile b, rows first[b] .. first[b + 1) (R at most): collect the
@@ -230,31 +218,6 @@ from_positions(int32_t n, const int32_t* __restrict__ inv, const T* __restrict__
 }
 
 // ---- iterations ----------------------------------------------------------------
-__device__ __forceinline__ uint32_t place(const Places& pl, int u) {
-    return u % 2 == 0 ? pl.w[u / 2] & 0xFFFFu : pl.w[u / 2] >> 16;
-}
-
-// A pointer that is the same in every lane, hidden from the compiler: what is
-// loaded from it in a loop stays in the loop, and it is an address in scalar
-// registers to which every lane adds the same offset of its own.  (Left to
-// itself the compiler keeps an address per row and entry, or the values
-// themselves, for all iterations, and spills them.)
-template <typename P>
-__device__ __forceinline__ __attribute__((address_space(1))) P* hidden(P* p) {
-    __attribute__((address_space(1))) P* q = (__attribute__((address_space(1))) P*)p;
-    asm volatile("" : "+s"(q));
-    return q;
-}
-
-// sum over the block's TT threads, in every thread; red: TT / 64 words
-template <typename T>
-__device__ __forceinline__ T tile_sum(const T* red) {
-#pragma clang fp contract(off)
-    T s = T(0);
-    for (int w = 0; w < TT / 64; ++w) s += red[w];
-    return s;
-}
-
 // NR rows per thread: tiles of at most R = NR TT rows
 template <typename T, int NR>
 __global__ void __launch_bounds__(TT)
@@ -486,16 +449,18 @@ cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
     }
 }
 
-// the rows per thread there are kernels for
-constexpr int NRS[] = {3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 18, 20, 22, 24, 28, 32};
+// the rows per thread of a tile (CG has kernels from 3 on: smaller systems take
+// the resident loop)
+constexpr int NRS[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 18, 20, 22, 24, 28, 32};
 template <typename T>
 constexpr int nr_max() { return sizeof(T) == 8 ? 16 : 32; }   // x, r, z and M^-1 in half of the registers
 
 template <typename T, int... I>
 const void* pick_kernel(int nr, std::integer_sequence<int, I...>) {
     const void* f = nullptr;
-    ((nr == NRS[I] && NRS[I] <= nr_max<T>() ? (void)(f = (const void*)cg_tile<T, std::min(NRS[I], nr_max<T>())>)
-                                            : (void)0), ...);
+    ((nr == NRS[I] && NRS[I] >= 3 && NRS[I] <= nr_max<T>()
+          ? (void)(f = (const void*)cg_tile<T, std::max(3, std::min(NRS[I], nr_max<T>()))>)
+          : (void)0), ...);
     return f;
 }
 template <typename T>
@@ -520,16 +485,6 @@ std::vector<int32_t> cut(const rp_plan* p, int64_t R, int most, bool by_rank) {
     if ((int)first.size() > most) return {};
     first.push_back((int32_t)p->n_rows);
     return first;
-}
-
-// Memory the loop keeps with the plan, if there is some: without it a solve
-// takes three launches, as a plan that does not fit does.
-template <typename V>
-bool got(V** q, size_t bytes) {
-    if (*q || hipMalloc((void**)q, std::max<size_t>(bytes, 1)) == hipSuccess) return true;
-    *q = nullptr;
-    (void)hipGetLastError();
-    return false;
 }
 
 int tile_free(rp_plan* p) {
@@ -580,6 +535,8 @@ int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t 
     return RP_OK;
 }
 
+}  // namespace
+
 // the plan's tiles, or that it does not fit (tiles.R = 0), found out once
 int tile_setup(rp_plan* p, hipStream_t s) {
     auto& tl = p->tiles;
@@ -609,7 +566,7 @@ int tile_setup(rp_plan* p, hipStream_t s) {
             bool ok = false;
             memory = got(&tl.order, sizeof(int32_t) * (size_t)p->n_rows) &&
                      got(&tl.inv, sizeof(int32_t) * (size_t)p->n_rows) &&
-                     got(&tl.vec, 4 * sizeof(double) * (size_t)p->n_rows);
+                     got(&tl.vec, TILE_VECS * sizeof(double) * (size_t)p->n_rows);
             if (memory) RP_TRY(tile_order(p, first[1][1], tl.order, tl.inv, s, &ok, &memory));
             if (ok) RP_TRY(tile_try(p, nr[1], first[1], s, &fits, &memory));
             if (!fits) RP_TRY(order_free(p));
@@ -619,6 +576,8 @@ int tile_setup(rp_plan* p, hipStream_t s) {
     tl.asked = memory;   // without memory now, a later solve may find some
     return RP_OK;
 }
+
+namespace {
 
 template <typename T>
 struct TileVal;
@@ -635,6 +594,28 @@ struct TileVal<float> {
 
 }  // namespace
 
+template <typename T>
+bool tile_room(rp_plan* p) {
+    return got(&TileVal<T>::val(p), sizeof(T) * (size_t)p->tiles.G * p->tiles.R * U);
+}
+
+// the slices of the values src: the matrix's, or (transposed) its transpose's
+template <typename T>
+int tile_slices(rp_plan* p, const T* src, bool transposed, hipStream_t s, const T** val) {
+    auto& tl = p->tiles;
+    *val = TileVal<T>::val(p);
+    const int64_t version = 2 * p->values_version + transposed;
+    if (TileVal<T>::version(p) == version) return RP_OK;
+    hipLaunchKernelGGL(tile_values<T>, dim3(tl.R / 256, tl.G), dim3(256), 0, s, tl.R, tl.first, tl.order, p->d_row_ptr,
+                       src, TileVal<T>::val(p));
+    RP_HIP_TRY(hipGetLastError());
+    TileVal<T>::version(p) = version;
+    return RP_OK;
+}
+
+template bool tile_room<double>(rp_plan*);
+template int tile_slices<double>(rp_plan*, const double*, bool, hipStream_t, const double**);
+
 // whether the plan fits the tiled loop in this precision
 template <typename T>
 int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
@@ -646,7 +627,7 @@ int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
     if (tl.R == 0 || nr > nr_max<T>() || tl.R + tl.halo_most > lds_words<T>()) return RP_OK;
     int per_cu = 0;
     RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tile_kernel<T>(nr), TT, 0));
-    *yes = per_cu > 0 && got(&TileVal<T>::val(p), sizeof(T) * (size_t)tl.G * tl.R * U) &&
+    *yes = per_cu > 0 && tile_room<T>(p) &&
            got(&tl.slots, sizeof(uint64_t) * RES_SETS * (3 * SPMV_BLOCK + (size_t)p->n_rows)) &&
            got(&tl.bar, sizeof(uint32_t));
     return RP_OK;
@@ -659,13 +640,8 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
                    int32_t k_end, hipStream_t s) {
     auto& tl = p->tiles;
     int32_t n = (int32_t)p->n_rows;
-    T* val = TileVal<T>::val(p);
-    if (TileVal<T>::version(p) != p->values_version) {
-        hipLaunchKernelGGL(tile_values<T>, dim3(tl.R / 256, tl.G), dim3(256), 0, s, tl.R, tl.first, tl.order,
-                           p->d_row_ptr, src, val);
-        RP_HIP_TRY(hipGetLastError());
-        TileVal<T>::version(p) = p->values_version;
-    }
+    const T* val = nullptr;
+    RP_TRY(tile_slices<T>(p, src, false, s, &val));
     typedef typename Word<T>::type W;
     const int64_t len = (int64_t)RES_SETS * (3 * SPMV_BLOCK + (int64_t)n);
     W* slots = (W*)tl.slots;
@@ -675,7 +651,6 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
     RP_HIP_TRY(hipGetLastError());
     const int32_t *first = tl.first, *halo = tl.halo, *n_halo = tl.n_halo;
     const Places* places = (const Places*)tl.places;
-    const T* v = val;
     T *tx = x, *tr = r, *tp = pv;
     const T* td = dinv;
     if (tl.order) {   // the vectors at the tiles' positions
@@ -686,7 +661,7 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
         hipLaunchKernelGGL(to_positions<T>, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.order, x, r, pv, dinv, tx);
         RP_HIP_TRY(hipGetLastError());
     }
-    void* args[] = {&n, (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&v, (void*)&td, &tx, &tr,
+    void* args[] = {&n, (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&val, (void*)&td, &tx, &tr,
                     &tp, &st, &k0, &k_end, &slots, &zs, &bar};
     RP_HIP_TRY(hipLaunchCooperativeKernel(tile_kernel<T>(tl.R / TT), dim3(tl.G), dim3(TT), args, 0, s));
     if (tl.order) {

@@ -303,22 +303,23 @@ struct rp_plan {
     float* d_z32 = nullptr;            // [n_rows] of the FP32 iteration
     uint32_t* d_bj_flag = nullptr;     // set when a block is not positive definite
 
-    // tiles of the CG loop on medium systems (cg_tile.hip), built by the first
-    // such solve; R = 0: the plan does not fit
+    // tiles of the one-launch CG and BiCGStab loops (cg_tile.hip, bi_tile.hip),
+    // built by the first such solve; R = 0: the plan does not fit
     struct Tiles {
         bool asked = false;
         int32_t R = 0, G = 0;          // rows per tile at most, tiles
         int32_t* first = nullptr;      // [G + 1] first row of each tile
         int32_t halo_most = 0;         // longest halo
         int32_t *order = nullptr, *inv = nullptr;   // [n] row at each position and back; nullptr: fused order
-        void* vec = nullptr;           // x, r, p, M^-1 at the positions of an order
+        void* vec = nullptr;           // a solve's vectors at the positions of an order
         int32_t* halo = nullptr;       // [G * HALO_MAX] columns of a tile's rows outside it, ascending
         int32_t* n_halo = nullptr;     // [G]
         void* places = nullptr;        // [G R] 8 x uint16: place in LDS of each entry's column
         double* val64 = nullptr;       // values in slices of 64 rows, entry by entry
         float* val32 = nullptr;
-        int64_t version64 = -1, version32 = -1;   // values_version they were laid out from
+        int64_t version64 = -1, version32 = -1;   // 2 values_version (+ 1: transposed) they were laid out from
         uint64_t* slots = nullptr;     // exchanged sums and z
+        uint64_t* bi_slots = nullptr;  // exchanged sums and halo values of BiCGStab (bi_tile.hip)
         uint32_t* bar = nullptr;       // abort word
     } tiles;
     uint64_t* d_slots = nullptr;       // what the resident CG loop exchanges (cg_loop.hip)
