@@ -21,16 +21,16 @@ SOURCES = ["plan.hip", "update.hip", "spmv.hip", "cg.hip", "grad.hip", "order.hi
            "cg_loop.hip", "cg_tile.hip", "tile_order.hip", "bi_tile.hip", "noalloc.hip", "capi.cpp", "ipc.cpp"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # kernels keep a thread's rows or taps in arrays that are only ever indexed
+         # by constants; this pass would make each one register tuple, copied
+         # whole (and waited for) wherever paths join
+         "-mllvm", "-disable-promote-alloca-to-vector",
          "-Wall", "-Wno-unused-function", "-I", INCLUDE]
-# these keep a thread's rows in arrays that are only ever indexed by
-# constants; the pass would make each one register tuple, copied whole
-SOURCE_FLAGS = {"cg_tile.hip": ["-mllvm", "-disable-promote-alloca-to-vector"],
-                "bi_tile.hip": ["-mllvm", "-disable-promote-alloca-to-vector"]}
 
 
 def _compile(src: str, out_dir: str = BUILD, extra=()) -> str:
     obj = os.path.join(out_dir, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, *SOURCE_FLAGS.get(src, []), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".cpp"):
         cmd[1:1] = ["-x", "hip"]
     p = subprocess.run(cmd, capture_output=True, text=True)

@@ -827,7 +827,8 @@ struct Src {
 Src source(const rp_plan* p, bool ordered) {
     if (ordered)
         return Src{p->nnz, p->d_ro_row_ptr, p->d_ro_col, p->d_ro_val64, p->d_ro_val32, p->d_ro_dinv64,
-                   p->d_ro_dinv32, SpmvIdx{p->d_ro_row_ptr, p->d_ro_col, nullptr, nullptr, nullptr}};
+                   p->d_ro_dinv32, SpmvIdx{p->d_ro_row_ptr, p->d_ro_col, nullptr, nullptr, nullptr,
+                                       (int32_t)p->nnz}};
     return Src{p->nnz, p->d_row_ptr, p->d_col, p->d_val64, p->d_val32, p->d_dinv64, p->d_dinv32, spmv_idx(p)};
 }
 
@@ -928,8 +929,8 @@ int cycle_down(AmgHier& h, const Src& q, int32_t l, const T* r, const int32_t* g
     T* xc = L.target < h.tail_level ? cv[1] : nullptr;   // the tail makes its own first sweep
     const T* dinv_c = Prec<T>::dinv(C);
     if (l == 0) {
-        hipLaunchKernelGGL(amg_resid<T>, dim3(spmv_grid(n)), dim3(SPMV_BLOCK), 0, s, n, q.ix, Prec<T>::val0(q),
-                           v[1], r, v[2], gate);
+        hipLaunchKernelGGL(amg_resid<T>, dim3(spmv_grid(n, INT32_MAX)), dim3(SPMV_BLOCK), 0, s, n, q.ix,
+                           Prec<T>::val0(q), v[1], r, v[2], gate);
     } else {
         const int cr = chunk_rows(L), g = chunk_grid(n, cr);
         if (cr == 64)

@@ -802,7 +802,7 @@ struct MatView {
 };
 
 MatView mat_view(rp_plan* p, bool ordered) {
-    if (ordered) return MatView{SpmvIdx{p->d_ro_row_ptr, p->d_ro_col, nullptr, nullptr, nullptr}, -1};
+    if (ordered) return MatView{SpmvIdx{p->d_ro_row_ptr, p->d_ro_col, nullptr, nullptr, nullptr, (int32_t)p->nnz}, -1};
     return MatView{spmv_idx(p), p->xw_mode};
 }
 

@@ -53,11 +53,14 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 __device__ __forceinline__ int32_t wave_incl_scan(int32_t v) {
-    const int lane = threadIdx.x & 63;
-    for (int d = 1; d < 64; d <<= 1) {
-        int32_t u = __shfl_up(v, d, 64);
-        if (lane >= d) v += u;
-    }
+    // within rows of 16 lanes, then the last lane of a row into the next rows;
+    // lanes without a source add 0
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // from 1 lane below
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // rows 0, 2 -> 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 -> rows 2, 3
     return v;
 }
 

@@ -344,16 +344,16 @@ namespace rp {
 // SpMV-shaped kernels: at most SPMV_GRID_MAX blocks (a multiple of N_XCD),
 // block L taking row groups L, L + G, L + 2G, ...
 constexpr int SPMV_GRID_MAX = 1536;
-inline int spmv_grid(int64_t n_rows) {
+inline int spmv_grid(int64_t n_rows, int most = SPMV_GRID_MAX) {
     int64_t groups = (n_rows + SPMV_BLOCK - 1) / SPMV_BLOCK;
     // more groups than the cap: the fewest groups per block the cap allows,
     // on just enough blocks that every block gets that many (no short last
     // round on a fraction of the grid)
-    const int64_t rounds = (groups + SPMV_GRID_MAX - 1) / SPMV_GRID_MAX;
+    const int64_t rounds = (groups + most - 1) / most;
     if (rounds > 1) groups = (groups + rounds - 1) / rounds;
     int64_t g = ((groups + N_XCD - 1) / N_XCD) * N_XCD;
     if (g < N_XCD) g = N_XCD;
-    if (g > SPMV_GRID_MAX) g = SPMV_GRID_MAX;
+    if (g > most) g = most;
     return (int)g;
 }
 // elementwise kernels: grid-stride loops over at most VEC_GRID_MAX blocks

@@ -14,7 +14,9 @@ spmv_kernel(int32_t n_rows, SpmvIdx ix, const T* __restrict__ val, const T* __re
         const int32_t r0 = g * SPMV_BLOCK;
         const int32_t nr = min(SPMV_BLOCK, n_rows - r0);
         const GroupRow<T> gr_ = spmv_group_row<T, NW>(ix, val, x, n_rows, g, nr, w, xs, lds, gr);
-        if ((int32_t)threadIdx.x < nr) y[r0 + threadIdx.x] = gr_.s;
+        // y is not read here again: non-temporal, it leaves x the caches (256^3
+        // FP64 247 -> 223 us)
+        if ((int32_t)threadIdx.x < nr) __builtin_nontemporal_store(gr_.s, y + r0 + threadIdx.x);
     }
 }
 
@@ -22,8 +24,8 @@ template <typename T>
 int launch_spmv(rp_plan* p, const T* val, const T* x, T* y, hipStream_t s) {
     if (p->n_rows == 0) return RP_OK;
     const XWin w{{p->xw_d[0], p->xw_d[1]}};
-#define RP_LAUNCH(NW)                                                                                    \
-    hipLaunchKernelGGL((spmv_kernel<T, NW>), dim3(spmv_grid(p->n_rows)), dim3(SPMV_BLOCK), 0, s,        \
+#define RP_LAUNCH(NW)                                                                                        \
+    hipLaunchKernelGGL((spmv_kernel<T, NW>), dim3(spmv_grid(p->n_rows, INT32_MAX)), dim3(SPMV_BLOCK), 0, s, \
                        (int32_t)p->n_rows, spmv_idx(p), val, x, y, w)
     RP_DISPATCH_NW(p->xw_mode, RP_LAUNCH);
 #undef RP_LAUNCH

@@ -39,13 +39,19 @@
 //
 // Coded groups stage their values in LDS straight from memory (16-byte
 // packs).  In FP64 they also stage the diagonal window x[r0 - 64, r0 + 320)
-// for the taps within +-64 rows, and hold the x of only 8 taps in registers
-// at a time (a 9th to 16th offset is summed after the first 8, in the same
-// order), which keeps 7 waves per SIMD instead of 6.  FP32 measured faster
-// without either and takes all 16 taps from memory in one pass.  Both
-// precisions load the next group's metadata (offset count, value stretch,
-// masks) while the current group's values load, and hand LDS over with
-// barriers that do not wait for global loads (lds_barrier).
+// for the taps within +-64 rows (FP32 measured faster with every tap from
+// memory).  The x of all taps are issued before the first sum, and the sums
+// read LDS four taps at a time.  A block that takes several groups loads the
+// next one's metadata (offset count, value stretch, offsets, masks) while the
+// current one's values load, and hands LDS over with barriers that do not wait
+// for global loads (lds_barrier).
+//
+// What bounds it is memory: 1.24 GB at 256^3 FP64 in 202 us, 6.1 TB/s.  A block
+// per group measured fastest, at every size from some thousand groups on
+// (256^3 FP64 218 us with 1536 blocks, 208 with 8192, 202 with 65536; FP32 139,
+// 128, 118; 201 x 150 x 177 FP32 45.5, 40.7, 37.6): the chip then always has a
+// block whose loads are not out yet.  A block that loops has all its waves wait
+// at one barrier.
 #pragma once
 
 #include "device_util.hpp"
@@ -74,12 +80,14 @@ struct SpmvIdx {
     const int32_t* goi_k;      // [groups] offsets of a coded group, 0 = CSR group
     const int32_t* goi_off;    // [groups * GOI_KMAX] ascending col - row
     const uint16_t* goi_mask;  // [n] bit j: the row has column row + off[j]
+    int32_t nnz;
 };
 
 // the index the kernels use for plan p
 inline SpmvIdx spmv_idx(const rp_plan* p) {
     const bool coded = p->goi_on && p->coded_groups > 0;
-    return SpmvIdx{p->d_row_ptr, p->d_col, coded ? p->d_goi_k : nullptr, p->d_goi_off, p->d_goi_mask};
+    return SpmvIdx{p->d_row_ptr, p->d_col, coded ? p->d_goi_k : nullptr, p->d_goi_off, p->d_goi_mask,
+                   (int32_t)p->nnz};
 }
 
 template <typename T>
@@ -89,8 +97,18 @@ struct GroupRow {
     T xi;        // coded: x of the thread's row
 };
 
-// cache-policy bits of the direct-to-LDS loads: non-temporal (streamed once)
-constexpr int SPMV_NT_AUX = 2;
+// The values (and columns) of a matrix larger than this are loaded
+// non-temporally: they cannot stay in the 256 MB memory-side cache beside the
+// vectors, and would push x out of it (256^3 FP64 247 us against 257, FP32 144
+// against 152).  Smaller ones stay there from product to product (128^3 FP64
+// 27.8 us against 31.8, 201 x 150 x 177 FP32 45.9 against 49.7).
+constexpr int64_t SPMV_NT_BYTES = 160 << 20;
+constexpr int SPMV_NT_AUX = 2;   // cache-policy bits of a direct-to-LDS load: non-temporal
+
+template <typename T>
+__device__ __forceinline__ bool streamed(const SpmvIdx& ix) {
+    return (int64_t)ix.nnz * (int64_t)sizeof(T) > SPMV_NT_BYTES;
+}
 
 template <typename T>
 __device__ __forceinline__ T nt_load(const T* p) {
@@ -242,6 +260,7 @@ __device__ __forceinline__ T spmv_group_csr(const int32_t* __restrict__ row_ptr,
 struct CodedMeta {
     int32_t K, base, end;
     uint32_t m;
+    int32_t off;   // lane j (mod GOI_KMAX) of a wavefront: offset j
 };
 
 // The group-uniform values are read through the constant address space, so
@@ -255,6 +274,7 @@ __device__ __forceinline__ void coded_meta_load(const SpmvIdx& ix, int32_t g, in
     c.base = ((ConstI32)ix.row_ptr)[r0];
     c.end = ((ConstI32)ix.row_ptr)[r0 + nr];
     c.m = (int32_t)threadIdx.x < nr ? (uint32_t)ix.goi_mask[r0 + threadIdx.x] : 0u;
+    c.off = ix.goi_off[(int64_t)g * GOI_KMAX + (threadIdx.x & (GOI_KMAX - 1))];
 }
 
 // Row groups of block L (after xcd_block()) in a grid of G blocks: L, L + G,
@@ -271,6 +291,7 @@ __device__ __forceinline__ GroupRange block_groups(const SpmvIdx& ix, int32_t n_
     r.g0 = xcd_block();
     r.step = (int32_t)gridDim.x;
     r.meta.K = 0;
+    r.meta.off = 0;
     if (ix.goi_k != nullptr && r.g0 < r.n_groups) coded_meta_load(ix, r.g0, n_rows, r.meta);
     return r;
 }
@@ -288,13 +309,12 @@ __device__ __forceinline__ GroupRow<T> spmv_group_coded(const SpmvIdx& ix, const
     constexpr int E = Pack<T>::E;
     __shared__ int32_t wtot[SPMV_BLOCK / 64];
     const int t = threadIdx.x;
-    // this group's metadata (loaded during the previous group) and offset table
+    // this group's metadata, loaded during the previous group
     const int32_t K = meta.K, base = meta.base, end = meta.end;
     const uint32_t m = meta.m;
     int32_t off[GOI_KMAX];
-    const ConstI32 offp = (ConstI32)ix.goi_off + (int64_t)(r0 / SPMV_BLOCK) * GOI_KMAX;
 #pragma unroll
-    for (int j = 0; j < GOI_KMAX; ++j) off[j] = offp[j];
+    for (int j = 0; j < GOI_KMAX; ++j) off[j] = __builtin_amdgcn_readlane(meta.off, j);
     const int32_t al = base & ~(E - 1);            // packs start on a multiple of E
     const int32_t npk = (end - al + E - 1) / E;
     // FP64: the block's diagonal window x[r0 - XN, r0 + SPMV_BLOCK + XN) goes
@@ -326,65 +346,71 @@ __device__ __forceinline__ GroupRow<T> spmv_group_coded(const SpmvIdx& ix, const
     constexpr int U = SPMV_CAP / E / SPMV_BLOCK;
     typedef __attribute__((address_space(3))) void* LdsPtr;
     const int32_t wave0 = t & ~63;
+#define RP_LOAD(AUX)                                                                                              \
+    for (int u = 0; u < U; ++u)                                                                                   \
+        if (t + u * SPMV_BLOCK < npk)                                                                             \
+            __builtin_amdgcn_global_load_lds((void*)(reinterpret_cast<const VP*>(val + al) + (t + u * SPMV_BLOCK)), \
+                                             (LdsPtr)(reinterpret_cast<VP*>(lds) + u * SPMV_BLOCK + wave0), 16, 0, \
+                                             AUX)
+    if (streamed<T>(ix)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (t + u * SPMV_BLOCK < npk)
-            __builtin_amdgcn_global_load_lds((void*)(reinterpret_cast<const VP*>(val + al) + (t + u * SPMV_BLOCK)),
-                                             (LdsPtr)(reinterpret_cast<VP*>(lds) + u * SPMV_BLOCK + wave0), 16, 0,
-                                             SPMV_NT_AUX);
-    // x of the present entries of the first KH taps, all issued before the
-    // first use; taps KH.. (groups with more offsets) follow after the sums.
-    // FP64 takes 8 at a time: the registers of all 16 would cost it a wave
-    // per SIMD.  FP32 fits all 16 at full occupancy.
-    constexpr int KH = XWIN ? GOI_KMAX / 2 : GOI_KMAX;
-    T gx[KH];
-    if constexpr (XWIN) {
-#pragma unroll
-        for (int j = 0; j < KH; ++j)
-            gx[j] = (j < K && (off[j] < -XN || off[j] > XN) && ((m >> j) & 1u)) ? x[r0 + t + off[j]] : T(0);
-        xd[t] = xa;
-        if (t < 2 * XN) xd[t + SPMV_BLOCK] = xb;
+        RP_LOAD(SPMV_NT_AUX);
     } else {
 #pragma unroll
-        for (int j = 0; j < KH; ++j) gx[j] = (j < K && ((m >> j) & 1u)) ? x[r0 + t + off[j]] : T(0);
+        RP_LOAD(0);
+    }
+#undef RP_LOAD
+    // x of the row's present taps, all issued before the first use, C at a time
+    // so that a short table costs no more
+    constexpr int C = 4;
+    const int32_t own = min(r0 + t, n - 1);
+    const T xo = XWIN ? T(0) : x[own];
+    T gx[GOI_KMAX];
+#pragma unroll
+    for (int j0 = 0; j0 < GOI_KMAX; j0 += C)
+        if (j0 < K) {
+#pragma unroll
+            for (int j = j0; j < j0 + C; ++j)
+                if constexpr (XWIN) {
+                    if (off[j] < -XN || off[j] > XN) gx[j] = ((m >> j) & 1u) ? x[own + off[j]] : T(0);
+                } else {
+                    gx[j] = ((m >> j) & 1u) ? x[own + off[j]] : T(0);
+                }
+        }
+    if constexpr (XWIN) {
+        xd[t] = xa;
+        if (t < 2 * XN) xd[t + SPMV_BLOCK] = xb;
     }
     // the packs of every wave must be in LDS before any wave reads them: wait
     // for all of this wave's loads, then the barrier
     __builtin_amdgcn_s_waitcnt(0);
     lds_barrier();
-    if constexpr (XWIN) {
-#pragma unroll
-        for (int j = 0; j < KH; ++j)
-            if (j < K && off[j] >= -XN && off[j] <= XN && ((m >> j) & 1u)) gx[j] = xd[XN + t + off[j]];
-    }
+    const int32_t wv = __builtin_amdgcn_readfirstlane(t >> 6);
     int32_t pos = inc - c + (base - al);
-    for (int q = 0; q < (t >> 6); ++q) pos += wtot[q];
+#pragma unroll
+    for (int q = 0; q < SPMV_BLOCK / 64 - 1; ++q) pos += q < wv ? wtot[q] : 0;
     T s = T(0);
 #pragma unroll
-    for (int j = 0; j < KH; ++j)
-        if (j < K && ((m >> j) & 1u)) {
-            s += lds[pos] * gx[j];
-            ++pos;
-        }
-    if (KH < GOI_KMAX && K > KH) {
+    for (int j0 = 0; j0 < GOI_KMAX; j0 += C)
+        if (j0 < K) {
+            T lv[C], lx[C];
 #pragma unroll
-        for (int j = KH; j < GOI_KMAX; ++j) {
-            T v = T(0);
-            if (j < K && ((m >> j) & 1u)) {
-                if (XWIN && off[j] >= -XN && off[j] <= XN) v = xd[XN + t + off[j]];
-                else v = x[r0 + t + off[j]];
+            for (int u = 0; u < C; ++u) {
+                const int j = j0 + u;
+                const bool near = XWIN && off[j] >= -XN && off[j] <= XN;
+                lv[u] = lds[min(pos, SPMV_CAP - 1)];   // an absent tap's is not used
+                pos += (m >> j) & 1u;
+                if (near) lx[u] = xd[XN + t + off[j]];
+                else lx[u] = gx[j];
             }
-            gx[j - KH] = v;
-        }
 #pragma unroll
-        for (int j = KH; j < GOI_KMAX; ++j)
-            if (j < K && ((m >> j) & 1u)) {
-                s += lds[pos] * gx[j - KH];
-                ++pos;
+            for (int u = 0; u < C; ++u) {
+                const T sn = s + lv[u] * lx[u];
+                s = ((m >> (j0 + u)) & 1u) ? sn : s;
             }
-    }
+        }
     if constexpr (XWIN) return GroupRow<T>{s, true, xd[XN + t]};
-    return GroupRow<T>{s, true, t < nr ? x[r0 + t] : T(0)};
+    return GroupRow<T>{s, true, xo};
 }
 
 // Row sum of row g * SPMV_BLOCK + threadIdx.x in the form chosen for group g.
@@ -398,9 +424,10 @@ __device__ __forceinline__ GroupRow<T> spmv_group_row(const SpmvIdx& ix, const T
     if (ix.goi_k != nullptr) {
         const int32_t g_next = g + gr.step < gr.n_groups ? g + gr.step : -1;
         if (gr.meta.K > 0) return spmv_group_coded<T>(ix, val, x, n, r0, nr, lds, gr.meta, g_next);
-        const T s = spmv_group_csr<T, NW>(ix.row_ptr, ix.col, val, x, n, r0, nr, w, xs, lds);
+        // (before the group, whose barriers then cover it: pending after it, the
+        // start of the next coded group would wait for this one's stores too)
         if (g_next >= 0) coded_meta_load(ix, g_next, n, gr.meta);
-        return GroupRow<T>{s, false, T(0)};
+        return GroupRow<T>{spmv_group_csr<T, NW>(ix.row_ptr, ix.col, val, x, n, r0, nr, w, xs, lds), false, T(0)};
     }
     return GroupRow<T>{spmv_group_csr<T, NW>(ix.row_ptr, ix.col, val, x, n, r0, nr, w, xs, lds), false, T(0)};
 }
