@@ -97,12 +97,13 @@ struct GroupRow {
     T xi;        // coded: x of the thread's row
 };
 
-// The values (and columns) of a matrix larger than this are loaded
-// non-temporally: they cannot stay in the 256 MB memory-side cache beside the
-// vectors, and would push x out of it (256^3 FP64 247 us against 257, FP32 144
-// against 152).  Smaller ones stay there from product to product (128^3 FP64
-// 27.8 us against 31.8, 201 x 150 x 177 FP32 45.9 against 49.7).
-constexpr int64_t SPMV_NT_BYTES = 160 << 20;
+// The values of a matrix larger than this are loaded non-temporally: beside a
+// solver's vectors, or another matrix, they do not stay in the 256 MB
+// memory-side cache, and would push x out of it (256^3 FP64 247 us against 257;
+// FP32 of 149 MB 39.0 against 42.9, two matrices in turn; multigrid CG at 122 MB
+// 17.8 ms against 18.2).  Smaller ones stay there from product to product
+// (855 000 rows FP64, 48 MB: 14.0 us against 15.2).
+constexpr int64_t SPMV_NT_BYTES = 64 << 20;
 constexpr int SPMV_NT_AUX = 2;   // cache-policy bits of a direct-to-LDS load: non-temporal
 
 template <typename T>
