@@ -134,7 +134,7 @@ int alloc_values(rp_plan* p) {
     RP_TRY(dalloc(&p->d_p32, n));
     RP_TRY(dalloc(&p->d_q32, n));
     RP_TRY(dalloc(&p->d_x32, n));
-    RP_HIP_TRY(hipMalloc(&p->d_partials, sizeof(double) * PART_TOTAL));
+    RP_HIP_TRY(hipMalloc(&p->d_partials, sizeof(double) * (size_t)(PART_TOTAL + fold_sums(n))));
     RP_TRY(dalloc(&p->d_st64, 1));
     RP_TRY(dalloc(&p->d_st32, 1));
     RP_TRY(dalloc(&p->d_st_outer, 1));

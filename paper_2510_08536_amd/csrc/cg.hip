@@ -183,11 +183,11 @@ cg_finalize(int32_t mode, int32_t k, int32_t max_iter, T tol2, T pause_frac2, in
     st->done = d;
 }
 
-// K1: q = A p; partials of (p, q) -> PART_A
+// K1: q = A p; partials of (p, q) -> pq, one per block
 template <typename T, int NW>
 __global__ void __launch_bounds__(SPMV_BLOCK)
 cg_spmv_pq(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict__ p, T* __restrict__ q,
-           T* __restrict__ part, const CgState<T>* st, XWin w) {
+           T* __restrict__ pq, const CgState<T>* st, XWin w) {
 #pragma clang fp contract(off)
     if (st->done != CG_RUNNING || st->iter >= st->max_iter) return;
     __shared__ __align__(16) T lds[SPMV_CAP];
@@ -206,7 +206,23 @@ cg_spmv_pq(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict
         }
     }
     const T b = block_sum<T, SPMV_BLOCK>(ppq, red);
-    if (threadIdx.x == 0) part[PART_A + xcd_block()] = b;
+    if (threadIdx.x == 0) pq[xcd_block()] = b;
+}
+
+// K1's sums of a block per group to FOLD_BLOCKS partials -> PART_A: block b adds
+// a run of them.  At 256^3 this launch takes 4 us and K1 without its loop saves
+// 20 (FP32) and 15 (FP64); below some 4 million rows they are about equal.
+constexpr int FOLD_BLOCKS = 256;
+template <typename T>
+__global__ void __launch_bounds__(VEC_BLOCK)
+cg_fold(int32_t m, const T* __restrict__ sums, T* __restrict__ part) {
+#pragma clang fp contract(off)
+    __shared__ T red[VEC_BLOCK / 64];
+    const int32_t per = (m + FOLD_BLOCKS - 1) / FOLD_BLOCKS, i0 = blockIdx.x * per;
+    T s = T(0);
+    for (int32_t i = i0 + (int32_t)threadIdx.x; i < min(m, i0 + per); i += VEC_BLOCK) s += sums[i];
+    const T b = block_sum<T, VEC_BLOCK>(s, red);
+    if (threadIdx.x == 0) part[PART_A + blockIdx.x] = b;
 }
 
 // K2: alpha = rz_k / (p, q); r -= alpha q; partials of (r, M^-1 r) ->
@@ -909,18 +925,24 @@ int launch_resume(Cg<T>& c) {
 // k < 0: K2 and K3 take the iteration number from the device state (graphs)
 template <typename T>
 int launch_iteration(Cg<T>& c, int32_t k, hipStream_t s) {
-    const dim3 gs(c.g_spmv), bs(SPMV_BLOCK), gv(c.g_vec), bv(VEC_BLOCK);
+    // the largest systems: a block per group, whose sums are folded
+    const bool fold = fold_sums(c.n) > 0;
+    const int32_t g_pq = fold ? FOLD_BLOCKS : c.g_spmv;
+    T* pq = fold ? c.part + PART_TOTAL : c.part + PART_A;
+    const dim3 gs(fold ? fold_sums(c.n) : c.g_spmv), bs(SPMV_BLOCK), gv(c.g_vec), bv(VEC_BLOCK);
     RP_TRY(timing_begin(c.plan, c.kernel_id, s));
 #define RP_LAUNCH(NW) \
-    hipLaunchKernelGGL((cg_spmv_pq<T, NW>), gs, bs, 0, s, c.n, c.ix, c.val, c.p, c.q, c.part, c.st, c.w)
+    hipLaunchKernelGGL((cg_spmv_pq<T, NW>), gs, bs, 0, s, c.n, c.ix, c.val, c.p, c.q, pq, c.st, c.w)
     RP_DISPATCH_NW(c.xw_mode, RP_LAUNCH);
 #undef RP_LAUNCH
     RP_TRY(timing_end(c.plan, c.kernel_id, s));
+    if (fold)
+        hipLaunchKernelGGL(cg_fold<T>, dim3(FOLD_BLOCKS), bv, 0, s, (int32_t)gs.x, pq, c.part);
     if (c.amg) {
         // K2 without (r, z); the V-cycle (skipped when K2 did no update)
         // stores z and the (r, z) partials; K3 reads z
         T* sweep = amg_first_sweep<T>(c.plan, c.amg_ordered);
-        hipLaunchKernelGGL((cg_update_r<T, false>), gv, bv, 0, s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st,
+        hipLaunchKernelGGL((cg_update_r<T, false>), gv, bv, 0, s, c.n, k, g_pq, c.r, c.q, c.dinv, c.part, c.st,
                            sweep, (T)RP_AMG_OMEGA);
         RP_HIP_TRY(hipGetLastError());
         RP_TRY(amg_apply<T>(c.plan, c.r, c.z, c.part, c.g_rz, false, sweep != nullptr, &c.st->kk, s, c.amg_ordered));
@@ -929,13 +951,13 @@ int launch_iteration(Cg<T>& c, int32_t k, hipStream_t s) {
     } else if (c.bj_minv) {
         if (c.bj_lane) {
 #define RP_LAUNCH(BS)                                                                                              \
-    hipLaunchKernelGGL((cg_update_r_bj_lane<T, BS>), gv, bv, 0, s, c.n, k, c.g_spmv, c.bj_minv, c.r, c.q, c.z, c.part, \
+    hipLaunchKernelGGL((cg_update_r_bj_lane<T, BS>), gv, bv, 0, s, c.n, k, g_pq, c.bj_minv, c.r, c.q, c.z, c.part, \
                        c.st)
             RP_DISPATCH_BS_LANE(c.bj_bs, RP_LAUNCH);
 #undef RP_LAUNCH
         } else {
 #define RP_LAUNCH(BS)                                                                                          \
-    hipLaunchKernelGGL((cg_update_r_bj<T, BS>), gv, bv, 0, s, c.n, k, c.g_spmv, c.bj_nb, c.bj_start, c.bj_minv, \
+    hipLaunchKernelGGL((cg_update_r_bj<T, BS>), gv, bv, 0, s, c.n, k, g_pq, c.bj_nb, c.bj_start, c.bj_minv, \
                        c.r, c.q, c.z, c.part, c.st)
             RP_DISPATCH_BS(c.bj_bs, RP_LAUNCH);
 #undef RP_LAUNCH
@@ -943,7 +965,7 @@ int launch_iteration(Cg<T>& c, int32_t k, hipStream_t s) {
         hipLaunchKernelGGL((cg_update_xp<T, true>), gv, bv, 0, s, c.n, k, c.g_vec, c.g_vec, 0, c.r, c.dinv, c.z, c.x, c.p,
                            c.part, c.st);
     } else {
-        hipLaunchKernelGGL(cg_update_r<T>, gv, bv, 0, s, c.n, k, c.g_spmv, c.r, c.q, c.dinv, c.part, c.st,
+        hipLaunchKernelGGL(cg_update_r<T>, gv, bv, 0, s, c.n, k, g_pq, c.r, c.q, c.dinv, c.part, c.st,
                            (T*)nullptr, T(0));
         hipLaunchKernelGGL((cg_update_xp<T, false>), gv, bv, 0, s, c.n, k, c.g_vec, c.g_vec, 0, c.r, c.dinv, c.z, c.x, c.p,
                            c.part, c.st);

@@ -382,6 +382,12 @@ constexpr int PART_B = SPMV_GRID_MAX;                        // bb
 constexpr int PART_RZ = 2 * SPMV_GRID_MAX;                   // (r, z)
 constexpr int PART_RR = 2 * SPMV_GRID_MAX + VEC_GRID_LIMIT;  // (r, r)
 constexpr int PART_TOTAL = 2 * SPMV_GRID_MAX + 2 * VEC_GRID_LIMIT;
+// behind them, on systems of more than FOLD_GROUPS row groups: the sums of K1's
+// blocks, one per group (0: K1 leaves partials)
+constexpr int64_t FOLD_GROUPS = 16384;
+inline int fold_sums(int64_t n_rows) {
+    return n_rows > FOLD_GROUPS * SPMV_BLOCK ? spmv_grid(n_rows, INT32_MAX) : 0;
+}
 
 // plan.hip
 int plan_build(rp_plan* p, const rp_rank_desc* share);
