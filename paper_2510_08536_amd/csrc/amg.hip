@@ -417,16 +417,20 @@ __device__ __forceinline__ T wave_row_sum(const int32_t* __restrict__ row_ptr, c
     }
     T s = T(0);
     if (e1 - e0 <= wcap<CR>()) {
+        // lanes past the chunk load its last entry again (a row has its diagonal,
+        // so there is one): a branch per load kept the loads from leaving together
+        // (a V-cycle 421 -> 408 us at 160^3, 263 -> 246 at 131 x 117 x 142)
         int32_t cv[WU];
         T vv[WU], xv[WU];
 #pragma unroll
         for (int u = 0; u < WU; ++u) {
             const int32_t e = e0 + t + u * WB;
-            cv[u] = e < e1 ? col[e] : 0;
-            vv[u] = e < e1 ? val[e] : T(0);
+            const int32_t ec = min(e, e1 - 1);
+            cv[u] = col[ec];
+            vv[u] = val[ec];
         }
 #pragma unroll
-        for (int u = 0; u < WU; ++u) xv[u] = (e0 + t + u * WB < e1) ? x(cv[u]) : T(0);
+        for (int u = 0; u < WU; ++u) xv[u] = x(cv[u]);
 #pragma unroll
         for (int u = 0; u < WU; ++u) {
             const int32_t e = e0 + t + u * WB;
@@ -486,11 +490,12 @@ amg_csr_post(int32_t n, const int32_t* __restrict__ row_ptr, const int32_t* __re
 int chunk_rows(const AmgLevel& L) { return L.nnz > 12 * L.n ? 32 : 64; }
 
 // grid of the chunked kernels: a multiple of 8 (xcd_block), one chunk per
-// block up to 16384 blocks
+// block (at most 16384 blocks a V-cycle took 430 us at 160^3 and 1463 at 256^3
+// where this takes 421 and 1385)
 int chunk_grid(int64_t n, int cr) {
     int64_t g = (n + cr - 1) / cr;
     g = ((g + N_XCD - 1) / N_XCD) * N_XCD;
-    return (int)std::max<int64_t>(N_XCD, std::min<int64_t>(g, 16384));
+    return (int)std::max<int64_t>(N_XCD, g);
 }
 
 // rc[I] = the restricted v of coarse row I (its rows in the list's order, see
@@ -525,10 +530,11 @@ amg_restrict(int32_t nc, const int32_t* __restrict__ rows_ptr, const int32_t* __
         for (int32_t base = f0; base < f1; base += RCAP) {
             int32_t k[RU];
             T vv[RU];
+            // past the list: its last row again, as in wave_row_sum
 #pragma unroll
-            for (int u = 0; u < RU; ++u) k[u] = base + t + u * AB < f1 ? rows[base + t + u * AB] : 0;
+            for (int u = 0; u < RU; ++u) k[u] = rows[min(base + t + u * AB, f1 - 1)];
 #pragma unroll
-            for (int u = 0; u < RU; ++u) vv[u] = base + t + u * AB < f1 ? v[k[u] & INT32_MAX] : T(0);
+            for (int u = 0; u < RU; ++u) vv[u] = v[k[u] & INT32_MAX];
 #pragma unroll
             for (int u = 0; u < RU; ++u) {
                 tv[t + u * AB] = vv[u];
@@ -981,9 +987,9 @@ int cycle_up(AmgHier& h, int32_t l, const int32_t* gate, hipStream_t s) {
 // vectors a pass each.  With the odd levels as launches of their own, a first
 // sweep per level and the tail's vectors in memory, a cycle took 355 us at
 // 131 x 117 x 142 cells, 598 at 160^3 and 1799 at 256^3 (FP64, 40 launches);
-// now 277, 461 and 1524 us (19 to 21 launches).  What is left is the fine
-// level's two products (38 + 39 us of the 277, 5.4 TB/s) and, below about
-// 10^5 rows, the launches.  swept: amg_first_sweep(h) already holds
+// now 242, 401 and 1387 us (19 to 21 launches).  What is left is the fine
+// level's two products (27 + 29 us of the 242, near the memory's rate) and,
+// below about 10^5 rows, the launches.  swept: amg_first_sweep(h) already holds
 // omega (dinv r).
 template <typename T>
 int vcycle(AmgHier& h, const Src& q, const T* r, T* y, T* part, int32_t n_part, bool rr, bool swept,
@@ -1024,9 +1030,9 @@ int vcycle(AmgHier& h, const Src& q, const T* r, T* y, T* part, int32_t n_part, 
     for (int32_t l = (h.tail_level - 1) & ~1; l > 0; l -= 2) RP_TRY(cycle_up<T>(h, l, gate, s));
     hipLaunchKernelGGL(amg_prolong<T>, dim3(grid_of(n)), dim3(AB), 0, s, n, L0.map,
                        (const T*)Prec<T>::vec(h.lev[L0.target])[3], v[1], gate);
-#define RP_LAUNCH(PT, RRF)                                                                                    \
-    hipLaunchKernelGGL((amg_post<T, PT, RRF>), dim3(spmv_grid(n)), dim3(SPMV_BLOCK), 0, s, n, q.ix, Prec<T>::val0(q), \
-                       v[1], r, Prec<T>::dinv0(q), omega, y, part, gate)
+#define RP_LAUNCH(PT, RRF)                                                                                       \
+    hipLaunchKernelGGL((amg_post<T, PT, RRF>), dim3(spmv_grid(n, PT ? SPMV_GRID_MAX : INT32_MAX)), dim3(SPMV_BLOCK), \
+                       0, s, n, q.ix, Prec<T>::val0(q), v[1], r, Prec<T>::dinv0(q), omega, y, part, gate)
     if (want && rr) RP_LAUNCH(true, true);
     else if (want) RP_LAUNCH(true, false);
     else RP_LAUNCH(false, false);
