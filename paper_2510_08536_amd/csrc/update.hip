@@ -113,16 +113,19 @@ __device__ __forceinline__ double slot_value(const RankSlots& r, int32_t k, cons
     return table[4 * r.s + reg][loc - base];
 }
 
-__device__ __forceinline__ void block_chunk(int64_t n, int32_t& a, int32_t& b) {
+__device__ __forceinline__ void block_chunk(int64_t n, int32_t block, int32_t& a, int32_t& b) {
     const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
-    const int64_t a64 = (int64_t)blockIdx.x * per;
+    const int64_t a64 = (int64_t)block * per;
     a = (int32_t)(a64 < n ? a64 : n);
     b = (int32_t)(a64 + per < n ? a64 + per : n);
 }
 
 // val64[j] = value of slot P^-1(j), val32 = RNE, dinv = 1 / diag, straight
 // from the per-rank arrays; same values and flags as scatter_kernel on the
-// staged buffer
+// staged buffer.  Bound by memory: 24 bytes a position, 2.8 GB at 256^3 in 620
+// us.  Neighbouring chunks run on one die: a line of `lower` is read for rows a
+// mesh line and a plane apart, and of randomly numbered faces for many rows
+// (180^3, numbered at random: 520 us with chunks dealt to the dies in turn, 410).
 __global__ void __launch_bounds__(256)
 gather_kernel(int32_t n_pos, int32_t n_rows, int32_t alpha, const int32_t* __restrict__ perm_inv,
               const double* const* __restrict__ table, const int32_t* __restrict__ slot_off,
@@ -131,7 +134,7 @@ gather_kernel(int32_t n_pos, int32_t n_rows, int32_t alpha, const int32_t* __res
               uint32_t* flags) {
     bool bad = false;
     int32_t j0, j1;
-    block_chunk(n_pos, j0, j1);
+    block_chunk(n_pos, xcd_block(), j0, j1);
     RankSlots rs;
     constexpr int U = 4;
     int32_t j = j0 + threadIdx.x;
@@ -161,7 +164,7 @@ gather_kernel(int32_t n_pos, int32_t n_rows, int32_t alpha, const int32_t* __res
         bad |= !isfinite(v);
     }
     int32_t i0, i1;
-    block_chunk(n_rows, i0, i1);
+    block_chunk(n_rows, xcd_block(), i0, i1);
     int32_t s = -1, lo = 0, hi = 0;
     for (int32_t i = i0 + threadIdx.x; i < i1; i += 256) {
         if (i < lo || i >= hi) {
@@ -189,7 +192,7 @@ symmetry_gather_kernel(int32_t n_faces, int32_t n_iface, int32_t alpha, bool che
     bool asym = false;
     if (check_faces) {
         int32_t f0, f1;
-        block_chunk(n_faces, f0, f1);
+        block_chunk(n_faces, blockIdx.x, f0, f1);
         int32_t s = -1, lo = 0, hi = 0;
         for (int32_t f = f0 + threadIdx.x; f < f1; f += 256) {
             if (f < lo || f >= hi) {
@@ -201,7 +204,7 @@ symmetry_gather_kernel(int32_t n_faces, int32_t n_iface, int32_t alpha, bool che
         }
     }
     int32_t e0, e1;
-    block_chunk(n_iface, e0, e1);
+    block_chunk(n_iface, blockIdx.x, e0, e1);
     int32_t s = -1, lo = 0, hi = 0;
     RankSlots rp;
     for (int32_t e = e0 + threadIdx.x; e < e1; e += 256) {
@@ -301,7 +304,10 @@ int launch_update_gather(rp_plan* p, const double* const* table, bool lower_give
     }
     const int64_t n_pos = p->n_slots;
     if (n_pos == 0 && p->n_rows == 0) return RP_OK;
-    const int g = grid_for(std::max<int64_t>(n_pos, p->n_rows), 256, 2048);
+    // two rounds of the 2048 blocks the chip holds: with one round the last
+    // blocks end far apart, with more a block's search for its ranks counts
+    // (256^3: 2048 blocks 687 us, 3072 765, 4096 652, 6144 691)
+    const int g = (grid_for(std::max<int64_t>(n_pos, p->n_rows), 256, 4096) + N_XCD - 1) / N_XCD * N_XCD;
     RP_TRY(timing_begin(p, RP_KERNEL_SCATTER, s));
     hipLaunchKernelGGL(gather_kernel, dim3(g), dim3(256), 0, s, (int32_t)n_pos, (int32_t)p->n_rows, p->alpha,
                        p->d_perm_inv, table, p->d_slot_off, p->d_row0, p->d_nf, p->d_val64, p->d_val32,
