@@ -326,7 +326,9 @@ int rp_update_values_slots(rp_plan* plan, const double* slots, void* stream);
  * RP_NOALLOC_MAX_RANKS ranks or an array that is not device memory (checked
  * before any device work).  Every call on one GPU shares that array: calls
  * that overlap on one GPU (other streams, threads or plans) race, so the
- * caller serialises them. */
+ * caller serialises them.  A captured update (this one or
+ * rp_update_values_slots) runs at every replay of its graph, and the next
+ * solve takes the values it left. */
 #define RP_NOALLOC_MAX_RANKS 4096
 int rp_update_values_noalloc(rp_plan* plan, const double* const* diag, const double* const* upper,
                              const double* const* lower, const double* const* iface, void* stream);

@@ -431,7 +431,7 @@ int bi_tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
 }
 
 // The iterations k0 .. k_end, enqueued, on a plan that fits.  The abort word
-// goes to h_flags[2].
+// goes to h_flags[LOOP_ABORT].
 int launch_bi_tile(rp_plan* p, const double* src, bool transposed, const double* dinv, double* x, double* r,
                    const double* rh, double* pv, double* v, BiState* st, int32_t k0, int32_t k_end, hipStream_t s) {
     auto& tl = p->tiles;
@@ -468,7 +468,7 @@ int launch_bi_tile(rp_plan* p, const double* src, bool transposed, const double*
         hipLaunchKernelGGL(bi_from_positions, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.inv, tx, x, r, pv, v);
         RP_HIP_TRY(hipGetLastError());
     }
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + 2, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return RP_OK;
 }
 

@@ -147,7 +147,7 @@ int alloc_values(rp_plan* p) {
     RP_TRY(dalloc(&p->d_bi_st, 1));
     RP_HIP_TRY(hipMemset(p->d_bi_st, 0, sizeof(BiState)));
     RP_HIP_TRY(hipHostMalloc((void**)&p->h_bi_st, sizeof(BiState), hipHostMallocDefault));
-    RP_HIP_TRY(hipHostMalloc((void**)&p->h_flags, 3 * sizeof(uint32_t), hipHostMallocDefault));
+    RP_HIP_TRY(hipHostMalloc((void**)&p->h_flags, (N_FLAGS + 1) * sizeof(uint32_t), hipHostMallocDefault));
     RP_HIP_TRY(hipMalloc((void**)&p->d_src, sizeof(const double*) * 4 * (size_t)std::max(p->alpha, 1)));
     return RP_OK;
 }
@@ -275,8 +275,7 @@ int update(rp_plan* p, const double* const* diag, const double* const* upper, co
         RP_TRY(launch_symmetry_check(p, p->d_recv, lower != nullptr, s));
         RP_TRY(launch_update(p, p->d_recv, s));
     }
-    p->has_values = true;
-    p->values_version += 1;
+    note_update(p);
     p->last_stream = s;
     return RP_OK;
 }
@@ -408,6 +407,7 @@ int rp_plan_block_jacobi(rp_plan* p, int32_t block_size, int64_t* n_blocks, int3
     RP_CHECK(p->has_values, RP_ERR_ARG, "no values yet: call rp_update_values first");
     RP_TRY(activate(p));
     hipStream_t s = p->last_stream;
+    RP_TRY(read_flags(p, s));
     RP_TRY(bj_prepare(p, block_size, s));
     RP_HIP_TRY(hipStreamSynchronize(s));
     const int64_t nb = p->bj_blocks, P = (int64_t)block_size * (block_size + 1) / 2;
@@ -529,8 +529,7 @@ int rp_update_values_slots(rp_plan* p, const double* slots, void* stream) {
     RP_TRY(launch_clear_flags(p->d_flags, s));
     RP_TRY(launch_symmetry_check(p, slots, true, s));
     RP_TRY(launch_update(p, slots, s));
-    p->has_values = true;
-    p->values_version += 1;
+    note_update(p);
     p->last_stream = s;
     return RP_OK;
 }

@@ -50,7 +50,7 @@ template <typename T>
 int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const T* dinv, T* x, T* r, T* pv, T* q,
                    CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s, bool* ran);
 // the same by the resident loop, on a plan with resident_block > 0; enqueued,
-// the abort word to h_flags[2]
+// the abort word to h_flags[LOOP_ABORT]
 template <typename T>
 int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
                        const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s);
@@ -1124,7 +1124,7 @@ int iterate(Cg<T>& c, const rp_solve_opts& o, Loop loop) {
             else
                 RP_TRY(launch_cg_tile<T>(c.plan, c.val, c.dinv, c.x, c.r, c.p, c.st, c.h->iter, k1, c.s));
             RP_TRY(read_state(c));
-            if (c.plan->h_flags[2]) {
+            if (c.plan->h_flags[LOOP_ABORT]) {
                 set_error("the one-launch CG loop gave up waiting for another workgroup's values");
                 return RP_ERR_HIP;
             }
@@ -1182,9 +1182,7 @@ void use_amg(Cg<T>& c, T* z, bool ordered) {
     c.g_rz = c.g_spmv;
 }
 
-int pending_value_error(rp_plan* p, hipStream_t s, bool need_symmetric) {
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags, p->d_flags, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    RP_HIP_TRY(hipStreamSynchronize(s));
+int pending_value_error(rp_plan* p, bool need_symmetric) {
     if (p->h_flags[0] & FLAG_VALUE) {
         set_error("the last update produced a value that is not finite or a diagonal <= 0");
         return RP_ERR_VALUE;
@@ -1197,7 +1195,8 @@ int pending_value_error(rp_plan* p, hipStream_t s, bool need_symmetric) {
     return RP_OK;
 }
 
-int check_solvable(rp_plan* p, hipStream_t s, bool need_symmetric = true) {
+// flags_read: the caller has read them (read_flags)
+int check_solvable(rp_plan* p, hipStream_t s, bool need_symmetric, bool flags_read) {
     if (!p->has_values) {
         set_error("rp_solve before any rp_update_values");
         return RP_ERR_ARG;
@@ -1207,16 +1206,17 @@ int check_solvable(rp_plan* p, hipStream_t s, bool need_symmetric = true) {
                   (long long)p->nnz_nl);
         return RP_ERR_UNSUPPORTED;
     }
-    return pending_value_error(p, s, need_symmetric);
+    if (!flags_read) RP_TRY(read_flags(p, s));
+    return pending_value_error(p, need_symmetric);
 }
 
 }  // namespace
 
-int values_solvable(rp_plan* p, hipStream_t s) { return check_solvable(p, s, true); }
+int values_solvable(rp_plan* p, hipStream_t s) { return check_solvable(p, s, true, false); }
 
 int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, rp_solve_info& info,
                hipStream_t s, bool ordered) {
-    RP_TRY(check_solvable(p, s));
+    RP_TRY(check_solvable(p, s, true, ordered));
     const MatView m = mat_view(p, ordered);
     Cg<double> c = make_cg<double>(p, m, ordered ? p->d_ro_val64 : p->d_val64,
                                    ordered ? p->d_ro_dinv64 : p->d_dinv64, x, b, p->d_r, p->d_p, p->d_q,
@@ -1288,7 +1288,7 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
 
 int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, rp_solve_info& info,
                 hipStream_t s, bool reliable, bool ordered) {
-    RP_TRY(check_solvable(p, s));
+    RP_TRY(check_solvable(p, s, true, ordered));
     const MatView m = mat_view(p, ordered);
     // FP64: r64 = b - A x and its norm; x is the FP64 solution
     Cg<double> out = make_cg<double>(p, m, ordered ? p->d_ro_val64 : p->d_val64,
@@ -1689,7 +1689,7 @@ int bi_iterate(Bi& q, int chunk, int32_t max_iter, bool tile, bool transposed) {
             RP_TRY(launch_bi_tile(c.plan, c.val, transposed, c.dinv, c.x, c.r, q.rh, q.p, q.v, q.st, q.h->iter, k1,
                                   c.s));
             RP_TRY(bi_read(q));
-            if (c.plan->h_flags[2]) {
+            if (c.plan->h_flags[LOOP_ABORT]) {
                 set_error("the one-launch BiCGStab loop gave up waiting for another workgroup's values");
                 return RP_ERR_HIP;
             }
@@ -1726,7 +1726,7 @@ int bi_iterate(Bi& q, int chunk, int32_t max_iter, bool tile, bool transposed) {
 
 int solve_bicgstab(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, rp_solve_info& info,
                    hipStream_t s, bool ordered) {
-    RP_TRY(check_solvable(p, s, false));
+    RP_TRY(check_solvable(p, s, false, ordered));
     const int64_t n = p->n_rows;
     if (!p->d_bi_work) RP_HIP_TRY(hipMalloc(&p->d_bi_work, sizeof(double) * 5 * (size_t)n));
     // A^T x = b: same pattern and diagonal, transposed values (the solve-order

@@ -488,7 +488,7 @@ template int resident_block<double>(rp_plan*, int*);
 template int resident_block<float>(rp_plan*, int*);
 
 // The iterations k0 .. min(k_end, budget) by the resident loop, enqueued, on a
-// plan that fits it (resident_block > 0).  The abort word goes to h_flags[2],
+// plan that fits it (resident_block > 0).  The abort word goes to h_flags[LOOP_ABORT],
 // to be looked at once the stream has passed.
 template <typename T>
 int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
@@ -508,7 +508,7 @@ int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int3
     void* args[] = {&n, &ng, (void*)&row_ptr, (void*)&col, (void*)&val, (void*)&dinv, &x, &r, &pv, &st, &k0, &k_end,
                     &slots, &zs, &bar};
     RP_HIP_TRY(hipLaunchCooperativeKernel(resident_kernel<T>(bt), dim3((n + bt - 1) / bt), dim3(bt), args, 0, s));
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + 2, p->d_loop_bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, p->d_loop_bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return RP_OK;
 }
 

@@ -634,7 +634,7 @@ int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
 }
 
 // The iterations k0 .. min(k_end, budget) by the tiled loop, enqueued, on a
-// plan that fits it.  The abort word goes to h_flags[2].
+// plan that fits it.  The abort word goes to h_flags[LOOP_ABORT].
 template <typename T>
 int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0,
                    int32_t k_end, hipStream_t s) {
@@ -668,7 +668,7 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
         hipLaunchKernelGGL(from_positions<T>, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.inv, tx, x, r, pv);
         RP_HIP_TRY(hipGetLastError());
     }
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + 2, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return RP_OK;
 }
 

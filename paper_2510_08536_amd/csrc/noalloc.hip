@@ -90,8 +90,7 @@ extern "C" int rp_update_values_noalloc(rp_plan* p, const double* const* diag, c
     RP_HIP_TRY(hipMemcpyAsync(ptr, table, sizeof(const double*) * 4 * (size_t)p->alpha, hipMemcpyHostToDevice, s));
     RP_TRY(launch_clear_flags(p->d_flags, s));
     RP_TRY(launch_update_gather(p, reinterpret_cast<const double* const*>(ptr), lower != nullptr, p->d_flags, s));
-    p->has_values = true;
-    p->values_version += 1;
+    note_update(p);
     p->last_stream = s;
     return RP_OK;
 }

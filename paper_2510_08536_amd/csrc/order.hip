@@ -190,6 +190,7 @@ int solve_in_order(rp_plan* p, const double* b, double* x, const rp_solve_opts& 
                    hipStream_t s) {
     const int32_t n = (int32_t)p->n_rows;
     const int g = vec_grid(n);
+    RP_TRY(read_flags(p, s));
     if (p->has_values && p->ro_version != p->values_version) {
         hipLaunchKernelGGL(order_values, dim3(vec_grid(std::max<int64_t>(p->nnz, n))), dim3(VEC_BLOCK), 0, s,
                            p->nnz, n, p->d_ro_sig, p->d_ro_perm, p->d_val64, p->d_val32, p->d_dinv64,

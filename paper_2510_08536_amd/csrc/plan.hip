@@ -545,8 +545,8 @@ int plan_build(rp_plan* p, const rp_rank_desc* share) {
     tmp.ptrs.push_back(d_if_ncell);
     if ((rc = upload(&d_off_all, p->off_all.data(), p->off_all.size()))) return rc;
     tmp.ptrs.push_back(d_off_all);
-    RP_HIP_TRY(hipMalloc(&p->d_flags, sizeof(uint32_t) * 2));
-    RP_HIP_TRY(hipMemset(p->d_flags, 0, sizeof(uint32_t) * 2));
+    RP_HIP_TRY(hipMalloc(&p->d_flags, sizeof(uint32_t) * N_FLAGS));
+    RP_HIP_TRY(hipMemset(p->d_flags, 0, sizeof(uint32_t) * N_FLAGS));
     owner.clear(); owner.shrink_to_fit();
     nbr.clear(); nbr.shrink_to_fit();
 

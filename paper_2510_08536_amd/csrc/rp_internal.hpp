@@ -44,6 +44,9 @@ enum : uint32_t {
 };
 // plan->d_flags[1]: set when the last update produced a non-symmetric matrix
 // (upper != lower, or an interface value != its partner's)
+// plan->d_flags[2]: updates that have run (read_flags)
+constexpr int N_FLAGS = 3;
+constexpr int LOOP_ABORT = N_FLAGS;   // word of plan->h_flags: abort word of a one-launch loop
 
 // ---------------------------------------------------------------------------
 // CG state kept on the device; S is the scalar type of the iteration.
@@ -231,6 +234,8 @@ struct rp_plan {
     float* d_dinv32 = nullptr;       // [n_rows]
     bool has_values = false;
     int64_t values_version = 0;      // bumped by every update
+    uint32_t updates_enqueued = 0;   // updates the host has enqueued, and by how many more
+    uint32_t updates_replayed = 0;   // the device's count of those that ran differs (read_flags)
     double* d_valT = nullptr;        // [nnz + SPMV_PAD] values of A^T (first transposed solve)
     int64_t valT_version = -1;       // values_version d_valT was built from
     uint32_t* d_tflag = nullptr;     // set when an entry has no transposed partner
@@ -253,8 +258,8 @@ struct rp_plan {
     rp::BiState* d_bi_st = nullptr;          // BiCGStab state and its pinned mirror
     rp::BiState* h_bi_st = nullptr;
     double* d_bi_work = nullptr;             // [5 n_rows] BiCGStab vectors rh, y, s, z, t (first use)
-    uint32_t* d_flags = nullptr;     // [2] error bits, asymmetry flag
-    uint32_t* h_flags = nullptr;     // pinned mirror; [2]: abort word of the resident CG loop
+    uint32_t* d_flags = nullptr;     // [N_FLAGS] error bits, asymmetry flag, updates run
+    uint32_t* h_flags = nullptr;     // pinned mirror, and LOOP_ABORT
 
     // offset-coded SpMV index (see spmv.hpp), built with the pattern
     int32_t* d_goi_k = nullptr;      // [groups] offsets per group, 0 = CSR group
@@ -400,7 +405,18 @@ int launch_symmetry_check(rp_plan* p, const double* src, bool lower_given, hipSt
 // device array); error bits go to flags[2]
 int launch_update_gather(rp_plan* p, const double* const* table, bool lower_given, uint32_t* flags,
                          hipStream_t s);
+// the start of an update: error bits cleared, the update counted
 int launch_clear_flags(uint32_t* flags, hipStream_t s);
+// the host's part of an enqueued update
+inline void note_update(rp_plan* p) {
+    p->has_values = true;
+    p->values_version += 1;
+    p->updates_enqueued += 1;
+}
+// h_flags as of here on the stream (synchronises), and values_version past any
+// update that ran without the host enqueueing it: one captured in a graph runs
+// again at every replay
+int read_flags(rp_plan* p, hipStream_t s);
 // spmv.hip
 int launch_spmv64(rp_plan* p, const double* x, double* y, hipStream_t s);
 int launch_spmv32(rp_plan* p, const float* x, float* y, hipStream_t s);

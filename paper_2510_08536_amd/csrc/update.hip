@@ -223,6 +223,7 @@ symmetry_gather_kernel(int32_t n_faces, int32_t n_iface, int32_t alpha, bool che
 
 __global__ void clear_flags(uint32_t* flags) {
     if (threadIdx.x < 2) flags[threadIdx.x] = 0u;
+    if (threadIdx.x == 2) flags[2] += 1u;
 }
 
 int grid_for(int64_t n, int block = 256, int cap = 8192) {
@@ -287,6 +288,17 @@ int build_transpose(rp_plan* p, hipStream_t s) {
 int launch_clear_flags(uint32_t* flags, hipStream_t s) {
     hipLaunchKernelGGL(clear_flags, dim3(1), dim3(64), 0, s, flags);
     RP_HIP_TRY(hipGetLastError());
+    return RP_OK;
+}
+
+int read_flags(rp_plan* p, hipStream_t s) {
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags, p->d_flags, N_FLAGS * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    RP_HIP_TRY(hipStreamSynchronize(s));
+    const uint32_t replayed = p->h_flags[2] - p->updates_enqueued;
+    if (replayed != p->updates_replayed) {
+        p->updates_replayed = replayed;
+        p->values_version += 1;
+    }
     return RP_OK;
 }
 
