@@ -488,6 +488,12 @@ int rp_plan_amg_apply(rp_plan* plan, const double* r, double* z, void* stream);
  * (one partial sum per block).  RP_ERR_ARG outside 0..16384. */
 int rp_plan_set_vec_grid(rp_plan* plan, int32_t blocks);
 
+/* Faults of the one-launch loops (a diagnostic knob): bit k of allocs makes the
+ * k-th allocation from here that such a loop asks for fail, as without memory
+ * (0: none).  A solve then takes launched kernels, as it does where its plan
+ * does not fit the loops. */
+int rp_plan_set_loop_faults(rp_plan* plan, uint64_t allocs);
+
 /* ---- lifetime / diagnostics --------------------------------------------- */
 /* Wait for the plan's pending work; reports a pending RP_ERR_VALUE. */
 int rp_sync(rp_plan* plan);

@@ -425,8 +425,8 @@ int bi_tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
     int per_cu = 0;
     RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, bi_kernel(nr, tl.halo_most), TT, 0));
     *yes = per_cu > 0 && tile_room<double>(p) &&
-           got(&tl.bi_slots, sizeof(uint64_t) * RES_SETS * (BI_SUMS * SPMV_BLOCK + 2 * (size_t)p->n_rows)) &&
-           got(&tl.bar, sizeof(uint32_t));
+           got(p, &tl.bi_slots, sizeof(uint64_t) * RES_SETS * (BI_SUMS * SPMV_BLOCK + 2 * (size_t)p->n_rows)) &&
+           got(p, &tl.bar, sizeof(uint32_t));
     return RP_OK;
 }
 

@@ -501,6 +501,13 @@ int rp_plan_set_vec_grid(rp_plan* p, int32_t blocks) {
     return RP_OK;
 }
 
+int rp_plan_set_loop_faults(rp_plan* p, uint64_t allocs) {
+    clear_error();
+    RP_CHECK(p != nullptr, RP_ERR_ARG, "plan is NULL");
+    p->alloc_faults = allocs;
+    return RP_OK;
+}
+
 int rp_plan_get_values(rp_plan* p, double* val64, float* val32, double* dinv64, float* dinv32) {
     clear_error();
     RP_CHECK(p != nullptr, RP_ERR_ARG, "plan is NULL");

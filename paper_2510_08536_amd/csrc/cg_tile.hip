@@ -493,6 +493,7 @@ int tile_free(rp_plan* p) {
         if (*q) RP_HIP_TRY(hipFree(*q));
         *q = nullptr;
     }
+    tl.R = tl.G = tl.halo_most = 0;
     return RP_OK;
 }
 
@@ -513,8 +514,8 @@ int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t 
     const int32_t G = (int32_t)first.size() - 1, R = nr * TT;
     RP_TRY(tile_free(p));
     *fits = false;
-    if (!got(&tl.first, sizeof(int32_t) * first.size()) || !got(&tl.halo, sizeof(int32_t) * (size_t)G * HALO_MAX) ||
-        !got(&tl.n_halo, sizeof(int32_t) * (size_t)G) || !got(&tl.places, sizeof(Places) * (size_t)G * R)) {
+    if (!got(p, &tl.first, sizeof(int32_t) * first.size()) || !got(p, &tl.halo, sizeof(int32_t) * (size_t)G * HALO_MAX) ||
+        !got(p, &tl.n_halo, sizeof(int32_t) * (size_t)G) || !got(p, &tl.places, sizeof(Places) * (size_t)G * R)) {
         *memory = false;
         return RP_OK;
     }
@@ -537,7 +538,8 @@ int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t 
 
 }  // namespace
 
-// the plan's tiles, or that it does not fit (tiles.R = 0), found out once
+// the plan's tiles, or that it does not fit or has no memory for them
+// (tiles.R = 0), found out once
 int tile_setup(rp_plan* p, hipStream_t s) {
     auto& tl = p->tiles;
     if (tl.asked) return RP_OK;
@@ -564,16 +566,18 @@ int tile_setup(rp_plan* p, hipStream_t s) {
         RP_TRY(tile_try(p, nr[1], first[1], s, &fits, &memory));
         if (!fits && memory) {
             bool ok = false;
-            memory = got(&tl.order, sizeof(int32_t) * (size_t)p->n_rows) &&
-                     got(&tl.inv, sizeof(int32_t) * (size_t)p->n_rows) &&
-                     got(&tl.vec, TILE_VECS * sizeof(double) * (size_t)p->n_rows);
+            memory = got(p, &tl.order, sizeof(int32_t) * (size_t)p->n_rows) &&
+                     got(p, &tl.inv, sizeof(int32_t) * (size_t)p->n_rows) &&
+                     got(p, &tl.vec, TILE_VECS * sizeof(double) * (size_t)p->n_rows);
             if (memory) RP_TRY(tile_order(p, first[1][1], tl.order, tl.inv, s, &ok, &memory));
             if (ok) RP_TRY(tile_try(p, nr[1], first[1], s, &fits, &memory));
             if (!fits) RP_TRY(order_free(p));
         }
     }
     if (!fits) RP_TRY(tile_free(p));
-    tl.asked = memory;   // without memory now, a later solve may find some
+    // for good, also where memory was short: the values' slices are laid out by
+    // these tables, and a search repeated by every solve costs more than it gives
+    tl.asked = true;
     return RP_OK;
 }
 
@@ -596,7 +600,7 @@ struct TileVal<float> {
 
 template <typename T>
 bool tile_room(rp_plan* p) {
-    return got(&TileVal<T>::val(p), sizeof(T) * (size_t)p->tiles.G * p->tiles.R * U);
+    return got(p, &TileVal<T>::val(p), sizeof(T) * (size_t)p->tiles.G * p->tiles.R * U);
 }
 
 // the slices of the values src: the matrix's, or (transposed) its transpose's
@@ -628,8 +632,8 @@ int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
     int per_cu = 0;
     RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tile_kernel<T>(nr), TT, 0));
     *yes = per_cu > 0 && tile_room<T>(p) &&
-           got(&tl.slots, sizeof(uint64_t) * RES_SETS * (3 * SPMV_BLOCK + (size_t)p->n_rows)) &&
-           got(&tl.bar, sizeof(uint32_t));
+           got(p, &tl.slots, sizeof(uint64_t) * RES_SETS * (3 * SPMV_BLOCK + (size_t)p->n_rows)) &&
+           got(p, &tl.bar, sizeof(uint32_t));
     return RP_OK;
 }
 

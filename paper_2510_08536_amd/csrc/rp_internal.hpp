@@ -311,7 +311,7 @@ struct rp_plan {
     // tiles of the one-launch CG and BiCGStab loops (cg_tile.hip, bi_tile.hip),
     // built by the first such solve; R = 0: the plan does not fit
     struct Tiles {
-        bool asked = false;
+        bool asked = false;            // built, or found not to fit: for good, the tables below stay
         int32_t R = 0, G = 0;          // rows per tile at most, tiles
         int32_t* first = nullptr;      // [G + 1] first row of each tile
         int32_t halo_most = 0;         // longest halo
@@ -331,6 +331,8 @@ struct rp_plan {
     int resident_block[2] = {-1, -1};  // its block size in FP64, FP32; 0: the plan does not fit it; -1: not asked yet
     uint32_t* d_loop_bar = nullptr;    // abort word and per-block barrier flags of the CG loop (cg_loop.hip)
 
+    uint64_t alloc_faults = 0;         // rp_plan_set_loop_faults: bit 0, the loops' next allocation fails
+
     rp::AmgHier* amg = nullptr;        // multigrid hierarchy (RP_PRECOND_AMG), built on first use
     rp::AmgHier* amg_ro = nullptr;     // the same on the solve-order copy
 
@@ -344,6 +346,13 @@ struct rp_plan {
 };
 
 namespace rp {
+
+// an allocation of the one-launch loops
+inline hipError_t loop_malloc(rp_plan* p, void** q, size_t bytes) {
+    const bool fault = p->alloc_faults & 1u;
+    p->alloc_faults >>= 1;
+    return fault ? hipErrorOutOfMemory : hipMalloc(q, bytes);
+}
 
 // launch-shape helpers
 // SpMV-shaped kernels: at most SPMV_GRID_MAX blocks (a multiple of N_XCD),

@@ -52,8 +52,8 @@ __device__ __forceinline__ T tile_sum(const T* red) {
 // Memory the loop keeps with the plan, if there is some: without it a solve
 // takes three launches, as a plan that does not fit does.
 template <typename V>
-inline bool got(V** q, size_t bytes) {
-    if (*q || hipMalloc((void**)q, std::max<size_t>(bytes, 1)) == hipSuccess) return true;
+inline bool got(rp_plan* p, V** q, size_t bytes) {
+    if (*q || loop_malloc(p, (void**)q, std::max<size_t>(bytes, 1)) == hipSuccess) return true;
     *q = nullptr;
     (void)hipGetLastError();
     return false;

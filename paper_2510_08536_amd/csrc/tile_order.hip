@@ -225,8 +225,8 @@ struct Free {
 };
 
 template <typename V>
-bool temp(Free& f, V** q, int64_t count) {
-    if (hipMalloc((void**)q, sizeof(V) * (size_t)std::max<int64_t>(count, 1)) != hipSuccess) {
+bool temp(rp_plan* p, Free& f, V** q, int64_t count) {
+    if (loop_malloc(p, (void**)q, sizeof(V) * (size_t)std::max<int64_t>(count, 1)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
@@ -251,8 +251,8 @@ int tile_order(rp_plan* p, int64_t cap, int32_t* order, int32_t* inv, hipStream_
     int32_t *la = nullptr, *lb = nullptr, *start = nullptr;
     uint32_t *size = nullptr, *used = nullptr, *flag = nullptr;
     unsigned long long* table = nullptr;
-    if (!temp(f, &la, n) || !temp(f, &lb, n) || !temp(f, &start, S) || !temp(f, &size, 2 * (int64_t)S + 2) ||
-        !temp(f, &table, slots)) {
+    if (!temp(p, f, &la, n) || !temp(p, f, &lb, n) || !temp(p, f, &start, S) || !temp(p, f, &size, 2 * (int64_t)S + 2) ||
+        !temp(p, f, &table, slots)) {
         *memory = false;
         return RP_OK;
     }

@@ -48,8 +48,8 @@ EXPORTED = ["rp_plan_create", "rp_plan_destroy", "rp_plan_sizes", "rp_plan_get_c
             "rp_update_values", "rp_update_values_slots", "rp_spmv", "rp_solve", "rp_solve_opts_default",
             "rp_value_grad", "rp_sync", "rp_last_error", "rp_plan_set_timing", "rp_plan_kernel_stats",
             "rp_plan_set_solve_order", "rp_plan_solve_order", "rp_rcm_order", "rp_plan_device_ptrs",
-            "rp_plan_set_vec_grid", "rp_update_values_noalloc", "rp_plan_block_jacobi", "rp_plan_export_recv",
-            "rp_recv_attach", "rp_recv_write", "rp_recv_detach", "rp_plan_amg_setup", "rp_plan_amg_levels",
+            "rp_plan_set_vec_grid", "rp_plan_set_loop_faults", "rp_update_values_noalloc", "rp_plan_block_jacobi",
+            "rp_plan_export_recv", "rp_recv_attach", "rp_recv_write", "rp_recv_detach", "rp_plan_amg_setup", "rp_plan_amg_levels",
             "rp_plan_amg_level", "rp_plan_amg_coarse_inverse", "rp_plan_amg_apply"]
 RP_PRECOND_JACOBI, RP_PRECOND_BLOCK_JACOBI, RP_PRECOND_AMG = 0, 1, 2
 RP_BJ_MAX_BLOCK = 8
@@ -139,6 +139,7 @@ _sig = {
     "rp_rcm_order": (C.c_int, [C.c_int32, _P, _P, _P]),
     "rp_plan_device_ptrs": (C.c_int, [_P, C.POINTER(rp_device_ptrs)]),
     "rp_plan_set_vec_grid": (C.c_int, [_P, C.c_int32]),
+    "rp_plan_set_loop_faults": (C.c_int, [_P, C.c_uint64]),
     "rp_plan_block_jacobi": (C.c_int, [_P, C.c_int32, _i64p, _P, _P, _P]),
     "rp_plan_export_recv": (C.c_int, [_P, C.POINTER(rp_ipc_handle), _i64p]),
     "rp_recv_attach": (C.c_int, [C.POINTER(rp_ipc_handle), C.POINTER(C.c_void_p)]),
@@ -401,6 +402,10 @@ class Plan:
     def set_vec_grid(self, blocks: int):
         """Fix the solvers' elementwise-kernel grid (0 = default sizing)."""
         _check(rp_plan_set_vec_grid(self._h, int(blocks)), "rp_plan_set_vec_grid")
+
+    def set_loop_faults(self, allocs: int = 0):
+        """Make allocations of the one-launch loops fail (bit k: the k-th from here)."""
+        _check(rp_plan_set_loop_faults(self._h, int(allocs)), "rp_plan_set_loop_faults")
 
     def get_values(self):
         v64 = np.zeros(max(self.n_slots, 1), np.float64)
