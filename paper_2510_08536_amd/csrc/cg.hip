@@ -56,6 +56,7 @@ int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int3
                        const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s);
 template <typename T>
 int resident_block(rp_plan* p, int* out);
+bool resident_room(rp_plan* p);
 // cg_tile.hip: the same on medium systems in fused order
 template <typename T>
 int tile_fits(rp_plan* p, hipStream_t s, bool* yes);
@@ -1085,7 +1086,7 @@ int choose_loop(const Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
     if (c.n <= RP_LOOP_TWO_MAX_ROWS) {
         int bt = 0;
         RP_TRY(resident_block<T>(c.plan, &bt));
-        if (bt > 0) *loop = Loop::RESIDENT;
+        if (bt > 0 && resident_room(c.plan)) *loop = Loop::RESIDENT;
     } else if (c.ix.row_ptr == c.plan->d_row_ptr) {   // the tiles are the fused order's
         bool fits = false;
         RP_TRY(tile_fits<T>(c.plan, c.s, &fits));

@@ -487,8 +487,17 @@ int resident_block(rp_plan* p, int* out) {
 template int resident_block<double>(rp_plan*, int*);
 template int resident_block<float>(rp_plan*, int*);
 
+// words the loop exchanges its values through, of either precision
+inline int64_t resident_slots(int64_t n) { return (int64_t)RES_SETS * (3 * RES_GROUPS + n); }
+
+// whether there is memory for them
+bool resident_room(rp_plan* p) {
+    return got(p, &p->d_slots, resident_slots(p->n_rows) * sizeof(uint64_t)) &&
+           got(p, &p->d_loop_bar, BAR_WORDS * sizeof(uint32_t));
+}
+
 // The iterations k0 .. min(k_end, budget) by the resident loop, enqueued, on a
-// plan that fits it (resident_block > 0).  The abort word goes to h_flags[LOOP_ABORT],
+// plan that fits it (resident_block > 0) and has room for it (resident_room).  The abort word goes to h_flags[LOOP_ABORT],
 // to be looked at once the stream has passed.
 template <typename T>
 int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
@@ -497,9 +506,7 @@ int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int3
     int32_t ng = (n + SPMV_BLOCK - 1) / SPMV_BLOCK;
     // slots of either precision: the sums, then z
     typedef typename Word<T>::type W;
-    const int64_t len = (int64_t)RES_SETS * (3 * RES_GROUPS + n);
-    if (!p->d_slots) RP_HIP_TRY(hipMalloc(&p->d_slots, len * sizeof(uint64_t)));
-    if (!p->d_loop_bar) RP_HIP_TRY(hipMalloc(&p->d_loop_bar, BAR_WORDS * sizeof(uint32_t)));
+    const int64_t len = resident_slots(n);
     W* slots = (W*)p->d_slots;
     W* zs = slots + RES_SETS * 3 * RES_GROUPS;
     uint32_t* bar = p->d_loop_bar;

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -352,6 +353,15 @@ inline hipError_t loop_malloc(rp_plan* p, void** q, size_t bytes) {
     const bool fault = p->alloc_faults & 1u;
     p->alloc_faults >>= 1;
     return fault ? hipErrorOutOfMemory : hipMalloc(q, bytes);
+}
+// Memory a one-launch loop keeps with the plan, if there is some: without it a
+// solve takes launched kernels, as a plan that does not fit does.
+template <typename V>
+inline bool got(rp_plan* p, V** q, size_t bytes) {
+    if (*q || loop_malloc(p, (void**)q, std::max<size_t>(bytes, 1)) == hipSuccess) return true;
+    *q = nullptr;
+    (void)hipGetLastError();
+    return false;
 }
 
 // launch-shape helpers

@@ -49,16 +49,6 @@ __device__ __forceinline__ T tile_sum(const T* red) {
     return s;
 }
 
-// Memory the loop keeps with the plan, if there is some: without it a solve
-// takes three launches, as a plan that does not fit does.
-template <typename V>
-inline bool got(rp_plan* p, V** q, size_t bytes) {
-    if (*q || loop_malloc(p, (void**)q, std::max<size_t>(bytes, 1)) == hipSuccess) return true;
-    *q = nullptr;
-    (void)hipGetLastError();
-    return false;
-}
-
 // cg_tile.hip
 int tile_setup(rp_plan* p, hipStream_t s);
 template <typename T>

@@ -53,3 +53,18 @@ def test_any_allocation_may_fail(mesh):
                 assert float((x - x3).norm()) <= bar * float(x3.norm()), (mesh, hex(faults), kw)
             assert torch.equal(first, again), (mesh, hex(faults), kw)
         plan.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_small_systems_without_memory(precision):
+    torch = torch_mod()
+    w = synth.small((20, 19, 18), ("blocks", 2, 1, 1), kappa=(1e-1, 1.0), seed=43)
+    plan = make_plan(w)
+    update(plan, share_values(w))
+    b = dev_tensor(w.rhs())
+    ref = plan.solve(b, tol=1e-9, precision=precision, fused_loop=RP_LOOP_THREE)
+    for faults in (1, 2, ALL, 0):
+        plan.set_loop_faults(faults)
+        got = plan.solve(b, tol=1e-9, precision=precision)
+        assert torch.equal(got[0], ref[0]) and got[1] == ref[1], hex(faults)
+    plan.close()
