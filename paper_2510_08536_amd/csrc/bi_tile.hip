@@ -143,7 +143,9 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
     __shared__ double P[lds_words<double>()];
     __shared__ double red[3][TT / 64];
     __shared__ double all[3][SPMV_BLOCK / 64];
-    __shared__ int32_t bad;
+    // a wait was given up; one word for every other check, so that none is set
+    // again before every wave has read it
+    __shared__ int32_t bad[2];
     if (st->done != CG_RUNNING) return;
     const int32_t t = threadIdx.x, b = blockIdx.x, G = gridDim.x;
     const int32_t base = first[b], rows = first[b + 1] - base, H = n_halo[b];
@@ -191,7 +193,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
             }
         }
     }
-    if (t == 0) bad = 0;
+    if (t < 2) bad[t] = 0;
     __syncthreads();
     const int32_t k_stop = k_end;
     int32_t k = k0, stop = CG_RUNNING;
@@ -217,7 +219,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         uint64_t w[HN];
         if (DIRECT) {
             halo_load<HN>(v_k, hid, w);
-            if (!halo_wait<HN>(v_k, hid, w, bar)) bad = 1;
+            if (!halo_wait<HN>(v_k, hid, w, bar)) bad[0] = 1;
         }
 #pragma unroll
         for (int h = 0; h < HN; ++h) {
@@ -243,9 +245,9 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
         if (t == 0) agent_store(s_v + b, W::of(tile_sum(red[0])));
         if (!DIRECT) halo_load<HN>(v_k, hid, w);
-        if (t < SPMV_BLOCK && !gather_slots<double, 1>(s_v, G, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<double, 1>(s_v, G, t, bar, all)) bad[0] = 1;
         __syncthreads();
-        if (bad) {
+        if (bad[0]) {
             given_up = true;
             break;
         }
@@ -280,7 +282,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
             s1 += rv[j] * rv[j];
         }
         if (DIRECT) halo_load<HN>(t_k, hid, w);
-        if (!halo_wait<HN>(DIRECT ? t_k : v_k, hid, w, bar)) bad = 1;
+        if (!halo_wait<HN>(DIRECT ? t_k : v_k, hid, w, bar)) bad[1] = 1;
 #pragma unroll
         for (int h = 0; h < HN; ++h) {
             if (DIRECT) {
@@ -292,7 +294,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
             }
         }
         __syncthreads();
-        if (bad) {
+        if (bad[1]) {
             given_up = true;
             break;
         }
@@ -314,9 +316,9 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
         if (t < 3) agent_store(s_t + 3 * b + t, W::of(tile_sum(red[t])));
         if (!DIRECT) halo_load<HN>(t_k, hid, w);
-        if (t < SPMV_BLOCK && !gather_slots<double, 3>(s_t, G, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<double, 3>(s_t, G, t, bar, all)) bad[0] = 1;
         __syncthreads();
-        if (bad) {
+        if (bad[0]) {
             given_up = true;
             break;
         }
@@ -353,14 +355,14 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
         if (t < 2) agent_store(s_r + 2 * b + t, W::of(tile_sum(red[t])));
         if (!DIRECT) {
-            if (!halo_wait<HN>(t_k, hid, w, bar)) bad = 1;
+            if (!halo_wait<HN>(t_k, hid, w, bar)) bad[1] = 1;
 #pragma unroll
             for (int h = 0; h < HN; ++h)
                 hr[DIRECT ? 0 : h] = hr[DIRECT ? 0 : h] - omega * W::value(w[h]);
         }
-        if (t < SPMV_BLOCK && !gather_slots<double, 2>(s_r, G, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<double, 2>(s_r, G, t, bar, all)) bad[1] = 1;
         __syncthreads();
-        if (bad) {
+        if (bad[1]) {
             given_up = true;
             break;
         }
