@@ -166,7 +166,12 @@ typedef struct rp_solve_opts {
                                 Kernel timing, graph replay, block-Jacobi and the
                                 multigrid always take three launches per iteration, as
                                 does RP_LOOP_COOPERATIVE where the device cannot launch
-                                the grid cooperatively.  RP_BICGSTAB in fused order, with at
+                                the grid cooperatively.  RP_LOOP_AUTO's loops need the whole
+                                grid on the device at once; where it finds no place in some
+                                tenths of a second (other streams', other processes' work),
+                                the solve goes on with launched kernels, and so do the
+                                plan's next 1, 2, 4, ... 1024 solves, a longer run each
+                                time the loop gives up again.  RP_BICGSTAB in fused order, with at
                                 most 7 entries a row and 1.3 million rows, runs all
                                 iterations in one launch by RP_LOOP_AUTO (equal up to the
                                 rounding of the dot products), else in five launches each. */
@@ -488,11 +493,13 @@ int rp_plan_amg_apply(rp_plan* plan, const double* r, double* z, void* stream);
  * (one partial sum per block).  RP_ERR_ARG outside 0..16384. */
 int rp_plan_set_vec_grid(rp_plan* plan, int32_t blocks);
 
-/* Faults of the one-launch loops (a diagnostic knob): bit k of allocs makes the
+/* Faults of the one-launch loops (a diagnostic knob).  Bit k of allocs makes the
  * k-th allocation from here that such a loop asks for fail, as without memory
- * (0: none).  A solve then takes launched kernels, as it does where its plan
- * does not fit the loops. */
-int rp_plan_set_loop_faults(rp_plan* plan, uint64_t allocs);
+ * (0: none).  waits bounds the polls of one wait for another workgroup's values
+ * (0: the default, some tenths of a second): past it a loop gives up, as it
+ * does behind other work that holds the device.  A solve then takes launched
+ * kernels: from the start where memory is missing, else from the x at hand. */
+int rp_plan_set_loop_faults(rp_plan* plan, uint64_t allocs, uint32_t waits);
 
 /* ---- lifetime / diagnostics --------------------------------------------- */
 /* Wait for the plan's pending work; reports a pending RP_ERR_VALUE. */

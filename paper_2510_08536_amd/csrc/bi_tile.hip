@@ -112,13 +112,13 @@ __device__ __forceinline__ void halo_load(const uint64_t* at, const int32_t* hid
     for (int h = 0; h < N; ++h) w[h] = hid[h] >= 0 ? agent_load_at(at, (uint32_t)hid[h]) : 0;
 }
 template <int N>
-__device__ __forceinline__ bool halo_wait(const uint64_t* at, const int32_t* hid, uint64_t* w, const uint32_t* bar) {
+__device__ __forceinline__ bool halo_wait(const uint64_t* at, const int32_t* hid, uint64_t* w, const Wait& wait) {
     for (uint32_t spins = 0;;) {
         bool empty = false;
 #pragma unroll
         for (int h = 0; h < N; ++h) empty |= w[h] == Word<double>::EMPTY;
         if (!empty) return true;
-        if (wait_over(spins, bar)) return false;
+        if (wait_over(spins, wait)) return false;
 #pragma unroll
         for (int h = 0; h < N; ++h)
             if (w[h] == Word<double>::EMPTY) w[h] = agent_load_at(at, (uint32_t)hid[h]);
@@ -131,7 +131,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         const int32_t* __restrict__ n_halo, const Places* __restrict__ places, const double* __restrict__ val,
         const double* __restrict__ dinv, double* __restrict__ x, double* __restrict__ r,
         const double* __restrict__ rh, double* __restrict__ p, double* __restrict__ v, BiState* st, int32_t k0,
-        int32_t k_end, uint64_t* slots, uint64_t* vs, uint64_t* ts, uint32_t* bar) {
+        int32_t k_end, uint64_t* slots, uint64_t* vs, uint64_t* ts, Wait wait) {
 #pragma clang fp contract(off)
     typedef Word<double> W;
     constexpr int R = NR * TT;
@@ -219,7 +219,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         uint64_t w[HN];
         if (DIRECT) {
             halo_load<HN>(v_k, hid, w);
-            if (!halo_wait<HN>(v_k, hid, w, bar)) bad[0] = 1;
+            if (!halo_wait<HN>(v_k, hid, w, wait)) bad[0] = 1;
         }
 #pragma unroll
         for (int h = 0; h < HN; ++h) {
@@ -245,7 +245,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
         if (t == 0) agent_store(s_v + b, W::of(tile_sum(red[0])));
         if (!DIRECT) halo_load<HN>(v_k, hid, w);
-        if (t < SPMV_BLOCK && !gather_slots<double, 1>(s_v, G, t, bar, all)) bad[0] = 1;
+        if (t < SPMV_BLOCK && !gather_slots<double, 1>(s_v, G, t, wait, all)) bad[0] = 1;
         __syncthreads();
         if (bad[0]) {
             given_up = true;
@@ -282,7 +282,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
             s1 += rv[j] * rv[j];
         }
         if (DIRECT) halo_load<HN>(t_k, hid, w);
-        if (!halo_wait<HN>(DIRECT ? t_k : v_k, hid, w, bar)) bad[1] = 1;
+        if (!halo_wait<HN>(DIRECT ? t_k : v_k, hid, w, wait)) bad[1] = 1;
 #pragma unroll
         for (int h = 0; h < HN; ++h) {
             if (DIRECT) {
@@ -316,7 +316,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
         if (t < 3) agent_store(s_t + 3 * b + t, W::of(tile_sum(red[t])));
         if (!DIRECT) halo_load<HN>(t_k, hid, w);
-        if (t < SPMV_BLOCK && !gather_slots<double, 3>(s_t, G, t, bar, all)) bad[0] = 1;
+        if (t < SPMV_BLOCK && !gather_slots<double, 3>(s_t, G, t, wait, all)) bad[0] = 1;
         __syncthreads();
         if (bad[0]) {
             given_up = true;
@@ -355,12 +355,12 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
         if (t < 2) agent_store(s_r + 2 * b + t, W::of(tile_sum(red[t])));
         if (!DIRECT) {
-            if (!halo_wait<HN>(t_k, hid, w, bar)) bad[1] = 1;
+            if (!halo_wait<HN>(t_k, hid, w, wait)) bad[1] = 1;
 #pragma unroll
             for (int h = 0; h < HN; ++h)
                 hr[DIRECT ? 0 : h] = hr[DIRECT ? 0 : h] - omega * W::value(w[h]);
         }
-        if (t < SPMV_BLOCK && !gather_slots<double, 2>(s_r, G, t, bar, all)) bad[1] = 1;
+        if (t < SPMV_BLOCK && !gather_slots<double, 2>(s_r, G, t, wait, all)) bad[1] = 1;
         __syncthreads();
         if (bad[1]) {
             given_up = true;
@@ -371,7 +371,7 @@ bi_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         rr = sum_red(all[1]);
     }
     if (given_up) {
-        if (t == 0) atomicOr(bar, 1u);
+        if (t == 0) atomicOr(wait.bar, 1u);
         return;
     }
 #pragma unroll
@@ -432,8 +432,8 @@ int bi_tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
     return RP_OK;
 }
 
-// The iterations k0 .. k_end, enqueued, on a plan that fits.  The abort word
-// goes to h_flags[LOOP_ABORT].
+// The iterations k0 .. k_end, enqueued, on a plan that fits.  See
+// launch_loop.
 int launch_bi_tile(rp_plan* p, const double* src, bool transposed, const double* dinv, double* x, double* r,
                    const double* rh, double* pv, double* v, BiState* st, int32_t k0, int32_t k_end, hipStream_t s) {
     auto& tl = p->tiles;
@@ -462,15 +462,15 @@ int launch_bi_tile(rp_plan* p, const double* src, bool transposed, const double*
     }
     const int32_t *first = tl.first, *halo = tl.halo, *n_halo = tl.n_halo;
     const Places* places = (const Places*)tl.places;
+    Wait wait{bar, wait_spins(p)};
     void* args[] = {&n,   (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&val, (void*)&td,
                     &tx,  &tr,           (void*)&trh,  &tp,            &tv,            &st,         &k0,
-                    &k_end, &slots,      &vs,          &ts,            &bar};
-    RP_HIP_TRY(hipLaunchCooperativeKernel(bi_kernel(tl.R / TT, tl.halo_most), dim3(tl.G), dim3(TT), args, 0, s));
+                    &k_end, &slots,      &vs,          &ts,            &wait};
+    RP_TRY(launch_loop(p, bi_kernel(tl.R / TT, tl.halo_most), tl.G, TT, args, bar, s));
     if (tl.order) {
         hipLaunchKernelGGL(bi_from_positions, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.inv, tx, x, r, pv, v);
         RP_HIP_TRY(hipGetLastError());
     }
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return RP_OK;
 }
 

@@ -501,10 +501,12 @@ int rp_plan_set_vec_grid(rp_plan* p, int32_t blocks) {
     return RP_OK;
 }
 
-int rp_plan_set_loop_faults(rp_plan* p, uint64_t allocs) {
+int rp_plan_set_loop_faults(rp_plan* p, uint64_t allocs, uint32_t waits) {
     clear_error();
     RP_CHECK(p != nullptr, RP_ERR_ARG, "plan is NULL");
     p->alloc_faults = allocs;
+    p->loop_spins = waits;
+    p->loop_rest = p->loop_given_up = 0;
     return RP_OK;
 }
 

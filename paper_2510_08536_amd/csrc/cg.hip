@@ -49,8 +49,7 @@ namespace rp {
 template <typename T>
 int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const T* dinv, T* x, T* r, T* pv, T* q,
                    CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s, bool* ran);
-// the same by the resident loop, on a plan with resident_block > 0; enqueued,
-// the abort word to h_flags[LOOP_ABORT]
+// the same by the resident loop, on a plan with resident_block > 0; enqueued (launch_loop)
 template <typename T>
 int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
                        const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s);
@@ -1092,6 +1091,7 @@ int choose_loop(const Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
         RP_TRY(tile_fits<T>(c.plan, c.s, &fits));
         if (fits) *loop = Loop::TILE;
     }
+    if (*loop != Loop::LAUNCHES && !loop_allowed(c.plan)) *loop = Loop::LAUNCHES;
     return RP_OK;
 }
 
@@ -1108,26 +1108,29 @@ int start_ahead(Cg<T>& c, Loop loop, int32_t k, int32_t max_iter) {
 // enqueue chunks of up to `chunk` iterations (never past max_iter) until the
 // state leaves CG_RUNNING or the budget is spent.  graph: each chunk is one
 // replay of a captured graph of `chunk` iterations (kernels past max_iter do
-// nothing); per-kernel timing always launches eagerly.
+// nothing); per-kernel timing always launches eagerly.  A one-launch loop that
+// gave up, or could not be launched, leaves *loop = LAUNCHES: the rows of some
+// workgroups may then hold a later iterate than others', so the caller starts
+// again from an x of its own at iteration c.h->iter.
 template <typename T>
-int iterate(Cg<T>& c, const rp_solve_opts& o, Loop loop) {
+int iterate(Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
     const bool timed = c.plan->timing.enabled, graph = o.graph != 0;
     const int chunk = std::max(1, o.check_every);
     const int32_t max_iter = o.max_iter, fused_loop = o.fused_loop;
-    if (loop != Loop::LAUNCHES) {
+    if (*loop != Loop::LAUNCHES) {
         // a launch's length is bounded: other work on the device waits for it
         constexpr int64_t LOOP_ITERS = 1 << 16;
         while (c.h->done == CG_RUNNING && c.h->iter < max_iter) {
             const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)c.h->iter + LOOP_ITERS, max_iter);
-            if (loop == Loop::RESIDENT)
+            if (*loop == Loop::RESIDENT)
                 RP_TRY(launch_cg_resident<T>(c.plan, c.n, c.ix.row_ptr, c.ix.col, c.val, c.dinv, c.x, c.r, c.p, c.st,
                                              c.h->iter, k1, c.s));
             else
                 RP_TRY(launch_cg_tile<T>(c.plan, c.val, c.dinv, c.x, c.r, c.p, c.st, c.h->iter, k1, c.s));
             RP_TRY(read_state(c));
-            if (c.plan->h_flags[LOOP_ABORT]) {
-                set_error("the one-launch CG loop gave up waiting for another workgroup's values");
-                return RP_ERR_HIP;
+            if (loop_gave_up(c.plan)) {
+                *loop = Loop::LAUNCHES;
+                break;
             }
         }
         return RP_OK;
@@ -1270,7 +1273,15 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
         }
         if (c.h->iter >= o.max_iter) break;
         const int32_t it_before = c.h->iter;
-        RP_TRY(iterate(c, o, loop));
+        const Loop taken = loop;
+        RP_TRY(iterate(c, o, &loop));
+        if (loop != taken) {   // any x is a start
+            RP_TRY((launch_residual<double, false>(c, false, nullptr)));
+            RP_TRY(launch_start(c, c.h->iter, tol2, 0.0, o.max_iter));
+            RP_TRY(read_state(c));
+            fresh = true;
+            continue;
+        }
         if (c.h->iter > it_before || c.h->done == CG_RUNNING) fresh = false;
     }
     if (!fresh && c.h->done != CG_ZERO_RHS) {
@@ -1347,8 +1358,15 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
             start_inner = false;
         }
         const int32_t it_before = in.h->iter;
-        RP_TRY(iterate(in, o, loop));
+        const Loop taken = loop;
+        RP_TRY(iterate(in, o, &loop));
         total_inner = in.h->iter;
+        if (loop != taken) {   // the correction is dropped; r32, which it took for its residual, is made again
+            RP_TRY((launch_residual<double, true>(out, false, p->d_r32)));
+            start_inner = true;
+            if (total_inner >= o.max_iter) break;
+            continue;
+        }
         const int32_t d = in.h->done;
         // fold the FP32 correction into x and take the FP64 residual
         hipLaunchKernelGGL(ir_accumulate, dim3(out.g_vec), dim3(VEC_BLOCK), 0, s, out.n, x, p->d_x32);
@@ -1681,18 +1699,19 @@ int bi_true_residual(Bi& q) {
     return bi_read(q);
 }
 
-int bi_iterate(Bi& q, int chunk, int32_t max_iter, bool tile, bool transposed) {
+// *tile: by the one-launch loop; false on return if it gave up (see iterate)
+int bi_iterate(Bi& q, int chunk, int32_t max_iter, bool* tile, bool transposed) {
     Cg<double>& c = q.c;
-    if (tile) {
+    if (*tile) {
         constexpr int64_t LOOP_ITERS = 1 << 15;   // a launch's length is bounded: other work waits for it
         while (q.h->done == CG_RUNNING && q.h->iter < max_iter) {
             const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)q.h->iter + LOOP_ITERS, max_iter);
             RP_TRY(launch_bi_tile(c.plan, c.val, transposed, c.dinv, c.x, c.r, q.rh, q.p, q.v, q.st, q.h->iter, k1,
                                   c.s));
             RP_TRY(bi_read(q));
-            if (c.plan->h_flags[LOOP_ABORT]) {
-                set_error("the one-launch BiCGStab loop gave up waiting for another workgroup's values");
-                return RP_ERR_HIP;
+            if (loop_gave_up(c.plan)) {
+                *tile = false;
+                break;
             }
         }
         return RP_OK;
@@ -1744,6 +1763,7 @@ int solve_bicgstab(rp_plan* p, const double* b, double* x, const rp_solve_opts& 
     bool tile = false;
     if (o.fused_loop == RP_LOOP_AUTO && !ordered && !p->timing.enabled && p->vec_grid_override == 0)
         RP_TRY(bi_tile_fits(p, s, &tile));
+    if (tile && !loop_allowed(p)) tile = false;
     RP_TRY(bi_launch_start(q, o.x0_zero != 0, 0, tol2));
     bool fresh = true;  // rr_true belongs to the current x
     int status = RP_NOT_CONVERGED;
@@ -1776,7 +1796,13 @@ int solve_bicgstab(rp_plan* p, const double* b, double* x, const rp_solve_opts& 
             break;
         }
         if (q.h->iter >= o.max_iter) break;
-        RP_TRY(bi_iterate(q, chunk, o.max_iter, tile, o.transpose != 0));
+        const bool taken = tile;
+        RP_TRY(bi_iterate(q, chunk, o.max_iter, &tile, o.transpose != 0));
+        if (tile != taken) {   // any x is a start
+            RP_TRY(bi_launch_start(q, false, q.h->iter, tol2));
+            fresh = true;
+            continue;
+        }
         fresh = false;
     }
     if (!fresh && q.h->done != CG_ZERO_RHS) RP_TRY(bi_true_residual(q));

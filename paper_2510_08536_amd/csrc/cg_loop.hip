@@ -35,6 +35,7 @@ namespace {
 constexpr int FLAG_STRIDE = 32;            // words: one 128-byte line per block flag
 constexpr int FLAG0 = FLAG_STRIDE;         // word 0: abort word; flags from line 1
 constexpr int LOOP_GRID_MAX = 128;
+constexpr uint32_t BAR_SPINS = 1u << 22;   // polls of a barrier at most: a few seconds
 
 // all blocks of the grid; false when the wait was abandoned.  seq counts
 // the barriers of this launch (the same in every block).
@@ -198,7 +199,7 @@ cg_loop(int32_t n, SpmvIdx ix, const T* __restrict__ val, const T* __restrict__ 
 // The partials are those of the launched kernels on systems of this size: one
 // per group of SPMV_BLOCK consecutive rows for all three sums (vec_grid gives
 // K2 one element per thread), summed in the same order, so every iterate is
-// the three-launch form's bit for bit.  The wait is bounded as above.
+// the three-launch form's bit for bit.  Waits are bounded (exchange.hpp).
 //
 // Bound by the two exchanges: a store and the load that meets it cross the
 // die boundaries, about 1.5 us each way with the reductions.  Per iteration
@@ -223,7 +224,7 @@ __global__ void __launch_bounds__(BT)
 cg_resident(int32_t n, int32_t ng, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
             const T* __restrict__ val, const T* __restrict__ dinv, T* __restrict__ x, T* __restrict__ r,
             T* __restrict__ p, CgState<T>* st, int32_t k0, int32_t k_end, typename Word<T>::type* slots,
-            typename Word<T>::type* zs, uint32_t* bar) {
+            typename Word<T>::type* zs, Wait wait) {
 #pragma clang fp contract(off)
     typedef typename Word<T>::type W;
     constexpr W EMPTY = Word<T>::EMPTY;
@@ -292,7 +293,7 @@ cg_resident(int32_t n, int32_t ng, const int32_t* __restrict__ row_ptr, const in
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the slots emptied last time are
         __syncthreads();
         if (first) agent_store(s_pq + group, Word<T>::of(sum_red(red1 + t / 64)));
-        if (t < SPMV_BLOCK && !gather_slots<T, 1>(s_pq, ng, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<T, 1>(s_pq, ng, t, wait, all)) bad = 1;
         __syncthreads();
         if (bad) {
             given_up = true;
@@ -334,14 +335,14 @@ cg_resident(int32_t n, int32_t ng, const int32_t* __restrict__ row_ptr, const in
 #pragma unroll
             for (int u = 0; u < RES_COLS; ++u) zj[u] = c[u] >= 0 ? agent_load_at(z_k, (uint32_t)c[u]) : W(0);
         }
-        if (t < SPMV_BLOCK && !gather_slots<T, 2>(s_rr, ng, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<T, 2>(s_rr, ng, t, wait, all)) bad = 1;
         if (remote) {
             for (uint32_t spins = 0;;) {
                 bool empty = false;
 #pragma unroll
                 for (int u = 0; u < RES_COLS; ++u) empty |= zj[u] == EMPTY;
                 if (!empty) break;
-                if (wait_over(spins, bar)) {
+                if (wait_over(spins, wait)) {
                     bad = 1;
                     break;
                 }
@@ -376,7 +377,7 @@ cg_resident(int32_t n, int32_t ng, const int32_t* __restrict__ row_ptr, const in
         }
     }
     if (given_up) {
-        if (t == 0) atomicOr(bar, 1u);
+        if (t == 0) atomicOr(wait.bar, 1u);
         return;
     }
     if (i < n) {
@@ -453,6 +454,27 @@ int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const
     return RP_OK;
 }
 
+int launch_loop(rp_plan* p, const void* kernel, int grid, int block, void** args, const uint32_t* bar,
+                hipStream_t s) {
+    p->h_flags[LOOP_ABORT] = 1u;
+    if (hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(block), args, 0, s) != hipSuccess) {
+        (void)hipGetLastError();
+        return RP_OK;
+    }
+    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    return RP_OK;
+}
+
+bool loop_gave_up(rp_plan* p) {
+    if (p->h_flags[LOOP_ABORT] == 0u) {
+        p->loop_given_up = 0;
+        return false;
+    }
+    p->loop_rest = 1 << std::min(p->loop_given_up, 10);
+    p->loop_given_up = std::min(p->loop_given_up + 1, 10);
+    return true;
+}
+
 template <typename T>
 const void* resident_kernel(int bt) {
     return bt == 512 ? (const void*)cg_resident<T, 512> : (const void*)cg_resident<T, 1024>;
@@ -497,8 +519,7 @@ bool resident_room(rp_plan* p) {
 }
 
 // The iterations k0 .. min(k_end, budget) by the resident loop, enqueued, on a
-// plan that fits it (resident_block > 0) and has room for it (resident_room).  The abort word goes to h_flags[LOOP_ABORT],
-// to be looked at once the stream has passed.
+// plan that fits it (resident_block > 0) and has room for it (resident_room).  See launch_loop.
 template <typename T>
 int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int32_t* col, const T* val,
                        const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0, int32_t k_end, hipStream_t s) {
@@ -512,11 +533,10 @@ int launch_cg_resident(rp_plan* p, int32_t n, const int32_t* row_ptr, const int3
     uint32_t* bar = p->d_loop_bar;
     hipLaunchKernelGGL(clear_slots, dim3(256), dim3(256), 0, s, (uint32_t*)slots, (int32_t)(len * sizeof(W) / 4), bar);
     RP_HIP_TRY(hipGetLastError());
+    Wait wait{bar, wait_spins(p)};
     void* args[] = {&n, &ng, (void*)&row_ptr, (void*)&col, (void*)&val, (void*)&dinv, &x, &r, &pv, &st, &k0, &k_end,
-                    &slots, &zs, &bar};
-    RP_HIP_TRY(hipLaunchCooperativeKernel(resident_kernel<T>(bt), dim3((n + bt - 1) / bt), dim3(bt), args, 0, s));
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, p->d_loop_bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    return RP_OK;
+                    &slots, &zs, &wait};
+    return launch_loop(p, resident_kernel<T>(bt), (n + bt - 1) / bt, bt, args, bar, s);
 }
 
 template int launch_cg_resident<double>(rp_plan*, int32_t, const int32_t*, const int32_t*, const double*,

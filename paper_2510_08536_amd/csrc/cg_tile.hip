@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(TT)
 cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict__ halo, const int32_t* __restrict__ n_halo,
         const Places* __restrict__ places, const T* __restrict__ val, const T* __restrict__ dinv, T* __restrict__ x,
         T* __restrict__ r, T* __restrict__ p, CgState<T>* st, int32_t k0, int32_t k_end,
-        typename Word<T>::type* slots, typename Word<T>::type* zs, uint32_t* bar) {
+        typename Word<T>::type* slots, typename Word<T>::type* zs, Wait wait) {
 #pragma clang fp contract(off)
     typedef typename Word<T>::type W;
     constexpr W EMPTY = Word<T>::EMPTY;
@@ -322,7 +322,7 @@ cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the slots emptied last time are
         __syncthreads();
         if (t == 0) agent_store(s_pq + b, Word<T>::of(tile_sum(red1)));
-        if (t < SPMV_BLOCK && !gather_slots<T, 1>(s_pq, G, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<T, 1>(s_pq, G, t, wait, all)) bad = 1;
         __syncthreads();
         if (bad) {
             given_up = true;
@@ -373,13 +373,13 @@ cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
 #pragma unroll
         for (int h = 0; h < HALO_PER_THREAD; ++h)
             zh[h] = hid[h] >= 0 ? agent_load_at(z_k, (uint32_t)hid[h]) : W(0);
-        if (t < SPMV_BLOCK && !gather_slots<T, 2>(s_rr, G, t, bar, all)) bad = 1;
+        if (t < SPMV_BLOCK && !gather_slots<T, 2>(s_rr, G, t, wait, all)) bad = 1;
         for (uint32_t spins = 0;;) {
             bool empty = false;
 #pragma unroll
             for (int h = 0; h < HALO_PER_THREAD; ++h) empty |= zh[h] == EMPTY;
             if (!empty) break;
-            if (wait_over(spins, bar)) {
+            if (wait_over(spins, wait)) {
                 bad = 1;
                 break;
             }
@@ -422,7 +422,7 @@ cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
         __syncthreads();
     }
     if (given_up) {
-        if (t == 0) atomicOr(bar, 1u);
+        if (t == 0) atomicOr(wait.bar, 1u);
         return;
     }
 #pragma unroll
@@ -638,7 +638,7 @@ int tile_fits(rp_plan* p, hipStream_t s, bool* yes) {
 }
 
 // The iterations k0 .. min(k_end, budget) by the tiled loop, enqueued, on a
-// plan that fits it.  The abort word goes to h_flags[LOOP_ABORT].
+// plan that fits it.  See launch_loop.
 template <typename T>
 int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, CgState<T>* st, int32_t k0,
                    int32_t k_end, hipStream_t s) {
@@ -665,14 +665,14 @@ int launch_cg_tile(rp_plan* p, const T* src, const T* dinv, T* x, T* r, T* pv, C
         hipLaunchKernelGGL(to_positions<T>, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.order, x, r, pv, dinv, tx);
         RP_HIP_TRY(hipGetLastError());
     }
+    Wait wait{bar, wait_spins(p)};
     void* args[] = {&n, (void*)&first, (void*)&halo, (void*)&n_halo, (void*)&places, (void*)&val, (void*)&td, &tx, &tr,
-                    &tp, &st, &k0, &k_end, &slots, &zs, &bar};
-    RP_HIP_TRY(hipLaunchCooperativeKernel(tile_kernel<T>(tl.R / TT), dim3(tl.G), dim3(TT), args, 0, s));
+                    &tp, &st, &k0, &k_end, &slots, &zs, &wait};
+    RP_TRY(launch_loop(p, tile_kernel<T>(tl.R / TT), tl.G, TT, args, bar, s));
     if (tl.order) {
         hipLaunchKernelGGL(from_positions<T>, dim3((n + 255) / 256), dim3(256), 0, s, n, tl.inv, tx, x, r, pv);
         RP_HIP_TRY(hipGetLastError());
     }
-    RP_HIP_TRY(hipMemcpyAsync(p->h_flags + LOOP_ABORT, bar, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     return RP_OK;
 }
 

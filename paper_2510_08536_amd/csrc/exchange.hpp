@@ -5,8 +5,9 @@
 // pass the die's L2 by, so nothing is written back or invalidated; and every
 // value is its own flag: its slot holds EMPTY (a NaN no value is stored as)
 // until it is stored, and a reader loads until it is not.  Slots rotate through
-// RES_SETS sets.  Waits are bounded: after BAR_SPINS loads the reader gives up,
-// and a reader that finds the abort word set gives up too.
+// RES_SETS sets.  Waits are bounded: after so many loads the reader gives up,
+// and a reader that finds the abort word set gives up too.  A workgroup that gives
+// up publishes nothing more, so all do; the host goes on with launched kernels.
 #pragma once
 
 #include "device_util.hpp"
@@ -14,7 +15,11 @@
 namespace rp {
 
 constexpr int RES_SETS = 4;
-constexpr uint32_t BAR_SPINS = 1u << 22;   // a few seconds of polling at most
+// Loads of one wait at most, some tenths of a second: what it can wait for
+// beside values on their way is a workgroup that has no place yet, behind another
+// stream's or process's kernels.
+constexpr uint32_t WAIT_SPINS = 1u << 18;
+inline uint32_t wait_spins(const rp_plan* p) { return p->loop_spins ? p->loop_spins : WAIT_SPINS; }
 
 __device__ __forceinline__ uint32_t load_relaxed(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -54,9 +59,15 @@ __device__ __forceinline__ void agent_store(V* p, V v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// the bound of a launch's waits
+struct Wait {
+    uint32_t* bar;    // abort word
+    uint32_t most;    // loads
+};
+
 // spins of one wait: true = give up (too many, or another block gave up)
-__device__ __forceinline__ bool wait_over(uint32_t& spins, const uint32_t* bar) {
-    return ++spins > BAR_SPINS || (spins % 256 == 0 && load_relaxed(bar) != 0u);
+__device__ __forceinline__ bool wait_over(uint32_t& spins, const Wait& wait) {
+    return ++spins > wait.most || (spins % 256 == 0 && load_relaxed(wait.bar) != 0u);
 }
 
 // The sums of N values per group once no slot of slots[0 .. N ng) is empty
@@ -65,7 +76,7 @@ __device__ __forceinline__ bool wait_over(uint32_t& spins, const uint32_t* bar) 
 // to red[j][0 .. 4).  False: the wait was abandoned.
 template <typename T, int N>
 __device__ __forceinline__ bool gather_slots(const typename Word<T>::type* slots, int32_t ng, int32_t t,
-                                             const uint32_t* bar, T (*red)[SPMV_BLOCK / 64]) {
+                                             const Wait& wait, T (*red)[SPMV_BLOCK / 64]) {
 #pragma clang fp contract(off)
     T s[N];
 #pragma unroll
@@ -80,7 +91,7 @@ __device__ __forceinline__ bool gather_slots(const typename Word<T>::type* slots
 #pragma unroll
             for (int j = 0; j < N; ++j) empty |= u[j] == Word<T>::EMPTY;
             if (!empty) break;
-            if (wait_over(spins, bar)) {
+            if (wait_over(spins, wait)) {
                 good = false;
                 break;
             }

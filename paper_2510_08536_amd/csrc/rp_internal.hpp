@@ -332,7 +332,10 @@ struct rp_plan {
     int resident_block[2] = {-1, -1};  // its block size in FP64, FP32; 0: the plan does not fit it; -1: not asked yet
     uint32_t* d_loop_bar = nullptr;    // abort word and per-block barrier flags of the CG loop (cg_loop.hip)
 
-    uint64_t alloc_faults = 0;         // rp_plan_set_loop_faults: bit 0, the loops' next allocation fails
+    uint64_t alloc_faults = 0;         // rp_plan_set_loop_faults: bit 0, the loops' next allocation fails;
+    uint32_t loop_spins = 0;           // loads of a wait at most (0: the default)
+    int32_t loop_given_up = 0;         // launches given up one after the other; after the k-th the
+    int32_t loop_rest = 0;             // next 2^k solves (1024 at most) take launched kernels
 
     rp::AmgHier* amg = nullptr;        // multigrid hierarchy (RP_PRECOND_AMG), built on first use
     rp::AmgHier* amg_ro = nullptr;     // the same on the solve-order copy
@@ -347,6 +350,14 @@ struct rp_plan {
 };
 
 namespace rp {
+
+// cg_loop.hip: enqueue a one-launch loop, every workgroup resident at once; its
+// abort word goes to h_flags[LOOP_ABORT], which is set too if it cannot be launched
+int launch_loop(rp_plan* p, const void* kernel, int grid, int block, void** args, const uint32_t* bar, hipStream_t s);
+// after the stream has passed it: whether it gave up
+bool loop_gave_up(rp_plan* p);
+// whether this solve may take a loop at all, asked once per solve
+inline bool loop_allowed(rp_plan* p) { return p->loop_rest == 0 || p->loop_rest-- == 0; }
 
 // an allocation of the one-launch loops
 inline hipError_t loop_malloc(rp_plan* p, void** q, size_t bytes) {

@@ -139,7 +139,7 @@ _sig = {
     "rp_rcm_order": (C.c_int, [C.c_int32, _P, _P, _P]),
     "rp_plan_device_ptrs": (C.c_int, [_P, C.POINTER(rp_device_ptrs)]),
     "rp_plan_set_vec_grid": (C.c_int, [_P, C.c_int32]),
-    "rp_plan_set_loop_faults": (C.c_int, [_P, C.c_uint64]),
+    "rp_plan_set_loop_faults": (C.c_int, [_P, C.c_uint64, C.c_uint32]),
     "rp_plan_block_jacobi": (C.c_int, [_P, C.c_int32, _i64p, _P, _P, _P]),
     "rp_plan_export_recv": (C.c_int, [_P, C.POINTER(rp_ipc_handle), _i64p]),
     "rp_recv_attach": (C.c_int, [C.POINTER(rp_ipc_handle), C.POINTER(C.c_void_p)]),
@@ -403,9 +403,10 @@ class Plan:
         """Fix the solvers' elementwise-kernel grid (0 = default sizing)."""
         _check(rp_plan_set_vec_grid(self._h, int(blocks)), "rp_plan_set_vec_grid")
 
-    def set_loop_faults(self, allocs: int = 0):
-        """Make allocations of the one-launch loops fail (bit k: the k-th from here)."""
-        _check(rp_plan_set_loop_faults(self._h, int(allocs)), "rp_plan_set_loop_faults")
+    def set_loop_faults(self, allocs: int = 0, waits: int = 0):
+        """Make allocations of the one-launch loops fail (bit k: the k-th from
+        here), or their waits end after so many polls (0: the default)."""
+        _check(rp_plan_set_loop_faults(self._h, int(allocs), int(waits)), "rp_plan_set_loop_faults")
 
     def get_values(self):
         v64 = np.zeros(max(self.n_slots, 1), np.float64)
