@@ -523,6 +523,7 @@ int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t 
     hipLaunchKernelGGL(tile_build, dim3(G), dim3(1024), 0, s, R, tl.first, tl.order, tl.inv, p->d_row_ptr, p->d_col,
                        tl.halo, tl.n_halo, (Places*)tl.places);
     RP_HIP_TRY(hipGetLastError());
+    loop_host(p);
     std::vector<int32_t> h(G);
     RP_HIP_TRY(hipMemcpyAsync(h.data(), tl.n_halo, sizeof(int32_t) * (size_t)G, hipMemcpyDeviceToHost, s));
     RP_HIP_TRY(hipStreamSynchronize(s));
@@ -536,13 +537,8 @@ int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t 
     return RP_OK;
 }
 
-}  // namespace
-
-// the plan's tiles, or that it does not fit or has no memory for them
-// (tiles.R = 0), found out once
-int tile_setup(rp_plan* p, hipStream_t s) {
+int tile_find(rp_plan* p, hipStream_t s) {
     auto& tl = p->tiles;
-    if (tl.asked) return RP_OK;
     int cus = 0, coop = 0;
     RP_HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, p->device));
     RP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
@@ -550,6 +546,7 @@ int tile_setup(rp_plan* p, hipStream_t s) {
     // by rank where that costs at most a quarter more rows per thread, else
     // (or where a halo is too long) in one run
     int nr[2] = {0, 0};
+    loop_host(p);
     std::vector<int32_t> first[2];
     if (coop && p->max_row <= U)
         for (int k = 0; k < 2; ++k)
@@ -574,10 +571,25 @@ int tile_setup(rp_plan* p, hipStream_t s) {
             if (!fits) RP_TRY(order_free(p));
         }
     }
-    if (!fits) RP_TRY(tile_free(p));
+    return fits ? RP_OK : tile_free(p);
+}
+
+}  // namespace
+
+// the plan's tiles, or that it does not fit or has no memory for them
+// (tiles.R = 0), found out once
+int tile_setup(rp_plan* p, hipStream_t s) {
+    if (p->tiles.asked) return RP_OK;
+    try {
+        RP_TRY(tile_find(p, s));
+    } catch (const std::bad_alloc&) {   // no host memory: as without device memory
+        RP_HIP_TRY(hipStreamSynchronize(s));
+        RP_TRY(tile_free(p));
+        RP_TRY(order_free(p));
+    }
     // for good, also where memory was short: the values' slices are laid out by
     // these tables, and a search repeated by every solve costs more than it gives
-    tl.asked = true;
+    p->tiles.asked = true;
     return RP_OK;
 }
 

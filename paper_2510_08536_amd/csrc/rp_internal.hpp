@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -359,11 +360,16 @@ bool loop_gave_up(rp_plan* p);
 // whether this solve may take a loop at all, asked once per solve
 inline bool loop_allowed(rp_plan* p) { return p->loop_rest == 0 || p->loop_rest-- == 0; }
 
-// an allocation of the one-launch loops
+// an allocation of the one-launch loops, on the device and (std::vector) the host
 inline hipError_t loop_malloc(rp_plan* p, void** q, size_t bytes) {
     const bool fault = p->alloc_faults & 1u;
     p->alloc_faults >>= 1;
     return fault ? hipErrorOutOfMemory : hipMalloc(q, bytes);
+}
+inline void loop_host(rp_plan* p) {
+    const bool fault = p->alloc_faults & 1u;
+    p->alloc_faults >>= 1;
+    if (fault) throw std::bad_alloc();
 }
 // Memory a one-launch loop keeps with the plan, if there is some: without it a
 // solve takes launched kernels, as a plan that does not fit does.

@@ -275,6 +275,7 @@ int tile_order(rp_plan* p, int64_t cap, int32_t* order, int32_t* inv, hipStream_
     hipLaunchKernelGGL(order_count, g, b, 0, s, n, seeds, la, size);
     hipLaunchKernelGGL(order_pairs, g, b, 0, s, n, p->d_row_ptr, p->d_col, la, table, slots - 1, flag + 1);
     RP_HIP_TRY(hipGetLastError());
+    loop_host(p);
     std::vector<uint32_t> hs(2 * (size_t)S + 2);
     std::vector<unsigned long long> ht(slots);
     RP_HIP_TRY(hipMemcpyAsync(hs.data(), size, sizeof(uint32_t) * hs.size(), hipMemcpyDeviceToHost, s));

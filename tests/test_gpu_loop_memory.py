@@ -1,11 +1,11 @@
-"""The one-launch loops where memory runs out: any of the allocations they ask
-for fails, alone or with all that follow.  A solve then takes the tiles that
-are left to it or the launched kernels, and so does every later one, whatever
-memory there is by then: iterates after a fixed budget agree with
-RP_LOOP_THREE to 1e-11 relative (1e-10 for BiCGStab, 1e-4 for the FP32
-iterations of a mixed solve: rounding of reordered sums, some 300 terms of a
-thread and a tree over 3e5 rows), and a second solve without any memory gives
-the first one's x bit for bit."""
+"""The one-launch loops where memory runs out, the device's or (while the tiles
+are built) the host's: any of the allocations they ask for fails, alone or with
+all that follow.  A solve then takes the tiles that are left to it or the
+launched kernels, and so does every later one, whatever memory there is by
+then: iterates after a fixed budget agree with RP_LOOP_THREE to 1e-11 relative
+(1e-10 for BiCGStab, 1e-4 for the FP32 iterations of a mixed solve: rounding of
+reordered sums, some 300 terms of a thread and a tree over 3e5 rows), and a
+second solve without any memory gives the first one's x bit for bit."""
 import numpy as np
 import pytest
 
