@@ -33,7 +33,6 @@ namespace {
 
 constexpr int BI_SUMS = 6;          // slots of a tile per set: (r^, v); (s, s), (t, s), (t, t); (r^, r), (r, r)
 constexpr int BI_NR[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10};
-constexpr int BI_NR_MAX = 10;
 constexpr int BI_HK = 6, BI_HK_NR = 4;     // halo entries per thread kept in registers, rows per thread they have room beside
 
 __global__ void __launch_bounds__(256) bi_clear(uint64_t* w, int64_t words, uint32_t* bar) {

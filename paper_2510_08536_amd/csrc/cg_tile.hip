@@ -452,8 +452,6 @@ cg_tile(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict_
 // the rows per thread of a tile (CG has kernels from 3 on: smaller systems take
 // the resident loop)
 constexpr int NRS[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 18, 20, 22, 24, 28, 32};
-template <typename T>
-constexpr int nr_max() { return sizeof(T) == 8 ? 16 : 32; }   // x, r, z and M^-1 in half of the registers
 
 template <typename T, int... I>
 const void* pick_kernel(int nr, std::integer_sequence<int, I...>) {
@@ -543,8 +541,10 @@ int tile_find(rp_plan* p, hipStream_t s) {
     RP_HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, p->device));
     RP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
     const int most = std::min(cus, SPMV_BLOCK);   // a thread per tile's sums
-    // by rank where that costs at most a quarter more rows per thread, else
-    // (or where a halo is too long) in one run
+    // by rank where that costs at most a quarter more rows per thread, and no
+    // solver the loop that the cut in one run has room for (128^3 rows in 3 x 3 x 3
+    // ranks: 18 rows per thread against 16); else, or where a halo is too long,
+    // the other one
     int nr[2] = {0, 0};
     loop_host(p);
     std::vector<int32_t> first[2];
@@ -558,9 +558,13 @@ int tile_find(rp_plan* p, hipStream_t s) {
                 }
             }
     bool fits = false, memory = true;
-    if (nr[0] > 0 && 4 * nr[0] <= 5 * nr[1]) RP_TRY(tile_try(p, nr[0], first[0], s, &fits, &memory));
+    const bool by_rank = nr[0] > 0 && 4 * nr[0] <= 5 * nr[1];
+    bool dear = false;
+    for (int most_nr : {BI_NR_MAX, nr_max<double>(), nr_max<float>()}) dear |= nr[1] <= most_nr && most_nr < nr[0];
+    if (by_rank && !dear) RP_TRY(tile_try(p, nr[0], first[0], s, &fits, &memory));
     if (!fits && nr[1] > 0) {
         RP_TRY(tile_try(p, nr[1], first[1], s, &fits, &memory));
+        if (!fits && by_rank && dear) RP_TRY(tile_try(p, nr[0], first[0], s, &fits, &memory));
         if (!fits && memory) {
             bool ok = false;
             memory = got(p, &tl.order, sizeof(int32_t) * (size_t)p->n_rows) &&

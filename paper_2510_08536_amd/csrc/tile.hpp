@@ -11,6 +11,9 @@ namespace rp {
 
 constexpr int TT = 512;                 // threads per block: 8 wavefronts, 256 registers each
 constexpr int U = 7;                    // entries per row at most: a cell and its six faces
+constexpr int BI_NR_MAX = 10;           // rows per thread at most: BiCGStab's vectors in half of the registers
+template <typename T>
+constexpr int nr_max() { return sizeof(T) == 8 ? 16 : 32; }   // CG's x, r, z and M^-1
 constexpr int HALO_PER_THREAD = 16;
 constexpr int HALO_MAX = HALO_PER_THREAD * TT;
 
