@@ -145,9 +145,8 @@ typedef struct rp_solve_opts {
     int32_t fused_loop;      /* RP_CG with Jacobi and RP_BICGSTAB, how an iteration is launched.
                                 RP_LOOP_THREE: one launch per phase (SpMV with (p, q);
                                 r update with (r, z), (r, r); x and p update).
-                                RP_LOOP_AUTO (default): all iterations in one cooperative
-                                launch that exchanges values instead of waiting at barriers,
-                                on systems of at most RP_LOOP_TWO_MAX_ROWS rows (every row
+                                RP_LOOP_AUTO (default): all iterations in one launch
+                                that exchanges values between its workgroups, on systems of at most RP_LOOP_TWO_MAX_ROWS rows (every row
                                 at most 8 entries) with the system in registers, and in fused
                                 order on medium ones (2 million rows in FP64, 4 in FP32, a
                                 row at most 7 entries) with the vectors in registers and LDS;
@@ -167,10 +166,14 @@ typedef struct rp_solve_opts {
                                 multigrid always take three launches per iteration, as
                                 does RP_LOOP_COOPERATIVE where the device cannot launch
                                 the grid cooperatively.  RP_LOOP_AUTO's loops need the whole
-                                grid on the device at once; where it finds no place in some
-                                tenths of a second (other streams', other processes' work),
-                                the solve goes on with launched kernels, and so do the
-                                plan's next 1, 2, 4, ... 1024 solves, a longer run each
+                                grid on the device at once.  Solves of several threads
+                                therefore run their loops side by side as far as the device
+                                holds them and else in turn; small systems, whose results
+                                are the same, take two launches per iteration while more
+                                solves run than that pays for.  Where a loop finds no place
+                                in some tenths of a second (other streams', other processes'
+                                work), the solve goes on with launched kernels, and so do
+                                the plan's next 1, 2, 4, ... 1024 solves, a longer run each
                                 time the loop gives up again.  RP_BICGSTAB in fused order, with at
                                 most 7 entries a row and 1.3 million rows, runs all
                                 iterations in one launch by RP_LOOP_AUTO (equal up to the

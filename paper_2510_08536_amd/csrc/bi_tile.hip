@@ -1,4 +1,4 @@
-// BiCGStab iterations in one cooperative launch: one workgroup per compute
+// BiCGStab iterations in one launch: one workgroup per compute
 // unit, each owning a tile of rows, as in the tiled CG loop (cg_tile.hip).
 //
 // Launched apart an iteration is five kernels that move 20 n words besides the

@@ -228,6 +228,7 @@ int create(int32_t n_ranks_total, const int32_t* n_cells_all, int32_t first, int
     p->n_slots = slots;
     // everything above is host-side validation; the GPU is touched from here on
     RP_HIP_TRY(hipGetDevice(&p->device));
+    RP_HIP_TRY(hipDeviceGetAttribute(&p->n_cus, hipDeviceAttributeMultiprocessorCount, p->device));
     RP_TRY(plan_build(p.get(), share));
     RP_TRY(alloc_values(p.get()));
     p->h_src.assign(4 * (size_t)alpha, nullptr);

@@ -1077,7 +1077,7 @@ int iterate_two(Cg<T>& c, int chunk, int32_t max_iter) {
 enum class Loop { LAUNCHES, RESIDENT, TILE };
 
 template <typename T>
-int choose_loop(const Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
+int choose_loop(const Cg<T>& c, const rp_solve_opts& o, SmallSolve* small, Loop* loop) {
     *loop = Loop::LAUNCHES;
     if (o.fused_loop != RP_LOOP_AUTO || c.plan->timing.enabled || o.graph || c.bj_minv || c.amg ||
         c.plan->vec_grid_override != 0)   // a fixed vector grid asks for the launched kernels
@@ -1085,7 +1085,8 @@ int choose_loop(const Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
     if (c.n <= RP_LOOP_TWO_MAX_ROWS) {
         int bt = 0;
         RP_TRY(resident_block<T>(c.plan, &bt));
-        if (bt > 0 && resident_room(c.plan)) *loop = Loop::RESIDENT;
+        if (bt > 0 && small->loops_fit(c.plan, (c.n + bt - 1) / bt) && resident_room(c.plan))
+            *loop = Loop::RESIDENT;
     } else if (c.ix.row_ptr == c.plan->d_row_ptr) {   // the tiles are the fused order's
         bool fits = false;
         RP_TRY(tile_fits<T>(c.plan, c.s, &fits));
@@ -1122,6 +1123,8 @@ int iterate(Cg<T>& c, const rp_solve_opts& o, Loop* loop) {
         constexpr int64_t LOOP_ITERS = 1 << 16;
         while (c.h->done == CG_RUNNING && c.h->iter < max_iter) {
             const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)c.h->iter + LOOP_ITERS, max_iter);
+            const int bt = c.plan->resident_block[sizeof(T) == 4];
+            const LoopPlace place(c.plan, *loop == Loop::RESIDENT ? (c.n + bt - 1) / bt : c.plan->tiles.G);
             if (*loop == Loop::RESIDENT)
                 RP_TRY(launch_cg_resident<T>(c.plan, c.n, c.ix.row_ptr, c.ix.col, c.val, c.dinv, c.x, c.r, c.p, c.st,
                                              c.h->iter, k1, c.s));
@@ -1233,8 +1236,9 @@ int solve_fp64(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, r
         use_amg(c, p->d_z, ordered);
     }
     const double tol2 = o.tol * o.tol;
+    SmallSolve small;
     Loop loop;
-    RP_TRY(choose_loop(c, o, &loop));
+    RP_TRY(choose_loop(c, o, &small, &loop));
     RP_TRY((launch_residual<double, false>(c, o.x0_zero != 0, nullptr)));
     RP_TRY(launch_start(c, 0, tol2, 0.0, o.max_iter));
     RP_TRY(start_ahead(c, loop, 0, o.max_iter));
@@ -1317,8 +1321,9 @@ int solve_mixed(rp_plan* p, const double* b, double* x, const rp_solve_opts& o, 
         RP_TRY(amg_prepare(p, true, s, ordered));
         use_amg(in, p->d_z32, ordered);
     }
+    SmallSolve small;
     Loop loop;
-    RP_TRY(choose_loop(in, o, &loop));
+    RP_TRY(choose_loop(in, o, &small, &loop));
 
     RP_TRY((launch_residual<double, true>(out, o.x0_zero != 0, p->d_r32)));
     RP_TRY(launch_finalize(out, FIN_RESIDUAL, 0, 0.0, 0.0));
@@ -1706,6 +1711,7 @@ int bi_iterate(Bi& q, int chunk, int32_t max_iter, bool* tile, bool transposed) 
         constexpr int64_t LOOP_ITERS = 1 << 15;   // a launch's length is bounded: other work waits for it
         while (q.h->done == CG_RUNNING && q.h->iter < max_iter) {
             const int32_t k1 = (int32_t)std::min<int64_t>((int64_t)q.h->iter + LOOP_ITERS, max_iter);
+            const LoopPlace place(c.plan, c.plan->tiles.G);
             RP_TRY(launch_bi_tile(c.plan, c.val, transposed, c.dinv, c.x, c.r, q.rh, q.p, q.v, q.st, q.h->iter, k1,
                                   c.s));
             RP_TRY(bi_read(q));

@@ -1,6 +1,7 @@
-// CG iterations in one cooperative launch (rp_solve_opts.fused_loop), in two
-// forms: cg_loop (RP_LOOP_COOPERATIVE), for systems of any size, and
-// cg_resident (RP_LOOP_AUTO on small systems), described further down.
+// CG iterations in one launch (rp_solve_opts.fused_loop), in two forms: cg_loop
+// (RP_LOOP_COOPERATIVE), for systems of any size, and cg_resident (RP_LOOP_AUTO
+// on small systems), described further down; and what the one-launch loops
+// share on the host (launch_loop).
 //
 // On small systems an iteration is bound by the gaps between its three
 // dependent kernels, not by memory.  Here one launch, with every block
@@ -25,6 +26,9 @@
 // word and leaves, and every block that sees the abort word leaves too; the
 // host reports it.  The flags and the abort word are cleared by a kernel
 // before each launch.
+#include <condition_variable>
+#include <mutex>
+
 #include "exchange.hpp"
 #include "spmv.hpp"
 
@@ -437,6 +441,7 @@ int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const
     RP_TRY(loop_grid<T>(n, &grid));
     if (grid < N_XCD) return RP_OK;
     if (!p->d_loop_bar) RP_HIP_TRY(hipMalloc(&p->d_loop_bar, BAR_WORDS * sizeof(uint32_t)));
+    const LoopPlace place(p, grid);
     hipLaunchKernelGGL(clear_barrier, dim3(1), dim3(1024), 0, s, p->d_loop_bar, FLAG0 + FLAG_STRIDE * grid);
     RP_HIP_TRY(hipGetLastError());
     T* part = (T*)p->d_partials;
@@ -454,10 +459,74 @@ int launch_cg_loop(rp_plan* p, int32_t n, const SpmvIdx& ix, const T* val, const
     return RP_OK;
 }
 
+namespace {
+
+// The compute units of a device that one-launch loops hold.
+//
+// Every workgroup of a loop has to find its place while the others wait for its
+// values, so loops on different streams must not take the units between them.
+// (The runtime's cooperative launches keep apart by running one after the
+// other, whatever they leave free.)  A loop therefore counts its workgroups in,
+// a unit each, and is launched once all of them fit beside those of the loops
+// that run.  Workgroups go to the dies in turn, so a die's share is counted up.
+struct Units {
+    std::mutex m;
+    std::condition_variable freed;
+    int held = 0;
+    uint64_t next = 0, turn = 0;   // those who wait are served in the order they came
+    int small = 0;                 // solves of small systems
+};
+constexpr int MAX_DEVICES = 64;
+Units g_units[MAX_DEVICES];
+
+int units(const rp_plan* p, int grid) { return std::min((grid + N_XCD - 1) / N_XCD * N_XCD, p->n_cus); }
+
+}  // namespace
+
+LoopPlace::LoopPlace(rp_plan* p, int grid) : device(p->device % MAX_DEVICES), need(units(p, grid)) {
+    Units& u = g_units[device];
+    std::unique_lock<std::mutex> lock(u.m);
+    const uint64_t mine = u.next++;
+    u.freed.wait(lock, [&] { return u.turn == mine && u.held + need <= p->n_cus; });
+    ++u.turn;
+    u.held += need;
+    u.freed.notify_all();
+}
+
+LoopPlace::~LoopPlace() {
+    Units& u = g_units[device];
+    {
+        std::lock_guard<std::mutex> lock(u.m);
+        u.held -= need;
+    }
+    u.freed.notify_all();
+}
+
+// Small systems have the same iterates in launched kernels, which several
+// streams overlap as finely as they come.  Loops are faster as long as the
+// solves that run need the device no more than twice over; measured per solve
+// with 1, 2, 4 and 8 threads, launches and loops, at 32^3 rows (64 units) 1.70 0.90
+// 0.53 0.53 ms and 0.89 0.48 0.27 0.25; at 44^3 (168) 2.56 1.45 1.46 0.97 and 1.46
+// 1.42 1.41 1.43; at 64^3 (256) 5.4 3.6 2.5 2.9 and 2.8 whatever the threads; mixed
+// 64^3 5.3 3.3 2.2 2.2 and 3.3 3.1 3.1 3.1.
+bool SmallSolve::loops_fit(rp_plan* p, int grid) {
+    device = p->device % MAX_DEVICES;
+    Units& u = g_units[device];
+    std::lock_guard<std::mutex> lock(u.m);
+    ++u.small;
+    return u.small * units(p, grid) <= 2 * p->n_cus;
+}
+
+SmallSolve::~SmallSolve() {
+    if (device < 0) return;
+    std::lock_guard<std::mutex> lock(g_units[device].m);
+    --g_units[device].small;
+}
+
 int launch_loop(rp_plan* p, const void* kernel, int grid, int block, void** args, const uint32_t* bar,
                 hipStream_t s) {
     p->h_flags[LOOP_ABORT] = 1u;
-    if (hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(block), args, 0, s) != hipSuccess) {
+    if (hipLaunchKernel(kernel, dim3(grid), dim3(block), args, 0, s) != hipSuccess) {
         (void)hipGetLastError();
         return RP_OK;
     }
@@ -491,14 +560,12 @@ int resident_block(rp_plan* p, int* out) {
     int& bt = p->resident_block[sizeof(T) == 4];
     if (bt < 0) {
         const int64_t n = p->n_rows;
-        int cus = 0, coop = 0, fit = 0;
-        RP_HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, p->device));
-        RP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-        if (coop && p->max_row <= RES_COLS && n <= (int64_t)RES_GROUPS * SPMV_BLOCK)
+        int fit = 0;
+        if (p->max_row <= RES_COLS && n <= (int64_t)RES_GROUPS * SPMV_BLOCK)
             for (int t = sizeof(T) == 8 ? 512 : 1024; t <= 1024 && fit == 0; t *= 2) {
                 int per_cu = 0;
                 RP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<T>(t), t, 0));
-                if (n <= (int64_t)cus * per_cu * t) fit = t;
+                if (n <= (int64_t)p->n_cus * per_cu * t) fit = t;
             }
         bt = fit;
     }

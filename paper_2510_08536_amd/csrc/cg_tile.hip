@@ -1,4 +1,4 @@
-// CG iterations on medium systems in one cooperative launch: one workgroup
+// CG iterations on medium systems in one launch: one workgroup
 // per compute unit, each owning a tile of consecutive rows for the whole
 // launch.
 //
@@ -537,10 +537,7 @@ int tile_try(rp_plan* p, int nr, const std::vector<int32_t>& first, hipStream_t 
 
 int tile_find(rp_plan* p, hipStream_t s) {
     auto& tl = p->tiles;
-    int cus = 0, coop = 0;
-    RP_HIP_TRY(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, p->device));
-    RP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    const int most = std::min(cus, SPMV_BLOCK);   // a thread per tile's sums
+    const int most = std::min(p->n_cus, SPMV_BLOCK);   // a thread per tile's sums
     // by rank where that costs at most a quarter more rows per thread, and no
     // solver the loop that the cut in one run has room for (128^3 rows in 3 x 3 x 3
     // ranks: 18 rows per thread against 16); else, or where a halo is too long,
@@ -548,7 +545,7 @@ int tile_find(rp_plan* p, hipStream_t s) {
     int nr[2] = {0, 0};
     loop_host(p);
     std::vector<int32_t> first[2];
-    if (coop && p->max_row <= U)
+    if (p->max_row <= U)
         for (int k = 0; k < 2; ++k)
             for (int v : NRS) {
                 first[k] = cut(p, (int64_t)v * TT, most, k == 0);

@@ -330,6 +330,7 @@ struct rp_plan {
         uint32_t* bar = nullptr;       // abort word
     } tiles;
     uint64_t* d_slots = nullptr;       // what the resident CG loop exchanges (cg_loop.hip)
+    int n_cus = 0;                     // the device's compute units
     int resident_block[2] = {-1, -1};  // its block size in FP64, FP32; 0: the plan does not fit it; -1: not asked yet
     uint32_t* d_loop_bar = nullptr;    // abort word and per-block barrier flags of the CG loop (cg_loop.hip)
 
@@ -352,8 +353,24 @@ struct rp_plan {
 
 namespace rp {
 
-// cg_loop.hip: enqueue a one-launch loop, every workgroup resident at once; its
-// abort word goes to h_flags[LOOP_ABORT], which is set too if it cannot be launched
+// cg_loop.hip: a loop's compute units, a unit per workgroup, waited for and held
+// from its launch until the stream has passed it
+struct LoopPlace {
+    LoopPlace(rp_plan* p, int grid);
+    ~LoopPlace();
+    LoopPlace(const LoopPlace&) = delete;
+    LoopPlace& operator=(const LoopPlace&) = delete;
+    int device, need;
+};
+// a solve of a small system, counted while it runs
+struct SmallSolve {
+    ~SmallSolve();
+    // whether the solves that run leave the device to loops of `grid` workgroups
+    bool loops_fit(rp_plan* p, int grid);
+    int device = -1;
+};
+// enqueue a one-launch loop that has its place; its abort word goes to
+// h_flags[LOOP_ABORT], which is set too if it cannot be launched
 int launch_loop(rp_plan* p, const void* kernel, int grid, int block, void** args, const uint32_t* bar, hipStream_t s);
 // after the stream has passed it: whether it gave up
 bool loop_gave_up(rp_plan* p);

