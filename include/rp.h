@@ -145,11 +145,12 @@ typedef struct rp_solve_opts {
     int32_t fused_loop;      /* RP_CG with Jacobi and RP_BICGSTAB, how an iteration is launched.
                                 RP_LOOP_THREE: one launch per phase (SpMV with (p, q);
                                 r update with (r, z), (r, r); x and p update).
-                                RP_LOOP_AUTO (default): all iterations in one launch
-                                that exchanges values between its workgroups, on systems of at most RP_LOOP_TWO_MAX_ROWS rows (every row
-                                at most 8 entries) with the system in registers, and in fused
-                                order on medium ones (2 million rows in FP64, 4 in FP32, a
-                                row at most 7 entries) with the vectors in registers and LDS;
+                                RP_LOOP_AUTO (default): all iterations in one launch that
+                                exchanges values between its workgroups, on systems of at
+                                most RP_LOOP_TWO_MAX_ROWS rows (every row at most 8
+                                entries) with the system in registers, and in fused order
+                                on medium ones (2 million rows in FP64, 4 in FP32, a row at
+                                most 7 entries) with the vectors in registers and LDS;
                                 finding a row order with locality, once per plan, where the
                                 numbering has none.  Else two launches on systems
                                 of at most RP_LOOP_TWO_MAX_ROWS rows, the x and p update of
