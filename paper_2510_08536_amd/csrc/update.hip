@@ -223,7 +223,7 @@ symmetry_gather_kernel(int32_t n_faces, int32_t n_iface, int32_t alpha, bool che
 
 __global__ void clear_flags(uint32_t* flags) {
     if (threadIdx.x < 2) flags[threadIdx.x] = 0u;
-    if (threadIdx.x == 2) flags[2] += 1u;
+    if (threadIdx.x == 2) atomicAdd(flags + 2, 1u);
 }
 
 int grid_for(int64_t n, int block = 256, int cap = 8192) {
@@ -316,10 +316,16 @@ int launch_update_gather(rp_plan* p, const double* const* table, bool lower_give
     }
     const int64_t n_pos = p->n_slots;
     if (n_pos == 0 && p->n_rows == 0) return RP_OK;
-    // two rounds of the 2048 blocks the chip holds: with one round the last
-    // blocks end far apart, with more a block's search for its ranks counts
-    // (256^3: 2048 blocks 687 us, 3072 765, 4096 652, 6144 691)
-    const int g = (grid_for(std::max<int64_t>(n_pos, p->n_rows), 256, 4096) + N_XCD - 1) / N_XCD * N_XCD;
+    // One round of the 2048 blocks the chip holds, or two.  With one, the last
+    // blocks of a long update end far apart; with two, each block's search for its
+    // ranks counts, and shorter updates pay for it (2048 / 4096 blocks: 600 000 rows
+    // in a slab 24 / 26 us, 128^3 65 / 66, 200 x 190 x 210 320 / 330, 224^3 471 / 453,
+    // 256^3 690 / 653; 3072 765, 6144 691).  Without a pattern in the numbering chunks
+    // differ more (27-point rows 64 x 63 x 62 34 / 37, 90^3 110 / 84; numbered at
+    // random 100^3 52 / 51, 120 x 118 x 116 105 / 97, 180^3 433 / 369).
+    const bool pattern = 2 * p->coded_groups > p->n_groups;
+    const int most = n_pos > (pattern ? 1 << 26 : 1 << 23) ? 4096 : 2048;
+    const int g = (grid_for(std::max<int64_t>(n_pos, p->n_rows), 256, most) + N_XCD - 1) / N_XCD * N_XCD;
     RP_TRY(timing_begin(p, RP_KERNEL_SCATTER, s));
     hipLaunchKernelGGL(gather_kernel, dim3(g), dim3(256), 0, s, (int32_t)n_pos, (int32_t)p->n_rows, p->alpha,
                        p->d_perm_inv, table, p->d_slot_off, p->d_row0, p->d_nf, p->d_val64, p->d_val32,
