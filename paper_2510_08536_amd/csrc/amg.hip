@@ -935,7 +935,7 @@ int cycle_down(AmgHier& h, const Src& q, int32_t l, const T* r, const int32_t* g
     T* xc = L.target < h.tail_level ? cv[1] : nullptr;   // the tail makes its own first sweep
     const T* dinv_c = Prec<T>::dinv(C);
     if (l == 0) {
-        hipLaunchKernelGGL(amg_resid<T>, dim3(spmv_grid(n, INT32_MAX)), dim3(SPMV_BLOCK), 0, s, n, q.ix,
+        hipLaunchKernelGGL(amg_resid<T>, dim3(product_grid(n, q.nnz)), dim3(SPMV_BLOCK), 0, s, n, q.ix,
                            Prec<T>::val0(q), v[1], r, v[2], gate);
     } else {
         const int cr = chunk_rows(L), g = chunk_grid(n, cr);
@@ -1031,7 +1031,7 @@ int vcycle(AmgHier& h, const Src& q, const T* r, T* y, T* part, int32_t n_part, 
     hipLaunchKernelGGL(amg_prolong<T>, dim3(grid_of(n)), dim3(AB), 0, s, n, L0.map,
                        (const T*)Prec<T>::vec(h.lev[L0.target])[3], v[1], gate);
 #define RP_LAUNCH(PT, RRF)                                                                                       \
-    hipLaunchKernelGGL((amg_post<T, PT, RRF>), dim3(spmv_grid(n, PT ? SPMV_GRID_MAX : INT32_MAX)), dim3(SPMV_BLOCK), \
+    hipLaunchKernelGGL((amg_post<T, PT, RRF>), dim3(PT ? spmv_grid(n) : product_grid(n, q.nnz)), dim3(SPMV_BLOCK),    \
                        0, s, n, q.ix, Prec<T>::val0(q), v[1], r, Prec<T>::dinv0(q), omega, y, part, gate)
     if (want && rr) RP_LAUNCH(true, true);
     else if (want) RP_LAUNCH(true, false);

@@ -936,8 +936,9 @@ int launch_resume(Cg<T>& c) {
 // k < 0: K2 and K3 take the iteration number from the device state (graphs)
 template <typename T>
 int launch_iteration(Cg<T>& c, int32_t k, hipStream_t s) {
-    // the largest systems: a block per group, whose sums are folded
-    const bool fold = fold_sums(c.n) > 0;
+    // the largest systems: a block per group, whose sums are folded (long rows: no,
+    // see product_grid)
+    const bool fold = fold_sums(c.n) > 0 && !long_rows(c.n, c.ix.nnz);
     const int32_t g_pq = fold ? FOLD_BLOCKS : c.g_spmv;
     T* pq = fold ? c.part + PART_TOTAL : c.part + PART_A;
     const dim3 gs(fold ? fold_sums(c.n) : c.g_spmv), bs(SPMV_BLOCK), gv(c.g_vec), bv(VEC_BLOCK);

@@ -414,6 +414,19 @@ inline int spmv_grid(int64_t n_rows, int most = SPMV_GRID_MAX) {
     if (g > most) g = most;
     return (int)g;
 }
+// Rows so long that a row group's products do not fit LDS: each thread walks a
+// row of its own, and its lines have to stay in the caches meanwhile.
+inline bool long_rows(int64_t n_rows, int64_t nnz) { return nnz > (int64_t)SPMV_UNROLL * n_rows; }
+// Blocks of a product that leaves no partial sums: one per row group.  With long
+// rows the looping grid where the groups do not all run at once: blocks that
+// start as others end spread over more lines (27-point rows, one block per group /
+// looping: 90^3 rows FP64 628 / 589 us, 140^3 2419 / 2194 and FP32 2235 / 2043;
+// 80^3 numbered at random, 2000 groups, 431 / 455).
+constexpr int64_t SPMV_AT_ONCE = 2048;   // blocks the chip holds
+inline int product_grid(int64_t n_rows, int64_t nnz) {
+    const bool loop = long_rows(n_rows, nnz) && n_rows > SPMV_AT_ONCE * SPMV_BLOCK;
+    return spmv_grid(n_rows, loop ? SPMV_GRID_MAX : INT32_MAX);
+}
 // elementwise kernels: grid-stride loops over at most VEC_GRID_MAX blocks
 constexpr int VEC_GRID_MAX = 1024;  // 512 and 2048 measured slower for K2/K3
 // Systems of at most RP_LOOP_TWO_MAX_ROWS rows get one element per thread, so

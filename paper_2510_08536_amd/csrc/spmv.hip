@@ -3,7 +3,13 @@
 
 namespace rp {
 
-template <typename T, int NW>
+// NT: y is stored non-temporally, so that it leaves x the caches, where it is large
+// (256^3 FP64 226 -> 197 us, 240 -> 214 with two matrices in turn; 200^3 106 -> 95; 201
+// x 150 x 177 FP32, 21 MB, 39.7 -> 39.4); a small one stays in them (numbered at random
+// 64^3 10.7 us against 12.5, 80^3 FP32 19.3 against 20.7)
+constexpr int64_t Y_NT_BYTES = 16 << 20;
+
+template <typename T, int NW, bool NT>
 __global__ void __launch_bounds__(SPMV_BLOCK)
 spmv_kernel(int32_t n_rows, SpmvIdx ix, const T* __restrict__ val, const T* __restrict__ x, T* __restrict__ y,
             XWin w) {
@@ -14,9 +20,10 @@ spmv_kernel(int32_t n_rows, SpmvIdx ix, const T* __restrict__ val, const T* __re
         const int32_t r0 = g * SPMV_BLOCK;
         const int32_t nr = min(SPMV_BLOCK, n_rows - r0);
         const GroupRow<T> gr_ = spmv_group_row<T, NW>(ix, val, x, n_rows, g, nr, w, xs, lds, gr);
-        // y is not read here again: non-temporal, it leaves x the caches (256^3
-        // FP64 247 -> 223 us)
-        if ((int32_t)threadIdx.x < nr) __builtin_nontemporal_store(gr_.s, y + r0 + threadIdx.x);
+        if ((int32_t)threadIdx.x < nr) {
+            if (NT) __builtin_nontemporal_store(gr_.s, y + r0 + threadIdx.x);
+            else y[r0 + threadIdx.x] = gr_.s;
+        }
     }
 }
 
@@ -24,9 +31,15 @@ template <typename T>
 int launch_spmv(rp_plan* p, const T* val, const T* x, T* y, hipStream_t s) {
     if (p->n_rows == 0) return RP_OK;
     const XWin w{{p->xw_d[0], p->xw_d[1]}};
-#define RP_LAUNCH(NW)                                                                                        \
-    hipLaunchKernelGGL((spmv_kernel<T, NW>), dim3(spmv_grid(p->n_rows, INT32_MAX)), dim3(SPMV_BLOCK), 0, s, \
-                       (int32_t)p->n_rows, spmv_idx(p), val, x, y, w)
+    const dim3 grid(product_grid(p->n_rows, p->nnz));
+    const bool nt = p->n_rows * (int64_t)sizeof(T) > Y_NT_BYTES;
+#define RP_LAUNCH(NW)                                                                                 \
+    if (nt)                                                                                           \
+        hipLaunchKernelGGL((spmv_kernel<T, NW, true>), grid, dim3(SPMV_BLOCK), 0, s, (int32_t)p->n_rows, \
+                           spmv_idx(p), val, x, y, w);                                                \
+    else                                                                                              \
+        hipLaunchKernelGGL((spmv_kernel<T, NW, false>), grid, dim3(SPMV_BLOCK), 0, s, (int32_t)p->n_rows, \
+                           spmv_idx(p), val, x, y, w)
     RP_DISPATCH_NW(p->xw_mode, RP_LAUNCH);
 #undef RP_LAUNCH
     RP_HIP_TRY(hipGetLastError());

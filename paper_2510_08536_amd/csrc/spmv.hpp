@@ -47,7 +47,7 @@
 // for global loads (lds_barrier).
 //
 // What bounds it is memory: 1.24 GB at 256^3 FP64 in 202 us, 6.1 TB/s.  A block
-// per group measured fastest, at every size from some thousand groups on
+// per group measured fastest where a group's products fit LDS (product_grid)
 // (256^3 FP64 218 us with 1536 blocks, 208 with 8192, 202 with 65536; FP32 139,
 // 128, 118; 201 x 150 x 177 FP32 45.5, 40.7, 37.6): the chip then always has a
 // block whose loads are not out yet.  A block that loops has all its waves wait
