@@ -316,15 +316,17 @@ int launch_update_gather(rp_plan* p, const double* const* table, bool lower_give
     }
     const int64_t n_pos = p->n_slots;
     if (n_pos == 0 && p->n_rows == 0) return RP_OK;
-    // One round of the 2048 blocks the chip holds, or two.  With one, the last
+    // One round of the 2048 blocks the chip holds, or more.  With one, the last
     // blocks of a long update end far apart; with two, each block's search for its
     // ranks counts, and shorter updates pay for it (2048 / 4096 blocks: 600 000 rows
     // in a slab 24 / 26 us, 128^3 65 / 66, 200 x 190 x 210 320 / 330, 224^3 471 / 453,
     // 256^3 690 / 653; 3072 765, 6144 691).  Without a pattern in the numbering chunks
-    // differ more (27-point rows 64 x 63 x 62 34 / 37, 90^3 110 / 84; numbered at
-    // random 100^3 52 / 51, 120 x 118 x 116 105 / 97, 180^3 433 / 369).
+    // differ more (numbered at random 100^3 52 / 51, 120 x 118 x 116 105 / 97, 180^3
+    // 433 / 369), and with long rows most (2048 / 4096 / 8192: 27-point rows 64 x 63 x
+    // 62 34 / 37, 80^3 74 / 59 / 61, 100^3 121 / 119 / 104, 140^3 449 / 444 / 435).
     const bool pattern = 2 * p->coded_groups > p->n_groups;
-    const int most = n_pos > (pattern ? 1 << 26 : 1 << 23) ? 4096 : 2048;
+    const bool longest = long_rows(p->n_rows, p->nnz) && n_pos > 1 << 24;
+    const int most = n_pos <= (pattern ? 1 << 26 : 1 << 23) ? 2048 : longest ? 8192 : 4096;
     const int g = (grid_for(std::max<int64_t>(n_pos, p->n_rows), 256, most) + N_XCD - 1) / N_XCD * N_XCD;
     RP_TRY(timing_begin(p, RP_KERNEL_SCATTER, s));
     hipLaunchKernelGGL(gather_kernel, dim3(g), dim3(256), 0, s, (int32_t)n_pos, (int32_t)p->n_rows, p->alpha,
