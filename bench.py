@@ -132,7 +132,7 @@ def main():
 
     import torch
     from paper_2510_08536_amd import (Plan, default_opts, RP_KERNEL_SPMV64, RP_KERNEL_SPMV32, RP_KERNEL_SCATTER,
-                                      RP_LOOP_AUTO, RP_LOOP_COOPERATIVE, RP_LOOP_THREE, RP_LOOP_TWO_MAX_ROWS)
+                                      RP_LOOP_AUTO, RP_LOOP_COOPERATIVE, RP_LOOP_THREE)
 
     assert torch.cuda.is_available()
     dev = torch.device("cuda:0")
@@ -340,14 +340,12 @@ def main():
         plan.update(*steps_vals[n_steps_total - 1])
         bj["amg_hierarchy"] = amg_info
     print(f"[bench] preconditioners: {bj}", flush=True)
-    # launches per CG iteration (kernel timing off in all): three, two (the
-    # x and p update fused with the next SpMV; systems of at most
-    # RP_LOOP_TWO_MAX_ROWS rows) and one cooperative launch; per-iteration
-    # time, on systems of up to 2^20 rows
+    # launches of CG (kernel timing off in all): three per iteration, the
+    # library's default (all iterations in one launch where the system fits
+    # it) and one cooperative launch with barriers; per-iteration time, on
+    # systems of up to 2^20 rows
     loop = {}
-    forms = [(RP_LOOP_THREE, "three_kernel"), (RP_LOOP_COOPERATIVE, "single_launch")]
-    if n <= RP_LOOP_TWO_MAX_ROWS:
-        forms.insert(1, (RP_LOOP_AUTO, "two_launch"))
+    forms = [(RP_LOOP_THREE, "three_kernel"), (RP_LOOP_AUTO, "default"), (RP_LOOP_COOPERATIVE, "single_launch")]
     for prec in (() if a.no_loop_legs or n > (1 << 20) else ("fp64", "mixed")):
         for fl, label in forms:
             kw = dict(tol=1e-8, x0_zero=1, precision=prec, fused_loop=fl)
@@ -456,9 +454,10 @@ def main():
                                          "built once: amg_hierarchy.setup_ms; a value update refreshes the "
                                          "coarse values: refresh_ms)"),
         "cg_loop": dict(loop, note="last timestep's system, x0 = 0, tol 1e-8, 3 solves each (median); "
-                                   "three_kernel: one launch per phase; two_launch: the x and p update "
-                                   "fused with the next SpMV (systems of at most 2^18 rows); single_launch: "
-                                   "the iterations in one cooperative launch with grid-wide barriers")
+                                   "three_kernel: one launch per phase, as the legs with kernel timing run; "
+                                   "default: RP_LOOP_AUTO, all iterations in one launch that exchanges values "
+                                   "where the system fits it; single_launch: the iterations in one cooperative "
+                                   "launch with grid-wide barriers")
         if loop else None,
         "fp64_warm_start": ({"ms_per_solve": round(float(np.median([wm for wm, _ in warm])), 3),
                              "iters": int(np.median([wi for _, wi in warm])),

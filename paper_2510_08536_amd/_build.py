@@ -23,7 +23,11 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # kernels keep a thread's rows or taps in arrays that are only ever indexed
          # by constants; this pass would make each one register tuple, copied
-         # whole (and waited for) wherever paths join
+         # whole (and waited for) wherever paths join.  Without it the FP32 SpMVs
+         # take 50 registers instead of 64, and the tiled loops of many rows a
+         # thread spill 118 instead of 2192; of the other kernels one takes more
+         # by a step of occupancy (FP32 block-Jacobi of 8 rows across wavefronts:
+         # 103 us an iteration at 4 million rows before, 98 now)
          "-mllvm", "-disable-promote-alloca-to-vector",
          "-Wall", "-Wno-unused-function", "-I", INCLUDE]
 

@@ -185,8 +185,9 @@ cg_finalize(int32_t mode, int32_t k, int32_t max_iter, T tol2, T pause_frac2, in
 
 // K1: q = A p; partials of (p, q) -> pq, one per block.  A q larger than
 // Q_NT_BYTES is stored non-temporally: it would not wait for K2 in the caches
-// and pushes p out of them (an iteration FP64 480 -> 458 us at 256^3, 221 -> 215
-// at 8 million rows; FP32 247 -> 245.5 at 256^3, but 119 -> 120 at 8 million).
+// and pushes p out of them (an iteration FP64 480 -> 458 us at 256^3, q 134 MB, 221
+// -> 215 at 8 million rows, 64 MB; FP32 247 -> 245.5 at 256^3, 67 MB).  A smaller one
+// waits there: FP32 at 8 million rows, 32 MB, 119 us against 120 non-temporally.
 constexpr int64_t Q_NT_BYTES = 48 << 20;
 template <typename T, int NW>
 __global__ void __launch_bounds__(SPMV_BLOCK)
