@@ -46,8 +46,9 @@ enum : uint32_t {
 };
 // plan->d_flags[1]: set when the last update produced a non-symmetric matrix
 // (upper != lower, or an interface value != its partner's)
-// plan->d_flags[2]: updates that have run (read_flags)
-constexpr int N_FLAGS = 3;
+// plan->d_flags[2]: updates that have run (read_flags); [3]: nothing, 16 bytes are
+// read back faster than 12
+constexpr int N_FLAGS = 4;
 constexpr int LOOP_ABORT = N_FLAGS;   // word of plan->h_flags: abort word of a one-launch loop
 
 // ---------------------------------------------------------------------------
