@@ -32,8 +32,9 @@ constexpr int GCHUNK = GU * VEC_BLOCK;     // items per block
 // same in every lane.  The chunks in flight on a die are neighbours
 // (xcd_block), so the cells a plane away are in its L2; small chunks keep that
 // window short.  Bound by the stream of g and the addressing (8 bytes written
-// per slot, 8 read per face): 200 x 190 x 210 cells 377 -> 180 us (4.2 TB/s),
-// 60 x 61 x 65 cells 58 -> 11, numbered at random 130 x 140 x 150 333 -> 114.
+// per slot, 8 read per face): 200 x 190 x 210 cells 378 -> 194 us (180 on the same
+// inputs again, 4.2 TB/s), 60 x 61 x 65 cells 58 -> 11, numbered at random 130 x 140
+// x 150 333 -> 114.
 // With blocks on the dies in turn 224 and 223 us; with 8192 items per block
 // 236 and 138 us.
 __global__ void __launch_bounds__(VEC_BLOCK)
